@@ -214,14 +214,16 @@ rla_status check_workspace(const Workspace& w, void* ws, size_t bytes) {
   return RLA_OK;
 }
 
-hipError_t build_tables(const Problem& pr, const Workspace& w, unsigned char* ws,
-                        hipStream_t stream) {
+// Varlen: the tables (build), and zeros in the rows of gaps' arrays outside
+// every sequence.
+hipError_t build_tables(const Problem& pr, const Workspace& w, unsigned char* ws, bool build,
+                        const GapRows& gaps, hipStream_t stream) {
   if (!pr.varlen || pr.N == 0) return hipSuccess;
   return launch_seq_table(pr.cu, (int32_t)pr.N, pr.ntok, (int32_t)pr.max_chunks,
                           reinterpret_cast<SeqInfo*>(ws + w.seqs),
                           reinterpret_cast<ChunkInfo*>(ws + w.chunks),
                           reinterpret_cast<int32_t*>(ws + w.nchunks),
-                          reinterpret_cast<int32_t*>(ws + w.order), stream);
+                          reinterpret_cast<int32_t*>(ws + w.order), build, gaps, stream);
 }
 
 rla_status forward(bool rdn, const rla_problem* problem, const void* q, const void* k,
@@ -252,10 +254,9 @@ rla_status forward(bool rdn, const rla_problem* problem, const void* q, const vo
   p.o = o; p.S_fin = S_final; p.R_fin = R_final;
   if (pr.save) set_saved(pr, w, ws, p);
 
-  hipError_t e = hipSuccess;
-  if (pr.varlen && pr.ntok > 0)   // tokens outside every sequence read as zero
-    e = launch_zero_fill(o, (size_t)pr.ntok * pr.H * pr.DV * (pr.out_bf16 ? 2 : 4), stream);
-  if (e == hipSuccess) e = build_tables(pr, w, ws, stream);
+  GapRows gaps;   // tokens outside every sequence read as zero
+  if (pr.ntok > 0) gaps.add(o, (size_t)pr.H * pr.DV * (pr.out_bf16 ? 2 : 4));
+  hipError_t e = build_tables(pr, w, ws, /*build=*/true, gaps, stream);
   if (e == hipSuccess) e = mark_stage(stream, true);
   if (e == hipSuccess && (pr.vflags & kVarQkNorm)) {   // q, k -> SiLU + L2 norm rows
     e = launch_qk_norm_fwd(q, k, ws + w.qh, ws + w.kh, pr.ntok * pr.H, (int)pr.DK, pr.bf16, stream);
@@ -304,20 +305,19 @@ rla_status backward(bool rdn, const rla_problem* problem, const void* q, const v
   p.dalpha_s = dalpha_s; p.dbeta = dbeta; p.dalpha_r = dalpha_r; p.dgamma = dgamma;
   p.dS0 = dS0; p.dR0 = dR0;
 
-  hipError_t e = hipSuccess;
-  if (pr.varlen && pr.ntok > 0) {   // tokens outside every sequence get zero gradients
-    const size_t el = pr.out_bf16 ? 2 : 4, tok = (size_t)pr.ntok * pr.H;
-    e = launch_zero_fill(dq, tok * pr.DK * el, stream);
-    if (e == hipSuccess) e = launch_zero_fill(dk, tok * pr.DK * el, stream);
-    if (e == hipSuccess) e = launch_zero_fill(dv, tok * pr.DV * el, stream);
-    if (e == hipSuccess) e = launch_zero_fill(dalpha_s, tok * 4, stream);
-    if (e == hipSuccess) e = launch_zero_fill(dbeta, tok * 4, stream);
-    if (e == hipSuccess) e = launch_zero_fill(dalpha_r, tok * 4, stream);
-    if (e == hipSuccess) e = launch_zero_fill(dgamma, tok * 4, stream);
-  }
-  if (e == hipSuccess && !pr.use_saved) e = build_tables(pr, w, ws, stream);
-  if (e == hipSuccess) e = mark_stage(stream, true);
   const bool qkn = (pr.vflags & kVarQkNorm) != 0;
+  GapRows gaps;   // tokens outside every sequence get zero gradients
+  if (pr.ntok > 0) {
+    const size_t el = pr.out_bf16 ? 2 : 4, H = (size_t)pr.H;
+    // (with qkn the rows of dq, dk come from the fp32 gradients of the
+    // normalised rows in the workspace, whose gaps are zero)
+    gaps.add(qkn ? ws + w.dqh : dq, H * pr.DK * (qkn ? 4 : el));
+    gaps.add(qkn ? ws + w.dkh : dk, H * pr.DK * (qkn ? 4 : el));
+    gaps.add(dv, H * pr.DV * el);
+    for (float* g : {dalpha_s, dbeta, dalpha_r, dgamma}) gaps.add(g, H * 4);
+  }
+  hipError_t e = build_tables(pr, w, ws, /*build=*/!pr.use_saved, gaps, stream);
+  if (e == hipSuccess) e = mark_stage(stream, true);
   if (qkn) {   // the chunked path reads the normalised rows (saved by a saving forward)
     if (e == hipSuccess && !pr.use_saved)
       e = launch_qk_norm_fwd(q, k, ws + w.qh, ws + w.kh, pr.ntok * pr.H, (int)pr.DK, pr.bf16, stream);
@@ -327,18 +327,9 @@ rla_status backward(bool rdn, const rla_problem* problem, const void* q, const v
     // the gradient kernel writes d(normalised q, k) in fp32 into the workspace
     p.dq = ws + w.dqh;
     p.dk = ws + w.dkh;
-    if (e == hipSuccess && pr.varlen) {   // rows outside every sequence stay zero
-      const size_t bytes = (size_t)pr.ntok * pr.H * pr.DK * 4;
-      e = launch_zero_fill(ws + w.dqh, bytes, stream);
-      if (e == hipSuccess) e = launch_zero_fill(ws + w.dkh, bytes, stream);
-    }
   }
   const bool pre = (pr.vflags & kVarGatePreact) != 0;
-  if (pre) {
-    p.decay_partials = reinterpret_cast<float*>(ws + w.dpart);
-    if (e == hipSuccess)
-      e = launch_zero_fill(ws + w.dpart, sizeof(float) * (size_t)pr.max_chunks * pr.H * 2, stream);
-  }
+  if (pre) p.decay_partials = reinterpret_cast<float*>(ws + w.dpart);
   if (!pr.use_saved) {
     if (e == hipSuccess) e = launch_prep(p, pr.bf16, stream);
     if (e == hipSuccess) e = mark_stage(stream, false);
@@ -363,7 +354,7 @@ rla_status backward(bool rdn, const rla_problem* problem, const void* q, const v
                            reinterpret_cast<const float*>(ws + w.dkh), dq, dk, pr.ntok * pr.H,
                            (int)pr.DK, pr.bf16, pr.out_bf16, stream);
   if (e == hipSuccess && pre && pr.decay_param_grad)
-    e = launch_decay_grad_reduce(p.decay_partials, (int)pr.max_chunks, (int)pr.H,
+    e = launch_decay_grad_reduce(p.decay_partials, (int)pr.max_chunks, p.st.nchunks, (int)pr.H,
                                  pr.decay_param_grad, stream);
   if (e == hipSuccess) e = mark_stage(stream, false);
   return to_status(e);

@@ -96,14 +96,26 @@ struct OpParams {
   float* grad_scale = nullptr;
 };
 
-// Zeroes `bytes` (a multiple of 4) at dst with a kernel rather than a memset
-// node, so that a caller may capture the call in a HIP graph.
-hipError_t launch_zero_fill(void* dst, size_t bytes, hipStream_t stream);
+// Token-major arrays whose rows outside every sequence are to read as zero:
+// base pointers and 4-byte words per token row.
+struct GapRows {
+  static constexpr int kMax = 7;
+  void* dst[kMax];
+  int64_t row_words[kMax];
+  int n = 0;
+  void add(void* p, size_t row_bytes) {
+    dst[n] = p;
+    row_words[n++] = (int64_t)(row_bytes / 4);
+  }
+};
 
-// Builds SeqInfo / ChunkInfo / order tables from device cu_seqlens.
+// Builds SeqInfo / ChunkInfo / order tables from device cu_seqlens (build;
+// otherwise they are there already) and zeroes the rows of `gaps`' tokens
+// outside every sequence, with kernels rather than memset nodes, so that a
+// caller may capture the call in a HIP graph.  nseq > 0.
 hipError_t launch_seq_table(const int32_t* cu, int32_t nseq, int64_t ntok, int32_t max_chunks,
                             SeqInfo* seqs, ChunkInfo* chunks, int32_t* nchunks, int32_t* order,
-                            hipStream_t stream);
+                            bool build, const GapRows& gaps, hipStream_t stream);
 
 // Chunk-parallel preparation: gate cumsums, masked decayed Gram/score
 // matrices and (RDN) the two triangular inverses.
@@ -136,9 +148,10 @@ hipError_t launch_qk_norm_bwd(const void* q, const void* k, const float* dqh, co
                               hipStream_t stream);
 
 // Sums the gradient kernel's per-chunk (a, b) partials over chunks per head:
-// out[h] = sum_c partials[c][h][0], out[H + h] = sum_c partials[c][h][1].
-hipError_t launch_decay_grad_reduce(const float* partials, int nch, int H, float* out,
-                                    hipStream_t stream);
+// out[h] = sum_c partials[c][h][0], out[H + h] = sum_c partials[c][h][1], over
+// the chunks there are (*nchunks on the device, or max_chunks without it).
+hipError_t launch_decay_grad_reduce(const float* partials, int max_chunks, const int32_t* nchunks, int H,
+                                    float* out, hipStream_t stream);
 
 // Recurrent step over T tokens per sequence (dense layout, st.dense_T = T,
 // st.nseq = B) with S0/R0 in (NULL = zeros) and S_fin/R_fin out.

@@ -95,10 +95,12 @@ __global__ __launch_bounds__(kThreads) void qk_norm_bwd_kernel(const IN* __restr
 }
 
 __global__ __launch_bounds__(kThreads) void decay_grad_reduce_kernel(const float* __restrict__ part,
-                                                                     int nch, int H,
-                                                                     float* __restrict__ out) {
+                                                                     int max_chunks,
+                                                                     const int32_t* __restrict__ nchunks,
+                                                                     int H, float* __restrict__ out) {
   __shared__ float ra[kThreads], rb[kThreads];
   const int h = blockIdx.x, tid = threadIdx.x;
+  const int nch = nchunks ? min(*nchunks, max_chunks) : max_chunks;   // every chunk's partials are written
   float a = 0.f, b = 0.f;
   for (int c = tid; c < nch; c += kThreads) {
     a += part[((int64_t)c * H + h) * 2 + 0];
@@ -165,11 +167,11 @@ hipError_t launch_qk_norm_bwd(const void* q, const void* k, const float* dqh, co
                    : qk_bwd_t<float, float, 64>(q, k, dqh, dkh, dq, dk, rows, stream);
 }
 
-hipError_t launch_decay_grad_reduce(const float* partials, int nch, int H, float* out,
-                                    hipStream_t stream) {
+hipError_t launch_decay_grad_reduce(const float* partials, int max_chunks, const int32_t* nchunks, int H,
+                                    float* out, hipStream_t stream) {
   if (H == 0) return hipSuccess;
-  hipLaunchKernelGGL(decay_grad_reduce_kernel, dim3(H), dim3(kThreads), 0, stream, partials, nch,
-                     H, out);
+  hipLaunchKernelGGL(decay_grad_reduce_kernel, dim3(H), dim3(kThreads), 0, stream, partials,
+                     max_chunks, nchunks, H, out);
   return hipGetLastError();
 }
 
