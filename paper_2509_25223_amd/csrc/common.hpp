@@ -63,6 +63,17 @@ __device__ __forceinline__ void bf16_split2(float a, float b, uint32_t& hi, uint
   lo = __builtin_bit_cast(uint32_t, bf16x2{(__bf16)ra, (__bf16)rb});
 }
 
+// Eight fp16 values as bf16 hi + lo (exact: 11 significant bits = 8 + 3; the
+// values of normalised rows lie well inside bf16's range).
+__device__ __forceinline__ void f16_split8(f16x8 x, bf16x8& hi, bf16x8& lo) {
+  typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+  uint32_t h[4], l[4];
+#pragma unroll
+  for (int e = 0; e < 4; ++e) bf16_split2((float)x[2 * e], (float)x[2 * e + 1], h[e], l[e]);
+  hi = __builtin_bit_cast(bf16x8, u32x4{h[0], h[1], h[2], h[3]});
+  lo = __builtin_bit_cast(bf16x8, u32x4{l[0], l[1], l[2], l[3]});
+}
+
 // ---------------------------------------------------------------------------
 // MFMA 16x16 tiles.  One wave computes D[16 x 16] += A[16 x K] * B[K x 16].
 //   bf16 (T = u16): v_mfma_f32_16x16x32_bf16, 8 k-values per lane per step.
@@ -953,6 +964,11 @@ __device__ __forceinline__ float resid_tanh(float x, float c) {
 
 __device__ __forceinline__ uint32_t cvt_pk_f16(float a, float b) {
   return __builtin_bit_cast(uint32_t, f16x2{to_f16(a), to_f16(b)});
+}
+
+// Two fp32 values given as bits, rounded to a bf16 pair.
+__device__ __forceinline__ uint32_t cvt_pk_bf16(uint32_t a, uint32_t b) {
+  return __builtin_bit_cast(uint32_t, bf16x2{(__bf16)__uint_as_float(a), (__bf16)__uint_as_float(b)});
 }
 
 // Packs two adjacent 16 x 16 accumulator tiles (a0: columns 0..15, a1:

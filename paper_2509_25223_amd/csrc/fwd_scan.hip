@@ -621,8 +621,9 @@ __global__ __launch_bounds__(kThreads) void fwd_scan_kernel(OpParams p) {
 }
 
 // ---------------------------------------------------------------------------
-// Wave-specialised forward scan: bf16 inputs, d_k = 128, 32 value columns,
-// the boxed operator (no variant flags).  Eight waves per workgroup in two
+// Wave-specialised forward scan: bf16 inputs, 32 value columns, the boxed
+// operator (no variant flags); Q16: q, k are the fp16 rows of the in-operator
+// normalisation.  Eight waves per workgroup in two
 // groups of four that pass the same barriers in the same order:
 //   chain waves (0-3): hold S and R (rows 32 w' .. 32 w' + 31) in their
 //     accumulators and do every product of the chunk (the algebra of
@@ -649,7 +650,8 @@ __global__ __launch_bounds__(kThreads) void fwd_scan_kernel(OpParams p) {
 // and the arithmetic are those of fwd_scan_kernel, except that the split-
 // state products sum the hi and lo terms per k-step and the checkpoints are
 // formed from the bf16 hi + lo state copies (the fp32 state to ~16 bits)
-// instead of the accumulators.
+// instead of the accumulators.  Q16 rows are split as bf16 hi + lo in the
+// chain's registers (a third MFMA adds lo x state-hi).
 // ---------------------------------------------------------------------------
 template <typename IN, int DK, int BV, bool RDN>
 struct FwdWsLayout {
@@ -672,12 +674,12 @@ struct FwdWsLayout {
   static constexpr int kMst = kRst + kBufBytes;
   static constexpr int kGraw = kMst + kChunk * BV;      // the gate block (one side wave's DMA)
   static constexpr int kZero = kGraw + kGateBlock * 4;   // 16 zero bytes (blocks above the diagonal)
-  // fp32 outputs: o of a chunk, column-major [BV][kOstLd] (the pad keeps the
-  // side's 4-byte gathers of one token's 4 columns in distinct banks)
+  // o of a chunk in fp32, column-major [BV][kOstLd] (the pad keeps the side's
+  // 4-byte gathers of one token's 4 columns in distinct banks)
   static constexpr int kOstLd = kChunk + 4;
   static constexpr int kOst = kZero + 16;
   static constexpr int kBytes = kOst + BV * kOstLd * 4;
-  static_assert(sizeof(IN) == 2 && DK == 128 && BV == 32, "bf16, d_k 128, 32 columns");
+  static_assert(sizeof(IN) == 2 && BV == 32, "bf16, 32 columns");
   static_assert(kVBytes == 4 * 1024, "V block = one DMA instruction per side wave");
   static_assert(kBytes <= 160 * 1024, "forward scan LDS");
   // RDN: T^S, then MG, MP, T^R, MR each double-buffered; RLA: MG, MP, MR
@@ -695,7 +697,7 @@ struct FwdWsLayout {
   }
 };
 
-template <typename IN, int DK, int BV, bool RDN, bool WRITE_O, bool CKPT, typename OT>
+template <typename IN, int DK, int BV, bool RDN, bool WRITE_O, bool CKPT, bool Q16>
 __global__ __launch_bounds__(2 * kThreads) void fwd_scan_ws_kernel(OpParams p) {
   typedef FwdWsLayout<IN, DK, BV, RDN> L;
   typedef typename L::XT XT;
@@ -746,7 +748,6 @@ __global__ __launch_bounds__(2 * kThreads) void fwd_scan_ws_kernel(OpParams p) {
   const IN* qg = reinterpret_cast<const IN*>(p.q);
   const IN* kg = reinterpret_cast<const IN*>(p.k);
   const IN* vg = reinterpret_cast<const IN*>(p.v);
-  OT* og = reinterpret_cast<OT*>(p.o);
   const XT* matg = reinterpret_cast<const XT*>(p.mat_ws);
   XT* fblk = reinterpret_cast<XT*>(p.fwd_blk);   // CKPT: U, UR, r blocks
   auto chunk_len = [&](int c) { return min(kChunk, si.len - c * kChunk); };
@@ -885,17 +886,20 @@ __global__ __launch_bounds__(2 * kThreads) void fwd_scan_ws_kernel(OpParams p) {
       *reinterpret_cast<uint4*>(dst + (uint32_t)((t0 + (lane & 15)) * 32 + 8 * (lane >> 4))) = v;
       sc[it] = exp2_int(ex);
     }
-    static_assert(IT == 2, "two tiles per wave");
+    static_assert(IT <= 2, "one or two tiles per wave");
     const int64_t so = ((int64_t)gc * H + h) * (DK / 16) * (DV / 32) + j0 / 32;
     if (lane < IT)   // one lane per tile scale
-      (st ? p.ck_R_sc : p.ck_S_sc)[so + (int64_t)(ww * IT + lane) * (DV / 32)] = lane ? sc[1] : sc[0];
+      (st ? p.ck_R_sc : p.ck_S_sc)[so + (int64_t)(ww * IT + lane) * (DV / 32)] = lane ? sc[IT - 1] : sc[0];
   };
 
   // KS, KR, QS, QR for this wave's 16 token rows (K, Q as A fragments)
   // from the state copies: each B fragment read once serves the K and the Q
   // product; eight independent MFMA chains (value tile x state x K/Q), each
-  // adding the hi and the lo product of every k-step
+  // adding the hi and the lo product of every k-step (Q16: also the residual
+  // of the rows times hi)
+  constexpr int KL_STEPS = Q16 ? KS_STEPS : 1;
   auto split_products = [&](const typename MI::frag (&kf)[KS_STEPS], const typename MI::frag (&qf)[KS_STEPS],
+                            const typename MI::frag (&kl)[KL_STEPS], const typename MI::frag (&ql)[KL_STEPS],
                             floatx4 (&ks)[JT], floatx4 (&kr)[JT], floatx4 (&qs)[JT], floatx4 (&qr)[JT]) {
 #pragma unroll
     for (int jt = 0; jt < JT; ++jt) ks[jt] = kr[jt] = qs[jt] = qr[jt] = zero4();
@@ -916,31 +920,38 @@ __global__ __launch_bounds__(2 * kThreads) void fwd_scan_ws_kernel(OpParams p) {
         qs[jt] = MI::mma(qf[s2], sl, qs[jt]);
         kr[jt] = MI::mma(kf[s2], rl, kr[jt]);
         qr[jt] = MI::mma(qf[s2], rl, qr[jt]);
+        if constexpr (Q16) {
+          ks[jt] = MI::mma(kl[s2], sh, ks[jt]);
+          qs[jt] = MI::mma(ql[s2], sh, qs[jt]);
+          kr[jt] = MI::mma(kl[s2], rh, kr[jt]);
+          qr[jt] = MI::mma(ql[s2], rh, qr[jt]);
+        }
       }
   };
 
-  // o leaves through LDS regions that are free from phase 5 until the side
-  // waves read them in the next chunk's phase 1: value tile 0 in chunk c's
-  // V block, tile 1 in the r block; wave ww's 16 rows as 1 KiB at ww KiB,
-  // row-major [16][16] in OT.  The side wave reads its slice of the V block
-  // before its own DMA refills that slice.
-  auto ostage = [&](int c, int jt) {
-    return reinterpret_cast<char*>(jt ? reinterpret_cast<char*>(Rst) : reinterpret_cast<char*>(vblk(c))) + ww * 1024;
-  };
-  // fp32 o from the column-major stage: four 4-byte reads give a lane 4
-  // columns of one token
+  // o from the column-major stage: four 4-byte reads give a lane 4 columns of
+  // one token (bf16: eight reads, 8 columns)
   float* ost = reinterpret_cast<float*>(smem + L::kOst);
   auto store_o = [&](int c) {   // side waves: chunk c's o rows 16 ww .. 16 ww + 15
-    constexpr int kVE = 16 / (int)sizeof(OT);   // elements per 16 bytes
     const int64_t tok = si.start + (int64_t)c * kChunk;
     const int len = chunk_len(c);
-    const int t = 16 * ww + lane / (16 / kVE), col = (lane % (16 / kVE)) * kVE;
+    const int64_t ob = (tok * H + h) * (int64_t)DV + j0;
+    const int t = 16 * ww + (lane >> 2);
+    if (p.out_bf16) {
+      static_assert(BV == 32, "four lanes per bf16 row");
+      const int col = 8 * (lane & 3);
+      const uint4 a = lds_read4x1_sync(ost + col * L::kOstLd + t, L::kOstLd * 4);
+      const uint4 b = lds_read4x1_sync(ost + (col + 4) * L::kOstLd + t, L::kOstLd * 4);
+      const uint4 v = {cvt_pk_bf16(a.x, a.y), cvt_pk_bf16(a.z, a.w), cvt_pk_bf16(b.x, b.y), cvt_pk_bf16(b.z, b.w)};
+      if (t < len) *reinterpret_cast<uint4*>(reinterpret_cast<u16*>(p.o) + ob + (uint32_t)(t * H * DV + col)) = v;
+    } else {
+      const int col = 4 * (lane & 3);
 #pragma unroll
-    for (int jt = 0; jt < JT; ++jt) {
-      const uint4 v = sizeof(OT) == 4 ? lds_read4x1_sync(ost + (jt * 16 + col) * L::kOstLd + t, L::kOstLd * 4)
-                                      : lds_read16_sync(ostage(c, jt) + (lane % (16 * 16 / kVE)) * 16);
-      if (lane < 16 * 16 / kVE && t < len)
-        *reinterpret_cast<uint4*>(og + (tok * H + h) * (int64_t)DV + j0 + jt * 16 + (uint32_t)(t * H * DV + col)) = v;
+      for (int jt = 0; jt < JT; ++jt) {
+        const uint4 v = lds_read4x1_sync(ost + (jt * 16 + col) * L::kOstLd + t, L::kOstLd * 4);
+        if (t < len)
+          *reinterpret_cast<uint4*>(reinterpret_cast<float*>(p.o) + ob + jt * 16 + (uint32_t)(t * H * DV + col)) = v;
+      }
     }
   };
 
@@ -980,19 +991,25 @@ __global__ __launch_bounds__(2 * kThreads) void fwd_scan_ws_kernel(OpParams p) {
 
     // ======== phase 1 ========
     if constexpr (CH) {
-      typename MI::frag Kf[KS_STEPS], Qf[KS_STEPS];
+      typename MI::frag Kf[KS_STEPS], Qf[KS_STEPS], Kl[KL_STEPS], Ql[KL_STEPS];
       const int t = 16 * ww + (lane & 15);
 #pragma unroll
       for (int s2 = 0; s2 < KS_STEPS; ++s2) {   // K^T commit: row t, 8 columns per store
-        Kf[s2] = Kn[s2];
-        Qf[s2] = Qn[s2];
-        const u16x8 kv = __builtin_bit_cast(u16x8, Kf[s2]);
         f16x8 kh;
+        if constexpr (Q16) {
+          kh = __builtin_bit_cast(f16x8, Kn[s2]);
+          f16_split8(kh, Kf[s2], Kl[s2]);
+          f16_split8(__builtin_bit_cast(f16x8, Qn[s2]), Qf[s2], Ql[s2]);
+        } else {
+          Kf[s2] = Kn[s2];
+          Qf[s2] = Qn[s2];
+          const u16x8 kv = __builtin_bit_cast(u16x8, Kf[s2]);
 #pragma unroll
-        for (int e = 0; e < 8; ++e) kh[e] = (f16)bf2f(kv[e]);
+          for (int e = 0; e < 8; ++e) kh[e] = (f16)bf2f(kv[e]);
+        }
         *reinterpret_cast<f16x8*>(TK::ptr(KT, t, s2 * 32 + (lane >> 4) * 8)) = kh;
       }
-      split_products(Kf, Qf, KS, KR, QS, QR);
+      split_products(Kf, Qf, Kl, Ql, KS, KR, QS, QR);
 #pragma unroll
       for (int jt = 0; jt < JT; ++jt) {
         const u16x4 v4 = acc_tile_tr<PadRows<IN, BV, 0>>(vblk(c), 16 * ww, jt * 16);
@@ -1017,7 +1034,7 @@ __global__ __launch_bounds__(2 * kThreads) void fwd_scan_ws_kernel(OpParams p) {
       else aMG = packed_rows_frags(mat(kMatMG, buf), ww, zero16);
     } else {
       if constexpr (WRITE_O) {
-        if (c > 0) store_o(c - 1);   // before the DMA below refills chunk c - 1's V block
+        if (c > 0) store_o(c - 1);
       }
       if (more) {
         issue_early(c + 1);
@@ -1162,19 +1179,8 @@ __global__ __launch_bounds__(2 * kThreads) void fwd_scan_ws_kernel(OpParams p) {
             const int t = 16 * ww + acc_row(r);
             ov[r] = __builtin_fmaf(ggm[t], __builtin_fmaf(egr[t], QR[jt][r], mru[r]), base[jt][r]);
           }
-          if constexpr (sizeof(OT) == 4) {   // this lane's 4 tokens of its column, one store
-            *reinterpret_cast<floatx4*>(ost + (jt * 16 + acc_col()) * L::kOstLd + 16 * ww + acc_row(0)) = ov;
-          } else {
-            // quad transpose: this lane's row 4 (lane / 16) + lane % 4, columns
-            // 4 ((lane % 16) / 4) .. + 3 of the wave's 16 x 16 tile
-            const floatx4 x = quad_transpose(ov);
-            const int row = 4 * (lane >> 4) + (lane & 3), col = 4 * ((lane & 15) >> 2);
-            char* dst = ostage(c, jt) + (row * 16 + col) * (int)sizeof(OT);
-            u16x4 b;
-#pragma unroll
-            for (int k = 0; k < 4; ++k) b[k] = f2bf(x[k]);
-            *reinterpret_cast<u16x4*>(dst) = b;
-          }
+          // this lane's 4 tokens of its column, one store
+          *reinterpret_cast<floatx4*>(ost + (jt * 16 + acc_col()) * L::kOstLd + 16 * ww + acc_row(0)) = ov;
         }
       }
       write_state_copies();
@@ -1210,20 +1216,8 @@ __global__ __launch_bounds__(2 * kThreads) void fwd_scan_ws_kernel(OpParams p) {
   else run(std::false_type{});
 }
 
-template <typename IN, int DK, int BV, bool RDN, bool WRITE_O, bool CKPT, typename OT>
-hipError_t launch_fwd_t(const OpParams& p, hipStream_t stream) {
-  typedef FwdLayout<IN, DK, BV, RDN> L;
-  const bool var = (p.vflags & kVarOperator) || p.qk_f16;
-  auto kern = var ? fwd_scan_kernel<IN, DK, BV, RDN, WRITE_O, CKPT, OT, true>
-                  : fwd_scan_kernel<IN, DK, BV, RDN, WRITE_O, CKPT, OT, false>;
-  int threads = kThreads, lds = L::kBytes;
-  if constexpr (sizeof(IN) == 2 && DK == 128 && BV == 32) {
-    if (!var) {   // the boxed operator: the wave-specialised scan
-      kern = fwd_scan_ws_kernel<IN, DK, BV, RDN, WRITE_O, CKPT, OT>;
-      threads = 2 * kThreads;
-      lds = FwdWsLayout<IN, DK, BV, RDN>::kBytes;
-    }
-  }
+template <typename K>
+hipError_t launch_fwd_kernel(K kern, const OpParams& p, int BV, int threads, int lds, hipStream_t stream) {
   hipError_t err = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
                                        hipFuncAttributeMaxDynamicSharedMemorySize, lds);
   if (err != hipSuccess) return err;
@@ -1235,29 +1229,47 @@ hipError_t launch_fwd_t(const OpParams& p, hipStream_t stream) {
   return hipGetLastError();
 }
 
-template <typename IN, int DK, int BV, typename OT>
+// The operator's variants (log-cosh residual, ungated output, decayed
+// residual) on the four-wave kernel; the boxed operator, with plain or
+// normalised rows, on the wave-specialised one (packed prefill of 20011
+// tokens from raw projections, H = 16, d = 128: 482 us with the four-wave
+// kernel, 397 us here).  fp32 inputs always take the four-wave kernel.
+template <typename IN, int DK, int BV, bool RDN, bool WRITE_O, bool CKPT>
+hipError_t launch_fwd_t(const OpParams& p, hipStream_t s) {
+  typedef FwdLayout<IN, DK, BV, RDN> L;
+  if constexpr (sizeof(IN) == 2) {
+    if (!(p.vflags & kVarOperator)) {
+      auto kern = p.qk_f16 ? fwd_scan_ws_kernel<IN, DK, BV, RDN, WRITE_O, CKPT, true>
+                           : fwd_scan_ws_kernel<IN, DK, BV, RDN, WRITE_O, CKPT, false>;
+      return launch_fwd_kernel(kern, p, BV, 2 * kThreads, FwdWsLayout<IN, DK, BV, RDN>::kBytes, s);
+    }
+    auto kern = p.out_bf16 ? fwd_scan_kernel<IN, DK, BV, RDN, WRITE_O, CKPT, u16, true>
+                           : fwd_scan_kernel<IN, DK, BV, RDN, WRITE_O, CKPT, float, true>;
+    return launch_fwd_kernel(kern, p, BV, kThreads, L::kBytes, s);
+  } else {
+    auto kern = (p.vflags & kVarOperator) ? fwd_scan_kernel<IN, DK, BV, RDN, WRITE_O, CKPT, float, true>
+                                          : fwd_scan_kernel<IN, DK, BV, RDN, WRITE_O, CKPT, float, false>;
+    return launch_fwd_kernel(kern, p, BV, kThreads, L::kBytes, s);
+  }
+}
+
+template <typename IN, int DK, int BV>
 hipError_t launch_fwd_dk(const OpParams& p, bool write_o, bool ckpt, hipStream_t s) {
   if (p.rdn) {
-    if (ckpt) return write_o ? launch_fwd_t<IN, DK, BV, true, true, true, OT>(p, s) : launch_fwd_t<IN, DK, BV, true, false, true, OT>(p, s);
-    return launch_fwd_t<IN, DK, BV, true, true, false, OT>(p, s);
+    if (ckpt) return write_o ? launch_fwd_t<IN, DK, BV, true, true, true>(p, s) : launch_fwd_t<IN, DK, BV, true, false, true>(p, s);
+    return launch_fwd_t<IN, DK, BV, true, true, false>(p, s);
   }
-  if (ckpt) return write_o ? launch_fwd_t<IN, DK, BV, false, true, true, OT>(p, s) : launch_fwd_t<IN, DK, BV, false, false, true, OT>(p, s);
-  return launch_fwd_t<IN, DK, BV, false, true, false, OT>(p, s);
+  if (ckpt) return write_o ? launch_fwd_t<IN, DK, BV, false, true, true>(p, s) : launch_fwd_t<IN, DK, BV, false, false, true>(p, s);
+  return launch_fwd_t<IN, DK, BV, false, true, false>(p, s);
 }
 
 }  // namespace
 
 hipError_t launch_fwd_scan(const OpParams& p, bool bf16, bool write_o, bool ckpt,
                            hipStream_t stream) {
-  if (bf16) {
-    if (p.out_bf16) {
-      if (p.DK == 128) return launch_fwd_dk<u16, 128, 32, u16>(p, write_o, ckpt, stream);
-      return launch_fwd_dk<u16, 64, 32, u16>(p, write_o, ckpt, stream);
-    }
-    if (p.DK == 128) return launch_fwd_dk<u16, 128, 32, float>(p, write_o, ckpt, stream);
-    return launch_fwd_dk<u16, 64, 32, float>(p, write_o, ckpt, stream);
-  }
-  return launch_fwd_dk<float, 64, 16, float>(p, write_o, ckpt, stream);
+  if (!bf16) return launch_fwd_dk<float, 64, 16>(p, write_o, ckpt, stream);
+  if (p.DK == 128) return launch_fwd_dk<u16, 128, 32>(p, write_o, ckpt, stream);
+  return launch_fwd_dk<u16, 64, 32>(p, write_o, ckpt, stream);
 }
 
 }  // namespace rla
