@@ -135,7 +135,7 @@ Workspace plan(const Problem& pr, int op) {
     const size_t sc = pr.bf16 ? sizeof(float) * mc * H * (size_t)(pr.DK / 16) * (size_t)(pr.DV / 32) : 0;
     w.ckS = take(st);
     w.ckR = take(st);
-    w.mask = take((size_t)pr.ntok * H * (size_t)pr.DV);
+    w.mask = take(mc * H * (size_t)pr.DV * kChunk);
     w.dS = take(st);
     w.dR = take(st);
     if (sc) {

@@ -4,19 +4,19 @@
 // the loss with respect to the chunk-END states (consumed by the chunk-
 // parallel gradient kernel) and, at the sequence start, dS0 and dR0.
 //
-// Adjoint of one forward chunk (see fwd_scan.hip for the forward), with
-// db = dO, dc = diag(gamma) dO and the clip mask m from the forward pass:
-//   dUR = diag(e^{h_C-h}) K dR_end + MR^T dc
-//   RDN: dYR = T^R^T dUR            RLA: dYR = dUR
+// Adjoint of one forward chunk (see fwd_scan.hip for the forward; prep's MG,
+// MP, MR are multiplied by T^S, T^S, T^R already), with db = dO, dc =
+// diag(gamma) dO and the clip mask m from the forward pass:
+//   dYR = T^R^T diag(e^{h_C-h}) K dR_end + (MR T^R)^T dc     (RLA: T = I)
 //   dX  = m * (diag(gamma) dYR)     (dr = gamma dYR, then the clip's mask)
 //   dKR = -diag(gamma e^{h}) dYR    (RDN only: UR depends on R0 through KR)
-//   dU  = diag(e^{g_C-g}) K dS_end + MP^T db - MG^T dX
-//   RDN: dY = T^S^T dU              RLA: not needed (U = diag(b) V)
+//   dY  = T^S^T diag(e^{g_C-g}) K dS_end + (MP T^S)^T db - (MG T^S)^T dX
+//   (RLA: this is dU; U = diag(b) V)
 //   dKS = -diag(e^{g_{t-1}}) dX - diag(b e^{g}) dY      (RLA: first term only)
 //   dS_start = e^{g_C} dS_end + Q^T diag(e^{g}) db + K^T dKS
 //   dR_start = e^{h_C} dR_end + Q^T diag(e^{h}) dc + K^T dKR
-// Also written per chunk: dv = dX + diag(b) dY (RLA: dX + diag(b) dU), and
-// the blocks dX, dY (RLA: dU), dYR (RLA: dUR) for the gradient kernel.
+// Also written per chunk: dv = dX + diag(b) dY, and the blocks dX, dY, dYR for
+// the gradient kernel.
 // Variants: ungated output db = e^{g_{t-1}}-weighted (the S_{t-1} q read-out)
 // and dc = dO; decayed residual dKS with e^{g} in place of e^{g_{t-1}};
 // log-cosh residual dX = (1 - (r / c)^2) gamma dYR, r read from the forward's
@@ -95,10 +95,10 @@ struct BwdScanLayout {
 };
 
 // per-token block slots ([BV][64], value-major); aliases follow lifetimes:
-// db is last read in P4 and dKS first written in P5; dc is last read in P2
-// and dX first written in P3; dUR is last read in P3 and dU first written in
-// P4.  RLA keeps dKS in the dKR slot (dKR = 0 there).
-enum { bDB_DKS = 0, bDC_DX = 1, bQDB = 2, bQDC = 3, bDUR_DU = 4, bDKR = 5 };
+// db, dc and the decayed K dS, K dR (KDS, KDR; RDN only) are last read in P2;
+// dX and dKR are written after it (four-wave kernel: in P3), dY and dKS after
+// a further barrier.
+enum { bDB_DKS = 0, bDC_DX = 1, bQDB = 2, bQDC = 3, bKDS_DY = 4, bKDR_DKR = 5 };
 
 // Writes this lane's 4 accumulator rows of a gradient-state tile into the
 // transposed copy (tile rows r0 + column, columns c0 + row) in the operand
@@ -219,16 +219,15 @@ __global__ __launch_bounds__(kThreads) void bwd_scan_kernel(OpParams p) {
   }
 
   floatx4 dS[IT][JT], dR[IT][JT];
+  load_acc_state<IT, JT>(dS, p.dS_fin, state_off + j0, DV, w * (DK / 4));
+  load_acc_state<IT, JT>(dR, p.dR_fin, state_off + j0, DV, w * (DK / 4));
 #pragma unroll
   for (int it = 0; it < IT; ++it)
 #pragma unroll
-    for (int jt = 0; jt < JT; ++jt)
-#pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const int i = w * (DK / 4) + it * 16 + acc_row(r), j = j0 + jt * 16 + acc_col();
-        dS[it][jt][r] = p.dS_fin ? p.dS_fin[state_off + (int64_t)i * DV + j] * sig : 0.f;
-        dR[it][jt][r] = p.dR_fin ? p.dR_fin[state_off + (int64_t)i * DV + j] * sig : 0.f;
-      }
+    for (int jt = 0; jt < JT; ++jt) {
+      dS[it][jt] *= sig;
+      dR[it][jt] *= sig;
+    }
   // Copies of the gradient states for the next chunk's K dS, K dR products.
   // bf16 inputs: fp16, scaled by 2^-e with e from the largest magnitude of
   // each whole state (the waves' maxima meet in LDS across a barrier); the
@@ -284,7 +283,7 @@ __global__ __launch_bounds__(kThreads) void bwd_scan_kernel(OpParams p) {
   // ---- staging of the next (earlier) chunk while this one computes ----
   //   K, Q, dO: register prefetch after P1 (transposed / converted at commit)
   //   gates, MR: LDS-DMA after P1 (MR double-buffered)
-  //   T^R, mask: after P3;  MG, MP: after P4;  T^S: after P5 (their last uses)
+  //   mask, T^R, T^S, MG, MP: after P3 (their last uses are before its end)
   // bf16 inputs; fp32 inputs single-buffer every matrix and move them all
   // after the chunk's last barrier.
   // dO block: one 16-byte vector per thread, token = lane, columns of wave w
@@ -318,7 +317,7 @@ __global__ __launch_bounds__(kThreads) void bwd_scan_kernel(OpParams p) {
       dma_linear_wave(p.gate_ws + ((int64_t)(si.chunk0 + c) * H + h) * kGateBlock, graw,
                       kGateBlock * 4);
   };
-  auto issue_mask = [&](int c) {   // rows of BV bytes; padding rows read row 0 (masked by 0 grads)
+  auto issue_mask = [&](int c) {
     if (tanh_resid) {   // the r block rows of this value block (rows past the end are zero)
       constexpr int kPerRow = BV * (int)sizeof(XT) / 16;
       static_assert(kChunk * kPerRow == kThreads, "r block = one DMA instruction per wave");
@@ -328,37 +327,22 @@ __global__ __launch_bounds__(kThreads) void bwd_scan_kernel(OpParams p) {
       dma16(src, mask + w * 1024);
       return;
     }
-    const int64_t tok = si.start + (int64_t)c * kChunk;
-    const int len = chunk_len(c);
-    constexpr int kPerRow = BV / 16;
-#pragma unroll
-    for (int m = 0; m < kChunk * BV / 1024; ++m) {
-      if (w == m) {
-        const int P = m * 64 + lane, t = P / kPerRow, cc = P % kPerRow;
-        const int ts = t < len ? t : 0;
-        const uint8_t* src = p.ck_mask + ((tok + ts) * H + h) * (int64_t)DV + j0 + cc * 16;
-        dma16(src, mask + m * 1024);
-      }
-    }
+    if (w < BV / 16) dma_mask(p.ck_mask + mask_off(si.chunk0 + c, h, H, DV) + j0 * kChunk, mask, w);
   };
   auto issue_early = [&](int c) {   // after P1
     issue_gates(c);
     if constexpr (L::kDB) dma_mat64<XT>(mat_src(c, kMatMR), mat(kMatMR, c & 1), mdo);
   };
-  auto issue_mid = [&](int c) {     // after P3
+  auto issue_late = [&](int c) {    // after P3
     if constexpr (L::kDB) {
       issue_mask(c);
-      if constexpr (RDN) dma_mat64<XT>(mat_src(c, kMatTR), mat(kMatTR, 0), mdo);
-    }
-  };
-  auto issue_late = [&](int c) {    // after P4
-    if constexpr (L::kDB) {
+      if constexpr (RDN) {
+        dma_mat64<XT>(mat_src(c, kMatTR), mat(kMatTR, 0), mdo);
+        dma_mat64<XT>(mat_src(c, kMatTS), mat(kMatTS, 0), mdo);
+      }
       dma_mat64<XT>(mat_src(c, kMatMG), mat(kMatMG, 0), mdo);
       dma_mat64<XT>(mat_src(c, kMatMP), mat(kMatMP, 0), mdo);
     }
-  };
-  auto issue_after5 = [&](int c) {  // after P5 (RDN)
-    if constexpr (L::kDB && RDN) dma_mat64<XT>(mat_src(c, kMatTS), mat(kMatTS, 0), mdo);
   };
   auto issue_all_single = [&](int c) {   // fp32: everything after the last barrier
     if constexpr (!L::kDB) {
@@ -531,115 +515,115 @@ __global__ __launch_bounds__(kThreads) void bwd_scan_kernel(OpParams p) {
       store_acc_tile<TT>(blk(bQDB), jt * 16, 16 * w, qdb);
       store_acc_tile<TT>(blk(bQDC), jt * 16, 16 * w, qdc);
     }
+    if constexpr (RDN) {   // operands of T^S^T, T^R^T
+#pragma unroll
+      for (int jt = 0; jt < JT; ++jt) {
+        floatx4 a, b;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          a[r] = dls[16 * w + acc_row(r)] * KdS[jt][r];
+          b[r] = dlr[16 * w + acc_row(r)] * KdR[jt][r];
+        }
+        store_acc_tile<TT>(blk(bKDS_DY), jt * 16, 16 * w, a);
+        store_acc_tile<TT>(blk(bKDR_DKR), jt * 16, 16 * w, b);
+      }
+    }
     // the transposed matrices' fragments are loaded ahead of the barriers
     // that precede their products (every matrix landed in an earlier chunk)
     const MatFrags<XT> aMR = cols_frags(mat(kMatMR, buf));
+    MatFrags<XT> aTR;
+    if constexpr (RDN) aTR = cols_frags(mat(kMatTR, 0));
     barrier_lds();
     if (c > 0) {
       issue_regs(c - 1);
       issue_early(c - 1);
     }
 
-    // ---- P2: dUR = diag(e^{h_C-h}) K dR_end + MR^T dc ----
-    floatx4 dUR[JT];
+    // ---- P2: dYR; dY but for the residual's term (Z) ----
+    floatx4 dYR[JT], Z[JT];
 #pragma unroll
     for (int jt = 0; jt < JT; ++jt) {
-      floatx4 a = zero4();
-      mma_frags<XT, TT>(a, aMR, blk(bDC_DX), jt * 16);
+      dYR[jt] = zero4();
+      mma_frags<XT, TT>(dYR[jt], aMR, blk(bDC_DX), jt * 16);
+      if constexpr (RDN) {
+        mma_frags<XT, TT>(dYR[jt], aTR, blk(bKDR_DKR), jt * 16);
+      } else {
 #pragma unroll
-      for (int r = 0; r < 4; ++r) dUR[jt][r] = dlr[16 * w + acc_row(r)] * KdR[jt][r] + a[r];
-      if constexpr (RDN) store_acc_tile<TT>(blk(bDUR_DU), jt * 16, 16 * w, dUR[jt]);
+        for (int r = 0; r < 4; ++r) dYR[jt][r] += dlr[16 * w + acc_row(r)] * KdR[jt][r];
+      }
     }
-    MatFrags<XT> aTR;
-    if constexpr (RDN) aTR = cols_frags(mat(kMatTR, 0));
+    {
+      const MatFrags<XT> aMP = cols_frags(mat(kMatMP, 0));
+      MatFrags<XT> aTS;
+      if constexpr (RDN) aTS = cols_frags(mat(kMatTS, 0));
+#pragma unroll
+      for (int jt = 0; jt < JT; ++jt) {
+        Z[jt] = zero4();
+        mma_frags<XT, TT>(Z[jt], aMP, blk(bDB_DKS), jt * 16);
+        if constexpr (RDN) {
+          mma_frags<XT, TT>(Z[jt], aTS, blk(bKDS_DY), jt * 16);
+        } else {
+#pragma unroll
+          for (int r = 0; r < 4; ++r) Z[jt][r] += dls[16 * w + acc_row(r)] * KdS[jt][r];
+        }
+      }
+    }
     barrier_lds();
 
-    // ---- P3: dYR, dX, dKR (RLA: dKS) ----
+    // ---- P3: dX, dKR ----
     floatx4 dX[JT];
 #pragma unroll
     for (int jt = 0; jt < JT; ++jt) {
-      floatx4 dYR = dUR[jt];
-      if constexpr (RDN) {
-        dYR = zero4();
-        mma_frags<XT, TT>(dYR, aTR, blk(bDUR_DU), jt * 16);
-      }
-      floatx4 dkr, dks;
+      floatx4 dkr;
+      const int j = jt * 16 + acc_col();
+      const uint32_t mw = tanh_resid ? 0 : mask_at(mask, j, 16 * w + acc_row(0));
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
-        const int t = 16 * w + acc_row(r), j = jt * 16 + acc_col();
+        const int t = 16 * w + acc_row(r);
         if constexpr (VAR) {
           float slope;
           if (tanh_resid) {
             const float rn = to_f<XT>(reinterpret_cast<const XT*>(mask)[t * BV + j]) * invc;
             slope = s0 * __builtin_fmaf(-rn, rn, 1.f);
           } else {
-            slope = mask[t * BV + j] ? 1.f : 0.f;
+            slope = mask_keep(mw, r, 1.f);
           }
-          dX[jt][r] = slope * (ggm[t] * dYR[r]);
+          dX[jt][r] = slope * (ggm[t] * dYR[jt][r]);
         } else {
-          dX[jt][r] = mask[t * BV + j] ? ggm[t] * dYR[r] : 0.f;
+          dX[jt][r] = mask_keep(mw, r, ggm[t] * dYR[jt][r]);
         }
-        dkr[r] = -ggm[t] * egr[t] * dYR[r];
-        dks[r] = -ekp[t] * dX[jt][r];
+        dkr[r] = -ggm[t] * egr[t] * dYR[jt][r];
       }
       store_acc_tile<TT>(blk(bDC_DX), jt * 16, 16 * w, dX[jt]);
-      store_acc_tile<TT>(blk(bDKR), jt * 16, 16 * w, RDN ? dkr : dks);
-      store_acc_tile<TT>(Yst, jt * 16, 16 * w, dYR);
+      if constexpr (RDN) store_acc_tile<TT>(blk(bKDR_DKR), jt * 16, 16 * w, dkr);
+      store_acc_tile<TT>(Yst, jt * 16, 16 * w, dYR[jt]);
     }
-    const MatFrags<XT> aMP = cols_frags(mat(kMatMP, 0));
     const MatFrags<XT> aMG = cols_frags(mat(kMatMG, 0));
     barrier_lds();
-    if (c > 0) issue_mid(c - 1);
+    if (c > 0) issue_late(c - 1);
 
-    // ---- P4: dU = diag(e^{g_C-g}) K dS_end + MP^T db - MG^T dX ----
-    floatx4 dU[JT];   // RLA: U = diag(b) V, so dV gets b dU
+    // ---- P4: dY, dKS; last prefetch issued: dv and checkpoint stores ----
 #pragma unroll
     for (int jt = 0; jt < JT; ++jt) {
-      floatx4 a = zero4(), b = zero4();
-      mma_frags<XT, TT>(a, aMP, blk(bDB_DKS), jt * 16);
+      floatx4 b = zero4(), dks;
       mma_frags<XT, TT>(b, aMG, blk(bDC_DX), jt * 16);
 #pragma unroll
-      for (int r = 0; r < 4; ++r) dU[jt][r] = dls[16 * w + acc_row(r)] * KdS[jt][r] + a[r] - b[r];
-      // RLA keeps dU there for the block store
-      store_acc_tile<TT>(blk(bDUR_DU), jt * 16, 16 * w, dU[jt]);
-    }
-    MatFrags<XT> aTS;
-    if constexpr (RDN) aTS = cols_frags(mat(kMatTS, 0));
-    barrier_lds();
-    if (c > 0) issue_late(c - 1);
-    if constexpr (!RDN) {   // last prefetch issued: dv and checkpoint stores
-      store_dv(dX, dU);
-      save_ckpt();
-    }
-    if constexpr (RDN) {
-      // ---- P5: dY = T^S^T dU, dKS ----
-      floatx4 dY[JT];
-#pragma unroll
-      for (int jt = 0; jt < JT; ++jt) {
-        floatx4 dks;
-        dY[jt] = zero4();
-        mma_frags<XT, TT>(dY[jt], aTS, blk(bDUR_DU), jt * 16);
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          const int t = 16 * w + acc_row(r);
-          dks[r] = -ekp[t] * dX[jt][r] - gbt[t] * egs[t] * dY[jt][r];
-        }
-        store_acc_tile<TT>(blk(bDB_DKS), jt * 16, 16 * w, dks);
+      for (int r = 0; r < 4; ++r) {
+        const int t = 16 * w + acc_row(r);
+        Z[jt][r] -= b[r];   // dY
+        dks[r] = -ekp[t] * dX[jt][r];
+        if constexpr (RDN) dks[r] -= gbt[t] * egs[t] * Z[jt][r];
       }
-      barrier_lds();
-      if (c > 0) issue_after5(c - 1);
-      // last prefetch issued: dv and checkpoint stores
-      store_dv(dX, dY);
-      save_ckpt();
-      // dU is dead: its slot keeps dY for the block store (P6 does not read it)
-#pragma unroll
-      for (int jt = 0; jt < JT; ++jt)
-        store_acc_tile<TT>(blk(bDUR_DU), jt * 16, 16 * w, dY[jt]);
+      store_acc_tile<TT>(blk(bDB_DKS), jt * 16, 16 * w, dks);
+      store_acc_tile<TT>(blk(bKDS_DY), jt * 16, 16 * w, Z[jt]);
     }
+    barrier_lds();
+    store_dv(dX, Z);
+    save_ckpt();
 
-    // ---- P6: state gradients at the chunk start ----
+    // ---- P5: state gradients at the chunk start ----
     // (bf16 inputs: the Q^T, K^T fragments from transpose reads issued as
-    // inline assembly, which leaves the DMA issued after P5 and the dv and
+    // inline assembly, which leaves the DMA issued after P3 and the dv and
     // checkpoint stores in flight; the builtin would drain them first)
     const float eS = edge[0], eR = edge[1];
     if constexpr (BF) {
@@ -667,9 +651,9 @@ __global__ __launch_bounds__(kThreads) void bwd_scan_kernel(OpParams p) {
           dS[it][jt] *= eS;
           dR[it][jt] *= eR;
           acc(dS[it][jt], qf, blk(bQDB), it, jt);
-          acc(dS[it][jt], kf, blk(RDN ? bDB_DKS : bDKR), it, jt);
+          acc(dS[it][jt], kf, blk(bDB_DKS), it, jt);
           acc(dR[it][jt], qf, blk(bQDC), it, jt);
-          if constexpr (RDN) acc(dR[it][jt], kf, blk(bDKR), it, jt);
+          if constexpr (RDN) acc(dR[it][jt], kf, blk(bKDR_DKR), it, jt);
         }
     } else {
 #pragma unroll
@@ -680,9 +664,9 @@ __global__ __launch_bounds__(kThreads) void bwd_scan_kernel(OpParams p) {
           dS[it][jt] *= eS;
           dR[it][jt] *= eR;
           mma_tiles<XT, kChunk, TKQ, TT>(dS[it][jt], QT, i0, blk(bQDB), jt * 16);
-          mma_tiles<XT, kChunk, TKQ, TT>(dS[it][jt], KT, i0, blk(RDN ? bDB_DKS : bDKR), jt * 16);
+          mma_tiles<XT, kChunk, TKQ, TT>(dS[it][jt], KT, i0, blk(bDB_DKS), jt * 16);
           mma_tiles<XT, kChunk, TKQ, TT>(dR[it][jt], QT, i0, blk(bQDC), jt * 16);
-          if constexpr (RDN) mma_tiles<XT, kChunk, TKQ, TT>(dR[it][jt], KT, i0, blk(bDKR), jt * 16);
+          if constexpr (RDN) mma_tiles<XT, kChunk, TKQ, TT>(dR[it][jt], KT, i0, blk(bKDR_DKR), jt * 16);
         }
       }
     }
@@ -705,7 +689,7 @@ __global__ __launch_bounds__(kThreads) void bwd_scan_kernel(OpParams p) {
       const int t = lane, v = w;   // lanes read consecutive tokens: no bank conflicts
 #pragma unroll
       for (int b = 0; b < 3; ++b) {
-        const XT* srcb = b == 0 ? blk(bDC_DX) : b == 1 ? blk(bDUR_DU) : Yst;
+        const XT* srcb = b == 0 ? blk(bDC_DX) : b == 1 ? blk(bKDS_DY) : Yst;
         uint4 x;
         if constexpr (BF) {   // two transpose reads per 16-byte row piece
           x = keep_if(tile_token_vec8<TT>(srcb, v * kVE), t < len);
@@ -721,48 +705,51 @@ __global__ __launch_bounds__(kThreads) void bwd_scan_kernel(OpParams p) {
     write_copies();
   }
 
-  if (p.dS0 || p.dR0) {
 #pragma unroll
-    for (int it = 0; it < IT; ++it)
+  for (int it = 0; it < IT; ++it)
 #pragma unroll
-      for (int jt = 0; jt < JT; ++jt)
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          const int i = w * (DK / 4) + it * 16 + acc_row(r), j = j0 + jt * 16 + acc_col();
-          if (p.dS0) p.dS0[state_off + (int64_t)i * DV + j] = dS[it][jt][r] * isig;
-          if (p.dR0) p.dR0[state_off + (int64_t)i * DV + j] = dR[it][jt][r] * isig;
-        }
-  }
+    for (int jt = 0; jt < JT; ++jt) {
+      dS[it][jt] *= isig;
+      dR[it][jt] *= isig;
+    }
+  if (p.dS0) save_state_f32<IT, JT>(dS, p.dS0 + state_off + j0, DV, w * (DK / 4));
+  if (p.dR0) save_state_f32<IT, JT>(dR, p.dR0 + state_off + j0, DV, w * (DK / 4));
 }
 
 // ---------------------------------------------------------------------------
 // Wave-specialised reverse scan: bf16 inputs, 32 value columns, the boxed
 // operator (no variant flags); Q16: q, k are the fp16 rows of the in-operator
 // normalisation, taken as they are.  Eight waves per workgroup in two
-// groups of four that pass the same seven barriers per chunk in the same
+// groups of four that pass the same five barriers per chunk in the same
 // order:
 //   chain waves (0-3): hold dS and dR (rows 32 w' .. 32 w' + 31) and do every
 //     product of the chunk (the algebra of bwd_scan_kernel) with no global
-//     memory access: K comes from the K^T tile, dv and the packed chunk-end
-//     checkpoints go to LDS;
+//     memory access: K and Q come from their tiles, dO from a raw block, dv
+//     and the packed chunk-end checkpoints go to LDS;
 //   side waves (4-7): all global memory traffic — the next (earlier)
-//     chunk's K, Q, dO rows and their commit into LDS, its gate vectors, the
-//     LDS-DMA of its matrices and clip mask, and the stores of the later
+//     chunk's K, Q rows and their commit into LDS, its gate vectors, the
+//     LDS-DMA of its dO, matrices and clip mask, and the stores of the later
 //     chunk's dX, dY, dYR blocks, dv and checkpoints — overlapping the chain.
 // Per chunk (phase: chain waves | side waves), walking backwards:
-//   0: state copies                               | commit K^T, dO^T; the later
-//                                                   chunk's dX block
-//   1: K dS, K dR; dc, e^g db, e^h dc             | its dY, dYR blocks and
-//                                                   checkpoints; the next gate
-//                                                   values; DMA of the next MR
-//   2: dUR                                        | its dv
-//   3: dYR, dX, dKR                               | commit Q^T; the next K, Q, dO
-//                                                   rows; DMA of the next T^R
-//   4: dU                                         | DMA of the next mask, MG, MP
-//   5: dY, dKS; dv and checkpoints into LDS       | DMA of the next T^S
-//   6: dS, dR at the chunk start; their maxima    | wait for the DMA; next gate vectors
-// Each matrix is refilled once the chain has read it into registers (T^R,
-// MG, MP, T^S) or, for MR, into the other buffer.
+//   0: state copies                               | K^T tile; gate vectors; the later
+//                                                   chunk's dR checkpoint
+//   1: dO tiles; K dS, K dR, decayed              | next K rows; Q^T tile; the later
+//                                                   dX, dYR blocks; DMA of the next gates
+//   2: dYR, dX, dKR; Z = dY but for dX's term;    | DMA of the next dO; next Q rows;
+//      checkpoints into LDS                         the later dY block
+//   3: dY = Z - (MG T^S)^T dX, dKS; dv into LDS;  | DMA of the next MR, T^R, T^S, MP
+//      dR at the chunk start, dS but for dKS
+//   4: dS at the chunk start; maxima              | DMA of the next mask, MG; dv; dS
+//                                                   checkpoint
+// A matrix is read into registers at the start of the phase that multiplies
+// by it (MR, T^R, T^S, MP: 2; MG: 3), refilled in the next, and its copy is
+// waited for just before that phase in the next chunk, so that the memory
+// operations are spread over the chunk (all of a chunk's traffic, 100 KiB, goes
+// through one CU's path; in bursts it stalls both roles) and each has most of
+// a chunk to land.  Beside that a chunk is bound by the chain, about 9600 to
+// 10500 cycles.  Five dependent phases instead of seven (128 x 128, 16 heads):
+// 4 x 4096 tokens 309 -> 305 us; normalised rows, 16000 tokens
+// packed, 427 -> 357 us.
 // ---------------------------------------------------------------------------
 template <typename IN, int DK, int BV, bool RDN>
 struct BwdWsLayout {
@@ -773,12 +760,14 @@ struct BwdWsLayout {
   typedef typename B::TSC TSC;
   static constexpr int kKT = B::kKT, kQT = B::kQT, kCopies = B::kCopies, kCopyBytes = B::kCopyBytes;
   static constexpr int kMats = B::kMats, kBufBytes = B::kBufBytes;
-  // matrix slots: the packed lower blocks (kPkBytes each)
-  static constexpr int kBufs = kMats + B::kNumSlots * kPkBytes;
-  static constexpr int kMask = kBufs + B::kNumBufs * kBufBytes;
-  static constexpr int kGateVec = 8 * kChunk;   // floats per chunk's gate vectors
-  static constexpr int kGates = kMask + B::kMaskBytes;   // two sets (chunk parity)
-  static constexpr int kYst = kGates + 2 * kGateVec * 4;    // dYR (token tile)
+  // matrix slots: the packed lower blocks (kPkBytes each); RDN: TS MG MP TR MR, RLA: MG MP MR
+  static constexpr int kNumSlots = RDN ? 5 : 3;
+  static constexpr int kBufs = kMats + kNumSlots * kPkBytes;
+  static constexpr int kMask = kBufs + (RDN ? 9 : 6) * kBufBytes;
+  static constexpr int kDo = kMask + B::kMaskBytes;         // raw dO rows [64][BV]
+  static constexpr int kGateVec = 8 * kChunk;               // floats of the chunk's gate vectors
+  static constexpr int kGates = kDo + kChunk * BV * (int)sizeof(IN);
+  static constexpr int kYst = kGates + kGateVec * 4;        // dYR (token tile)
   static constexpr int kRed = kYst + kBufBytes;             // per-wave maxima [8]
   static constexpr int kDvLd = kChunk + 4;                  // dv row stride (floats)
   static constexpr int kDv = kRed + 8 * 4;                  // dv, fp32 [BV][kDvLd] (column-major)
@@ -792,8 +781,17 @@ struct BwdWsLayout {
   static constexpr int kBytes = kZero + 16;
   static_assert(sizeof(IN) == 2 && BV == 32, "bf16, 32 columns");
   static_assert(kBytes <= 160 * 1024, "backward scan LDS");
-  __device__ static constexpr int slot(int mat, int buf) { return B::slot(mat, buf); }
+  __device__ static constexpr int slot(int mat) {
+    if (!RDN) return mat == kMatMG ? 0 : mat == kMatMP ? 1 : 2;
+    return mat == kMatTS ? 0 : mat == kMatMG ? 1 : mat == kMatMP ? 2 : mat == kMatTR ? 3 : 4;
+  }
 };
+
+// per-token block slots, each written in another phase than its last read
+// (phases written -> last read): db (1 -> 2; then dKS, 3 -> 4), dc (1 -> 2), e^g db,
+// e^h dc (1 -> 3), dX (2 -> 1), dY (3 -> 1), the decayed K dS, K dR (1 -> 2), dKR (2 -> 3);
+// the last three RDN only
+enum { wDB_DKS = 0, wDC, wQDB, wQDC, wDX, wDY, wKDS, wKDR, wDKR };
 
 template <typename IN, int DK, int BV, bool RDN, bool Q16>
 __global__ __launch_bounds__(2 * kThreads) void bwd_scan_ws_kernel(OpParams p) {
@@ -806,8 +804,7 @@ __global__ __launch_bounds__(2 * kThreads) void bwd_scan_ws_kernel(OpParams p) {
   constexpr int JT = BV / 16;
   constexpr int IT = DK / 64;
   constexpr int KS_STEPS = DK / MI::kStep;
-  extern __shared__ __align__(16) unsigned char smem_[];
-  unsigned char* smem = smem_;
+  extern __shared__ __align__(16) unsigned char smem[];
   XT* KT = reinterpret_cast<XT*>(smem + L::kKT);
   XT* QT = reinterpret_cast<XT*>(smem + L::kQT);
   XT* dSc = reinterpret_cast<XT*>(smem + L::kCopies);
@@ -820,14 +817,13 @@ __global__ __launch_bounds__(2 * kThreads) void bwd_scan_ws_kernel(OpParams p) {
   f16* ckst = reinterpret_cast<f16*>(smem + L::kCk);
   float* ckscl = reinterpret_cast<float*>(smem + L::kCkSc);
   float* graw = reinterpret_cast<float*>(smem + L::kGraw);   // prep's gate block
-  auto mat = [&](int m, int buf) {
-    return reinterpret_cast<XT*>(smem + L::kMats + L::slot(m, buf) * kPkBytes);
-  };
-  const XT* zero16 = reinterpret_cast<const XT*>(smem + L::kZero);
+  const IN* Do = reinterpret_cast<const IN*>(smem + L::kDo);
+  auto mat = [&](int m) { return reinterpret_cast<XT*>(smem + L::kMats + L::slot(m) * kPkBytes); };
+  const uint32_t zero16 = lds_addr(smem + L::kZero);
   auto blk = [&](int b) { return reinterpret_cast<XT*>(smem + L::kBufs + b * L::kBufBytes); };
-  // gate vectors of chunk c: beta, gamma, e^{g_t}, e^{g_{t-1}}, e^{h_t},
+  // gate vectors of the chunk: beta, gamma, e^{g_t}, e^{g_{t-1}}, e^{h_t},
   // e^{g_C - g_t}, e^{h_C - h_t}, then [e^{g_C}, e^{h_C}]
-  auto gvec = [&](int c, int k) { return gates + (c & 1) * L::kGateVec + k * kChunk; };
+  auto gvec = [&](int k) { return gates + k * kChunk; };
 
   const int H = p.H, DV = p.DV, tid = threadIdx.x, lane = tid & 63;
   const int wu = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -873,8 +869,6 @@ __global__ __launch_bounds__(2 * kThreads) void bwd_scan_ws_kernel(OpParams p) {
   auto mat_src = [&](int c, int m) {
     return matg + ((int64_t)(si.chunk0 + c) * H + h) * kNumMats * kMatElems + m * kMatElems;
   };
-  constexpr int kOPerThread = 16 / (int)sizeof(IN);
-  static_assert(kChunk * BV == kThreads * kOPerThread, "one dO vector per chain thread");
 
   // One loop body, instantiated once per role (std::true_type: chain
   // waves): both roles pass the same barriers in the same order by
@@ -883,7 +877,6 @@ __global__ __launch_bounds__(2 * kThreads) void bwd_scan_ws_kernel(OpParams p) {
   constexpr bool CH = decltype(role)::value;
   floatx4 dS[IT][JT], dR[IT][JT];      // chain: the gradient states
   typename MI::frag Kn[KS_STEPS], Qn[KS_STEPS];   // side: the next chunk's K, Q rows 16 ww + (lane & 15)
-  IN on[kOPerThread];                              // side: its dO vector
   float scS = 1.f, scR = 1.f;
   uint32_t tmS[IT], tmR[IT];
   auto publish_state_max = [&]() {   // chain: the four tile maxima, reduced together
@@ -917,74 +910,55 @@ __global__ __launch_bounds__(2 * kThreads) void bwd_scan_ws_kernel(OpParams p) {
   // The side's global addresses are a chunk's uniform base plus a 32-bit
   // lane offset that does not change from chunk to chunk, so the memory
   // instructions take a scalar base and the lane part is formed once.
-  // K or Q rows: token row 16 ww + (lane & 15) of the chunk whose rows start at base
-  auto load_rows = [&](typename MI::frag (&afr)[KS_STEPS], const IN* base, bool ok) {
-    const uint32_t o = (uint32_t)((16 * ww + (lane & 15)) * H * DK + (lane >> 4) * 8);
+  // chunk c's K or Q rows, token row 16 ww + (lane & 15); past the end the
+  // last row (the products with such rows are multiplied by 0 or not stored)
+  auto load_rows = [&](typename MI::frag (&afr)[KS_STEPS], const IN* src, int c) {
+    const IN* base = src + ((si.start + (int64_t)c * kChunk) * H + h) * (int64_t)DK;
+    const uint32_t o = (uint32_t)(min(16 * ww + (lane & 15), chunk_len(c) - 1) * H * DK + (lane >> 4) * 8);
 #pragma unroll
-    for (int s2 = 0; s2 < KS_STEPS; ++s2) {
-      u16x8 v = {0, 0, 0, 0, 0, 0, 0, 0};
-      if (ok) v = *reinterpret_cast<const u16x8*>(base + o + s2 * 32);
-      afr[s2] = __builtin_bit_cast(typename MI::frag, v);
-    }
+    for (int s2 = 0; s2 < KS_STEPS; ++s2)
+      afr[s2] = __builtin_bit_cast(typename MI::frag, *reinterpret_cast<const u16x8*>(base + o + s2 * 32));
   };
-  auto issue_regs = [&](int c) {   // side: K, Q rows and this thread's dO vector of chunk c
+  auto issue_do = [&](int c) {   // side: dO rows; past the end any valid row (zeroed by the chain)
+    static_assert(kChunk * BV * sizeof(IN) == kWaves * 1024, "dO block = one DMA instruction per side wave");
+    constexpr int kPerRow = BV * (int)sizeof(IN) / 16;
+    const int P = ww * 64 + lane, t = min(P / kPerRow, chunk_len(c) - 1), cc = P % kPerRow;
     const int64_t tok = si.start + (int64_t)c * kChunk;
-    const int len = chunk_len(c);
-    const bool ok = 16 * ww + (lane & 15) < len;
-    const int64_t rb = (tok * H + h) * (int64_t)DK;
-    load_rows(Kn, kg + rb, ok);
-    load_rows(Qn, qg + rb, ok);
-    typedef IN INV __attribute__((ext_vector_type(kOPerThread)));
-    const int tt = lane, j = ww * kOPerThread;
-    INV v = {};
-    if (tt < len)
-      v = *reinterpret_cast<const INV*>(dog + (tok * H + h) * (int64_t)DV + j0 + j + (uint32_t)(tt * H * DV));
-#pragma unroll
-    for (int u = 0; u < kOPerThread; ++u) on[u] = v[u];
+    dma16(dog + (tok * H + h) * (int64_t)DV + j0 + (uint32_t)(t * H * DV + cc * (16 / (int)sizeof(IN))),
+          smem + L::kDo + ww * 1024);
   };
   // side wave 0 moves chunk c's gate block (g, h, beta, gamma) into LDS with
   // one DMA instruction and, after its wait, forms every gate vector
   auto issue_gates = [&](int c) {
     if (ww == 0) dma_linear_wave(p.gate_ws + ((int64_t)(si.chunk0 + c) * H + h) * kGateBlock, graw, kGateBlock * 4);
   };
-  auto write_gates = [&](int c) {
-    if (ww != 0) return;
-    const int t = lane;
-    const float g = graw[t], gp = graw[max(t - 1, 0)], gl = graw[kChunk - 1];
-    const float hr = graw[64 + t], hl = graw[64 + kChunk - 1];
-    gvec(c, 0)[t] = graw[128 + t];
-    gvec(c, 1)[t] = graw[192 + t];
-    gvec(c, 2)[t] = __expf(g);
-    gvec(c, 3)[t] = t > 0 ? __expf(gp) : 1.f;
-    gvec(c, 4)[t] = __expf(hr);
-    gvec(c, 5)[t] = __expf(gl - g);
-    gvec(c, 6)[t] = __expf(hl - hr);
-    gvec(c, 7)[0] = __expf(gl);   // every lane stores the same value
-    gvec(c, 7)[1] = __expf(hl);
+  auto write_gates = [&]() {
+    if (ww == 0) write_gate_vectors(graw, gates);
   };
-  // side: chunk c's matrix m into slot buffer buf; the side wave x issues two
-  // of the five DMA instructions (chosen per matrix to even out the phases)
-  auto dma_mat = [&](int c, int m, int buf, int x) {
-    dma_mat_packed<true>(mat_src(c, m), mat(m, buf), (ww - x) & 3, kWaves);
-  };
-  auto issue_mask = [&](int c) {   // side: rows of BV bytes; padding rows read row 0 (masked by 0 gradients)
-    const int64_t tok = si.start + (int64_t)c * kChunk;
-    const int len = chunk_len(c);
-    constexpr int kPerRow = BV / 16;
-    constexpr int kInst = kChunk * BV / 1024;
-    static_assert(kInst <= kWaves, "one mask DMA instruction per side wave at most");
-    if (ww < kInst) {
-      const int P = ww * 64 + lane, t = P / kPerRow, cc = P % kPerRow;
-      const int ts = t < len ? t : 0;
-      dma16(p.ck_mask + (tok * H + h) * (int64_t)DV + j0 + (uint32_t)(ts * H * DV + cc * 16), mask + ww * 1024);
+  // side: chunk c's matrix m; the side wave x issues two of the five DMA
+  // instructions, the others one (the four of issue_mats: five instructions
+  // of every wave; RLA's two: at least two)
+  auto dma_mat = [&](int c, int m, int x) { dma_mat_packed<true>(mat_src(c, m), mat(m), (ww - x) & 3, kWaves); };
+  auto issue_mats = [&](int c) {
+    dma_mat(c, kMatMR, 0);
+    dma_mat(c, kMatMP, 1);
+    if constexpr (RDN) {
+      dma_mat(c, kMatTR, 2);
+      dma_mat(c, kMatTS, 3);
     }
+  };
+  // The side's waits leave its newest memory operations in flight, so the
+  // order in which it issues groups of them is pinned.
+  auto pin = [] { asm volatile("" ::: "memory"); };
+  auto issue_mask = [&](int c) {   // side
+    if (ww < BV / 16) dma_mask(p.ck_mask + mask_off(si.chunk0 + c, h, H, DV) + j0 * kChunk, mask, ww);
   };
   // side: block b (0 dX, 1 dY, 2 dYR) of chunk c, tokens 16 ww .. 16 ww + 15,
   // one 64-byte segment per token; rows past the end are zero
   auto store_block = [&](int c, int b) {
     static_assert(sizeof(XT) == 2, "four lanes per 32-value token row");
     const int64_t gc = si.chunk0 + c;
-    const XT* srcb = b == 0 ? blk(bDC_DX) : b == 1 ? blk(bDUR_DU) : Yst;
+    const XT* srcb = b == 0 ? blk(wDX) : b == 1 ? blk(wDY) : Yst;
     const int t = 16 * ww + (lane & 15);
     const uint4 x = keep_if(tile_token_rows16_sync<TT>(srcb, 16 * ww), t < chunk_len(c));
     *reinterpret_cast<uint4*>(bblk + blk_off(gc, h, H, b, DV) + j0 + (uint32_t)(t * DV + 8 * (lane >> 4))) = x;
@@ -1013,339 +987,366 @@ __global__ __launch_bounds__(2 * kThreads) void bwd_scan_ws_kernel(OpParams p) {
       }
     }
   };
-  // side: chunk c's end-state checkpoints from LDS, rows 32 ww .. 32 ww + 31
-  // of each: two transpose reads give a lane 16 bytes of one row, so each
-  // store writes 16 rows (1 KiB contiguous); and their tile scales
-  auto store_ckpt = [&](int c) {
+  // side: chunk c's end-state checkpoint of dS or dR (st) from LDS, this
+  // wave's rows: two transpose reads give a lane 16 bytes of one row, so each
+  // store writes 16 rows (1 KiB contiguous); with dR the tile scales of both
+  auto store_ckpt = [&](int c, int st) {
     const int64_t gc = si.chunk0 + c;
     const int64_t ob = ((int64_t)gc * H + h) * DK * DV + (int64_t)j0 * DK;
     const int64_t so = ((int64_t)gc * H + h) * (DK / 16) * (DV / 32) + j0 / 32;
+    f16* dst = reinterpret_cast<f16*>(st ? p.dR_ws : p.dS_ws) + ob;
 #pragma unroll
-    for (int st = 0; st < 2; ++st) {
-      f16* dst = reinterpret_cast<f16*>(st ? p.dR_ws : p.dS_ws) + ob;
-#pragma unroll
-      for (int u = 0; u < IT; ++u) {
-        const int t0 = ww * (DK / 4) + 16 * u;
-        const uint4 x = tile_token_rows16_sync<TSC>(ckst + st * BV * (TSC::kRowB / 2), t0);
-        *reinterpret_cast<uint4*>(dst + (uint32_t)((t0 + (lane & 15)) * BV + 8 * (lane >> 4))) = x;
-      }
+    for (int u = 0; u < IT; ++u) {
+      const int t0 = ww * (DK / 4) + 16 * u;
+      const uint4 x = tile_token_rows16_sync<TSC>(ckst + st * BV * (TSC::kRowB / 2), t0);
+      *reinterpret_cast<uint4*>(dst + (uint32_t)((t0 + (lane & 15)) * BV + 8 * (lane >> 4))) = x;
     }
-    if (lane < 2 * IT) {   // one lane per tile scale, both states in one store
-      const int st = lane / IT, it = lane % IT;
-      (st ? p.dR_sc : p.dS_sc)[so + (int64_t)(ww * IT + it) * (DV / 32)] = ckscl[st * (DK / 16) + ww * IT + it];
+    if (st && lane < 2 * IT) {   // one lane per tile scale, both states in one store
+      const int s2 = lane / IT, it = lane % IT;
+      (s2 ? p.dR_sc : p.dS_sc)[so + (int64_t)(ww * IT + it) * (DV / 32)] = ckscl[s2 * (DK / 16) + ww * IT + it];
     }
   };
-  // side: rows 16 ww + (lane & 15) of a K^T or Q^T tile (fp16) from the
-  // prefetched bf16 rows, one 16-byte store per k-step
+  // side: the prefetched rows in fp16 (Q16: they are), pinned here, and their
+  // store as rows 16 ww + (lane & 15) of a K^T or Q^T tile, one 16-byte store
+  // per k-step
+  auto to_f16_rows = [&](typename MI::frag (&x)[KS_STEPS]) {
+#pragma unroll
+    for (int s2 = 0; s2 < KS_STEPS; ++s2) {
+      u16x8 v = __builtin_bit_cast(u16x8, x[s2]);
+      if constexpr (!Q16) {
+        f16x8 y;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) y[e] = (f16)bf2f(v[e]);
+        v = __builtin_bit_cast(u16x8, y);
+      }
+      asm volatile("" : "+v"(v));
+      x[s2] = __builtin_bit_cast(typename MI::frag, v);
+    }
+  };
   auto commit_rows = [&](XT* dst, const typename MI::frag (&src)[KS_STEPS]) {
     const int t = 16 * ww + (lane & 15);
 #pragma unroll
-    for (int s2 = 0; s2 < KS_STEPS; ++s2) {
-      const u16x8 v = __builtin_bit_cast(u16x8, src[s2]);
-      f16x8 x = __builtin_bit_cast(f16x8, v);
-      if constexpr (!Q16) {
-#pragma unroll
-        for (int e = 0; e < 8; ++e) x[e] = (f16)bf2f(v[e]);
-      }
-      *reinterpret_cast<f16x8*>(TKQ::ptr(dst, t, s2 * 32 + (lane >> 4) * 8)) = x;
-    }
-  };
-  auto commit_do = [&]() {   // side: dO^T (scaled) of the chunk whose vector on holds
-    XT* dbT = blk(bDB_DKS);
-#pragma unroll
-    for (int u = 0; u < kOPerThread; ++u)   // lanes write consecutive tokens
-      *TT::ptr(dbT, ww * kOPerThread + u, lane) = from_f<XT>(to_f<IN>(on[u]) * sig);
+    for (int s2 = 0; s2 < KS_STEPS; ++s2)
+      *reinterpret_cast<f16x8*>(TKQ::ptr(dst, t, s2 * 32 + (lane >> 4) * 8)) = __builtin_bit_cast(f16x8, src[s2]);
   };
 
   // ---- prologue: the last chunk's staging; the end-state maxima ----
   if constexpr (CH) {
+    load_acc_state<IT, JT>(dS, p.dS_fin, state_off + j0, DV, ww * (DK / 4));
+    load_acc_state<IT, JT>(dR, p.dR_fin, state_off + j0, DV, ww * (DK / 4));
 #pragma unroll
     for (int it = 0; it < IT; ++it)
 #pragma unroll
-      for (int jt = 0; jt < JT; ++jt)
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          const int i = ww * (DK / 4) + it * 16 + acc_row(r), j = j0 + jt * 16 + acc_col();
-          dS[it][jt][r] = p.dS_fin ? p.dS_fin[state_off + (int64_t)i * DV + j] * sig : 0.f;
-          dR[it][jt][r] = p.dR_fin ? p.dR_fin[state_off + (int64_t)i * DV + j] * sig : 0.f;
-        }
+      for (int jt = 0; jt < JT; ++jt) {
+        dS[it][jt] *= sig;
+        dR[it][jt] *= sig;
+      }
     publish_state_max();
   } else {
     if (nch > 0) {
       const int c = nch - 1;
-      issue_regs(c);
+      load_rows(Kn, kg, c);
+      load_rows(Qn, qg, c);
       issue_gates(c);
+      issue_do(c);
       issue_mask(c);
-      if constexpr (RDN) {
-        dma_mat(c, kMatTS, 0, 1);
-        dma_mat(c, kMatTR, 0, 2);
-      }
-      dma_mat(c, kMatMG, 0, 2);
-      dma_mat(c, kMatMP, 0, 3);
-      dma_mat(c, kMatMR, c & 1, 3);
+      issue_mats(c);
+      dma_mat(c, kMatMG, 2);
       wait_vmem();
-      write_gates(c);
+      to_f16_rows(Kn);
+      to_f16_rows(Qn);
     }
   }
   if (tid == 0) *reinterpret_cast<uint4*>(smem + L::kZero) = uint4{0, 0, 0, 0};
   barrier_lds();
 
-  floatx4 KdS[JT], KdR[JT], dUR[JT], dX[JT];
-  MatFrags<XT> aMR, aTR, aMP, aMG, aTS;
-  for (int c = nch - 1; c >= 0; --c) {
-    const int gc = si.chunk0 + c;
-    const int buf = c & 1;
-    const int len = chunk_len(c);
-    const int64_t tok = si.start + (int64_t)c * kChunk;
-    const float* gbt = gvec(c, 0);
-    const float* ggm = gvec(c, 1);
-    const float* egs = gvec(c, 2);
-    const float* egsp = gvec(c, 3);
-    const float* egr = gvec(c, 4);
-    const float* dls = gvec(c, 5);
-    const float* dlr = gvec(c, 6);
-    const float* edge = gvec(c, 7);
+  typedef Mfma<XT> MX;
+  constexpr int XS = kChunk / MX::kStep;   // k-steps over the chunk's tokens
+  constexpr int NF = IT * XS;
+  auto tok_frags = [&](const XT* tile, typename MX::frag (&f)[JT][XS]) {
+#pragma unroll
+    for (int ks = 0; ks < XS; ++ks)
+#pragma unroll
+      for (int jt = 0; jt < JT; ++jt) f[jt][ks] = TT::template frag<MX>(tile, jt * 16, ks * MX::kStep);
+  };
+  // acc[jt] += a * tile, the column blocks' chains interleaved
+  auto mma_tok = [&](floatx4 (&acc)[JT], const MatFrags<XT>& a, const typename MX::frag (&f)[JT][XS]) {
+#pragma unroll
+    for (int ks = 0; ks < XS; ++ks)
+#pragma unroll
+      for (int jt = 0; jt < JT; ++jt) acc[jt] = MX::mma(a.f[ks], f[jt][ks], acc[jt]);
+  };
+  auto mma_state = [&](floatx4 (&acc)[IT][JT], const typename MX::frag (&a)[NF], const typename MX::frag (&f)[JT][XS]) {
+#pragma unroll
+    for (int ks = 0; ks < XS; ++ks)
+#pragma unroll
+      for (int it = 0; it < IT; ++it)
+#pragma unroll
+        for (int jt = 0; jt < JT; ++jt) acc[it][jt] = MX::mma(a[it * XS + ks], f[jt][ks], acc[it][jt]);
+  };
 
-    // ======== phase 0: copies and commit | the later chunk's outputs ========
+  floatx4 KdS[JT], KdR[JT], dX[JT], Z[JT];
+  MatFrags<XT> aMR, aTR, aMP, aMG, aTS;
+  typename MX::frag qt[NF], kt[NF];   // this wave's state rows of Q^T, K^T
+  for (int c = nch - 1; c >= 0; --c) {
+    const int len = chunk_len(c);
+    // this lane's four tokens of gate vector k
+    auto gate4 = [&](int k) { return *reinterpret_cast<const floatx4*>(gvec(k) + 16 * ww + acc_row(0)); };
+    floatx4 gbt, ggm, egs, egsp, egr, dls, dlr;
+
+    // ======== phase 0: copies | commits ========
     if constexpr (CH) {
       write_copies();
     } else {
-      commit_rows(KT, Kn);   // read by phase 1 (Q^T, read in phase 6 only, in phase 3)
-      commit_do();
-      if (c + 1 < nch) store_block(c + 1, 0);   // dX: its slot takes dc in phase 1
+      commit_rows(KT, Kn);   // read by phases 1 and 2
+      write_gates();
+      if (c + 1 < nch) store_ckpt(c + 1, 1);
     }
     barrier_lds();
 
-    // ======== phase 1: K dS_end, K dR_end; dc, e^g db, e^h dc ========
+    // ======== phase 1: dO and its products with the gates; K dS_end, K dR_end, decayed ========
     if constexpr (CH) {
-      typename Mfma<XT>::frag Kf[KS_STEPS];   // rows 16 ww + (lane & 15) of the K^T tile
+      typename MX::frag kf[2], f[2][2][JT];
+      auto load_step = [&](int s2) {   // rows 16 ww + (lane & 15) of the K^T tile; the state copies
+        kf[s2 & 1] = *reinterpret_cast<const typename MX::frag*>(TKQ::ptr(KT, 16 * ww + (lane & 15), s2 * 32 + (lane >> 4) * 8));
 #pragma unroll
-      for (int s2 = 0; s2 < KS_STEPS; ++s2)
-        Kf[s2] = *reinterpret_cast<const typename Mfma<XT>::frag*>(
-            TKQ::ptr(KT, 16 * ww + (lane & 15), s2 * 32 + (lane >> 4) * 8));
-#pragma unroll
-      for (int jt = 0; jt < JT; ++jt) {
-        KdS[jt] = zero4();
-        KdR[jt] = zero4();
-        mma_rega_tile<XT, DK, TSC>(KdS[jt], Kf, dSc, jt * 16);
-        mma_rega_tile<XT, DK, TSC>(KdR[jt], Kf, dRc, jt * 16);
-        KdS[jt] *= scS;   // undo the copies' scales (powers of two: exact)
-        KdR[jt] *= scR;
-        floatx4 dc, qdb, qdc;
-        const floatx4 o4 = load_acc_tile<TT>(blk(bDB_DKS), jt * 16, 16 * ww);
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          const int t = 16 * ww + acc_row(r);
-          dc[r] = ggm[t] * o4[r];
-          qdb[r] = egs[t] * o4[r];
-          qdc[r] = egr[t] * dc[r];
+        for (int jt = 0; jt < JT; ++jt) {
+          f[s2 & 1][0][jt] = TSC::template frag<MX>(dSc, jt * 16, s2 * MX::kStep);
+          f[s2 & 1][1][jt] = TSC::template frag<MX>(dRc, jt * 16, s2 * MX::kStep);
         }
-        store_acc_tile<TT>(blk(bDC_DX), jt * 16, 16 * ww, dc);
-        store_acc_tile<TT>(blk(bQDB), jt * 16, 16 * ww, qdb);
-        store_acc_tile<TT>(blk(bQDC), jt * 16, 16 * ww, qdc);
-      }
-      aMR = packed_cols_frags_sync(mat(kMatMR, buf), ww, zero16);
-    } else {
-      if (c + 1 < nch) {   // dY (its slot takes dUR in phase 2), dYR, checkpoints
-        store_block(c + 1, 1);
-        store_block(c + 1, 2);
-        store_ckpt(c + 1);
-      }
-      if (c > 0) {
-        issue_gates(c - 1);
-        dma_mat(c - 1, kMatMR, (c - 1) & 1, 3);
-      }
-    }
-    barrier_lds();
-
-    // ======== phase 2: dUR = diag(e^{h_C-h}) K dR_end + MR^T dc ========
-    if constexpr (CH) {
+      };
+      u16x4 dov[JT];
+#pragma unroll
+      for (int jt = 0; jt < JT; ++jt) dov[jt] = acc_tile_tr<PadRows<IN, BV, 0>>(Do, 16 * ww, jt * 16);
+      ggm = gate4(1);
+      egs = gate4(2);
+      egr = gate4(4);
+      load_step(0);
+      dls = gate4(5);
+      dlr = gate4(6);
+      sched_fence();
 #pragma unroll
       for (int jt = 0; jt < JT; ++jt) {
-        floatx4 a = zero4();
-        mma_frags<XT, TT>(a, aMR, blk(bDC_DX), jt * 16);
+        KdS[jt] = KdR[jt] = zero4();
+        floatx4 o4;
 #pragma unroll
-        for (int r = 0; r < 4; ++r) dUR[jt][r] = dlr[16 * ww + acc_row(r)] * KdR[jt][r] + a[r];
-        if constexpr (RDN) store_acc_tile<TT>(blk(bDUR_DU), jt * 16, 16 * ww, dUR[jt]);
+        for (int r = 0; r < 4; ++r) o4[r] = (float)to_f16(bf2f(dov[jt][r]) * sig);
+        if (len < kChunk) {   // rows past the end
+#pragma unroll
+          for (int r = 0; r < 4; ++r) o4[r] = 16 * ww + acc_row(r) < len ? o4[r] : 0.f;
+        }
+        const floatx4 dc = ggm * o4;
+        store_acc_tile<TT>(blk(wDB_DKS), jt * 16, 16 * ww, o4);
+        store_acc_tile<TT>(blk(wDC), jt * 16, 16 * ww, dc);
+        store_acc_tile<TT>(blk(wQDB), jt * 16, 16 * ww, egs * o4);
+        store_acc_tile<TT>(blk(wQDC), jt * 16, 16 * ww, egr * dc);
       }
-      if constexpr (RDN) aTR = packed_cols_frags_sync(mat(kMatTR, 0), ww, zero16);
-    } else {
-      if (c + 1 < nch) store_dv(c + 1);
-    }
-    barrier_lds();
-
-    // ======== phase 3: dYR, dX, dKR (RLA: dKS) ========
-    if constexpr (CH) {
 #pragma unroll
-      for (int jt = 0; jt < JT; ++jt) {
-        floatx4 dYR = dUR[jt];
+      for (int s2 = 0; s2 < KS_STEPS; ++s2) {
+        if (s2 + 1 < KS_STEPS) load_step(s2 + 1);
+        sched_fence();
+#pragma unroll
+        for (int jt = 0; jt < JT; ++jt) {
+          KdS[jt] = MX::mma(kf[s2 & 1], f[s2 & 1][0][jt], KdS[jt]);
+          KdR[jt] = MX::mma(kf[s2 & 1], f[s2 & 1][1][jt], KdR[jt]);
+        }
+      }
+#pragma unroll
+      for (int jt = 0; jt < JT; ++jt) {   // undo the copies' scales (powers of two: exact)
+        KdS[jt] = dls * (KdS[jt] * scS);
+        KdR[jt] = dlr * (KdR[jt] * scR);
         if constexpr (RDN) {
-          dYR = zero4();
-          mma_frags<XT, TT>(dYR, aTR, blk(bDUR_DU), jt * 16);
+          store_acc_tile<TT>(blk(wKDS), jt * 16, 16 * ww, KdS[jt]);
+          store_acc_tile<TT>(blk(wKDR), jt * 16, 16 * ww, KdR[jt]);
         }
-        floatx4 dkr, dks;
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          const int t = 16 * ww + acc_row(r), j = jt * 16 + acc_col();
-          dX[jt][r] = mask[t * BV + j] ? ggm[t] * dYR[r] : 0.f;
-          dkr[r] = -ggm[t] * egr[t] * dYR[r];
-          dks[r] = -egsp[t] * dX[jt][r];
-        }
-        store_acc_tile<TT>(blk(bDC_DX), jt * 16, 16 * ww, dX[jt]);
-        store_acc_tile<TT>(blk(bDKR), jt * 16, 16 * ww, RDN ? dkr : dks);
-        store_acc_tile<TT>(Yst, jt * 16, 16 * ww, dYR);
       }
-      aMP = packed_cols_frags_sync(mat(kMatMP, 0), ww, zero16);
-      aMG = packed_cols_frags_sync(mat(kMatMG, 0), ww, zero16);
     } else {
-      commit_rows(QT, Qn);   // then the next chunk's rows may replace Kn, Qn, on
-      if (c > 0) issue_regs(c - 1);
-      if constexpr (RDN) {   // T^R was read into registers before the previous barrier
-        if (c > 0) dma_mat(c - 1, kMatTR, 0, 2);
+      if (c > 0) {
+        load_rows(Kn, kg, c - 1);
+        issue_gates(c - 1);
       }
+      pin();
+      commit_rows(QT, Qn);   // read at the end of phase 2
+      if (c + 1 < nch) {
+        store_block(c + 1, 0);
+        store_block(c + 1, 2);
+      }
+      // this chunk's matrices and mask (from phases 3, 4 of the later one);
+      // since then MG, the checkpoints (2 IT + 1 stores) and these two blocks
+      wait_vmem_but<2 * IT + 4>();
     }
     barrier_lds();
 
-    // ======== phase 4: dU = diag(e^{g_C-g}) K dS_end + MP^T db - MG^T dX ========
-    floatx4 dU[JT];   // RLA: U = diag(b) V, so dV gets b dU
+    // ======== phase 2: dYR, dX, dKR; Z = T^S^T diag(e^{g_C-g}) K dS_end + (MP T^S)^T db ========
     if constexpr (CH) {
+      typename MX::frag fc[JT][XS], fr[JT][XS], fb[JT][XS], fs[JT][XS];
+      tok_frags(blk(wDC), fc);
+      if constexpr (RDN) tok_frags(blk(wKDR), fr);
+      uint32_t mw[JT];
+#pragma unroll
+      for (int jt = 0; jt < JT; ++jt) mw[jt] = mask_at(mask, jt * 16 + acc_col(), 16 * ww + acc_row(0));
+      sched_fence();
+      if constexpr (RDN) {
+        const uint32_t m[4] = {lds_addr(mat(kMatMR)), lds_addr(mat(kMatTR)), lds_addr(mat(kMatMP)), lds_addr(mat(kMatTS))};
+        MatFrags<f16>* const x[4] = {&aMR, &aTR, &aMP, &aTS};
+        packed_cols_frags_sync<4>(m, ww, zero16, x);
+      } else {
+        const uint32_t m[2] = {lds_addr(mat(kMatMR)), lds_addr(mat(kMatMP))};
+        MatFrags<f16>* const x[2] = {&aMR, &aMP};
+        packed_cols_frags_sync<2>(m, ww, zero16, x);
+      }
+      tok_frags(blk(wDB_DKS), fb);
+      if constexpr (RDN) tok_frags(blk(wKDS), fs);
+      sched_fence();
+      floatx4 dYR[JT];
+#pragma unroll
+      for (int jt = 0; jt < JT; ++jt) dYR[jt] = Z[jt] = zero4();
+      mma_tok(dYR, aMR, fc);
+      if constexpr (RDN) mma_tok(dYR, aTR, fr);
+      mma_tok(Z, aMP, fb);
+      if constexpr (RDN) mma_tok(Z, aTS, fs);
 #pragma unroll
       for (int jt = 0; jt < JT; ++jt) {
-        floatx4 a = zero4(), b = zero4();
-        mma_frags<XT, TT>(a, aMP, blk(bDB_DKS), jt * 16);
-        mma_frags<XT, TT>(b, aMG, blk(bDC_DX), jt * 16);
-#pragma unroll
-        for (int r = 0; r < 4; ++r) dU[jt][r] = dls[16 * ww + acc_row(r)] * KdS[jt][r] + a[r] - b[r];
-        store_acc_tile<TT>(blk(bDUR_DU), jt * 16, 16 * ww, dU[jt]);
-      }
-      if constexpr (RDN) aTS = packed_cols_frags_sync(mat(kMatTS, 0), ww, zero16);
-    } else {
-      if (c > 0) {   // the mask (read in phase 3) and MG, MP (read into registers)
-        issue_mask(c - 1);
-        dma_mat(c - 1, kMatMG, 0, 2);
-        dma_mat(c - 1, kMatMP, 0, 3);
-      }
-    }
-    barrier_lds();
-
-    // ======== phase 5: dY = T^S^T dU, dKS; dv; checkpoints ========
-    if constexpr (CH) {
-      floatx4 tail[JT];   // RDN: dY; RLA: dU
-      if constexpr (RDN) {
-#pragma unroll
-        for (int jt = 0; jt < JT; ++jt) {
-          floatx4 dks;
-          tail[jt] = zero4();
-          mma_frags<XT, TT>(tail[jt], aTS, blk(bDUR_DU), jt * 16);
-#pragma unroll
-          for (int r = 0; r < 4; ++r) {
-            const int t = 16 * ww + acc_row(r);
-            dks[r] = -egsp[t] * dX[jt][r] - gbt[t] * egs[t] * tail[jt][r];
-          }
-          store_acc_tile<TT>(blk(bDB_DKS), jt * 16, 16 * ww, dks);
+        if constexpr (!RDN) {
+          dYR[jt] += KdR[jt];
+          Z[jt] += KdS[jt];
         }
-      } else {
+        floatx4 dkr;
 #pragma unroll
-        for (int jt = 0; jt < JT; ++jt) tail[jt] = dU[jt];
+        for (int r = 0; r < 4; ++r) {
+          dX[jt][r] = mask_keep(mw[jt], r, ggm[r] * dYR[jt][r]);
+          dkr[r] = -ggm[r] * egr[r] * dYR[jt][r];
+        }
+        store_acc_tile<TT>(blk(wDX), jt * 16, 16 * ww, dX[jt]);
+        if constexpr (RDN) store_acc_tile<TT>(blk(wDKR), jt * 16, 16 * ww, dkr);
+        store_acc_tile<TT>(Yst, jt * 16, 16 * ww, dYR[jt]);
       }
-      {   // dv = dX + diag(b) tail into the column-major stage: this lane's 4
-          // tokens t0 .. t0 + 3 of column 16 jt + (lane & 15), one 16-byte store
-        const int t0 = 16 * ww + acc_row(0);
-        const floatx4 b4 = *reinterpret_cast<const floatx4*>(gbt + t0);
+      // gradient w.r.t. this chunk's end states (tile maxima from
+      // publish_state_max: dS, dR are unchanged since), each 16-row tile
+      // divided by its power of two, in the state-copy layout
 #pragma unroll
-        for (int jt = 0; jt < JT; ++jt) {
-          floatx4 val;
+      for (int st = 0; st < 2; ++st) {
 #pragma unroll
-          for (int r = 0; r < 4; ++r) val[r] = __builtin_fmaf(b4[r], tail[jt][r], dX[jt][r]) * isig;
-          *reinterpret_cast<floatx4*>(dvst + (jt * 16 + acc_col()) * L::kDvLd + t0) = val;
+        for (int it = 0; it < IT; ++it) {
+          const int e = pow2_scale_exp(st ? tmR[it] : tmS[it]);
+          const float sc = exp2_int(-e);
+#pragma unroll
+          for (int jt = 0; jt < JT; ++jt)
+            store_state_copy<TSC>(ckst + st * BV * (TSC::kRowB / 2), jt * 16, ww * (DK / 4) + 16 * it,
+                                  (st ? dR[it][jt] : dS[it][jt]) * sc);
+          ckscl[st * (DK / 16) + ww * IT + it] = exp2_int(e);   // every lane: the wave-uniform value
         }
       }
-      {   // gradient w.r.t. this chunk's end states (tile maxima from
-          // publish_state_max: dS, dR are unchanged since), each 16-row tile
-          // divided by its power of two, in the state-copy layout
-#pragma unroll
-        for (int st = 0; st < 2; ++st) {
-#pragma unroll
-          for (int it = 0; it < IT; ++it) {
-            const int e = pow2_scale_exp(st ? tmR[it] : tmS[it]);
-            const float sc = exp2_int(-e);
-#pragma unroll
-            for (int jt = 0; jt < JT; ++jt)
-              store_state_copy<TSC>(ckst + st * BV * (TSC::kRowB / 2), jt * 16, ww * (DK / 4) + 16 * it,
-                                    (st ? dR[it][jt] : dS[it][jt]) * sc);
-            ckscl[st * (DK / 16) + ww * IT + it] = exp2_int(e);   // every lane: the wave-uniform value
-          }
-        }
-      }
-      if constexpr (RDN) {   // dU is dead: its slot keeps dY for the block store
-#pragma unroll
-        for (int jt = 0; jt < JT; ++jt) store_acc_tile<TT>(blk(bDUR_DU), jt * 16, 16 * ww, tail[jt]);
-      }
-    } else {
-      if constexpr (RDN) {   // T^S was read into registers before the previous barrier
-        if (c > 0) dma_mat(c - 1, kMatTS, 0, 1);
-      }
-    }
-    barrier_lds();
-
-    // ======== phase 6: state gradients at the chunk start ========
-    if constexpr (CH) {
-      typedef Mfma<XT> MX;
-      const float eS = edge[0], eR = edge[1];
-      constexpr int KS2 = kChunk / MX::kStep;
-      constexpr int NF = IT * KS2;
+      gbt = gate4(0);
+      egsp = gate4(3);
       int fr0[NF], fk0[NF];
 #pragma unroll
-      for (int f = 0; f < NF; ++f) {
-        fr0[f] = ww * (DK / 4) + (f / KS2) * 16;
-        fk0[f] = (f % KS2) * MX::kStep;
+      for (int x = 0; x < NF; ++x) {
+        fr0[x] = ww * (DK / 4) + (x / XS) * 16;
+        fk0[x] = (x % XS) * MX::kStep;
       }
-      typename MX::frag qf[NF], kf[NF];
-      frags_tr_sync<TKQ, XT, NF>(QT, fr0, fk0, qf);
-      frags_tr_sync<TKQ, XT, NF>(KT, fr0, fk0, kf);
-      auto acc = [&](floatx4& d, const typename MX::frag* a, const XT* b, int it, int jt) {
+      frags_tr_sync<TKQ, XT, NF>(QT, fr0, fk0, qt);
+      frags_tr_sync<TKQ, XT, NF>(KT, fr0, fk0, kt);
+    } else {
+      if (c > 0) {
+        issue_do(c - 1);   // in the chain's tiles since phase 1
+        pin();
+        load_rows(Qn, qg, c - 1);
+      }
+      if (c + 1 < nch) store_block(c + 1, 1);
+      // this chunk's MG (from phase 4 of the later one); since then the
+      // checkpoints (2 IT + 1 stores) and three blocks
+      wait_vmem_but<2 * IT + 4>();
+    }
+    barrier_lds();
+
+    // ======== phase 3: dY = Z - (MG T^S)^T dX, dKS; dv; dR at the chunk start, dS but for dKS ========
+    if constexpr (CH) {
+      typename MX::frag fx[JT][XS], fc[JT][XS], fb[JT][XS], fr[JT][XS];
+      tok_frags(blk(wDX), fx);
+      tok_frags(blk(wQDC), fc);
+      tok_frags(blk(wQDB), fb);
+      if constexpr (RDN) tok_frags(blk(wDKR), fr);
+      const float eS = gvec(7)[0], eR = gvec(7)[1];
+      sched_fence();
+      const uint32_t m[1] = {lds_addr(mat(kMatMG))};
+      MatFrags<f16>* const x[1] = {&aMG};
+      packed_cols_frags_sync<1>(m, ww, zero16, x);
+      floatx4 b[JT];
 #pragma unroll
-        for (int ks = 0; ks < KS2; ++ks)
-          d = MX::mma(a[it * KS2 + ks], TT::template frag<MX>(b, jt * 16, ks * MX::kStep), d);
-      };
+      for (int jt = 0; jt < JT; ++jt) b[jt] = zero4();
+      mma_tok(b, aMG, fx);
 #pragma unroll
       for (int it = 0; it < IT; ++it)
 #pragma unroll
         for (int jt = 0; jt < JT; ++jt) {
           dS[it][jt] *= eS;
           dR[it][jt] *= eR;
-          acc(dS[it][jt], qf, blk(bQDB), it, jt);
-          acc(dS[it][jt], kf, blk(RDN ? bDB_DKS : bDKR), it, jt);
-          acc(dR[it][jt], qf, blk(bQDC), it, jt);
-          if constexpr (RDN) acc(dR[it][jt], kf, blk(bDKR), it, jt);
         }
+      mma_state(dR, qt, fc);
+      mma_state(dS, qt, fb);
+      if constexpr (RDN) mma_state(dR, kt, fr);
+#pragma unroll
+      for (int jt = 0; jt < JT; ++jt) {
+        floatx4 dks, val;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          Z[jt][r] -= b[jt][r];   // dY
+          dks[r] = -egsp[r] * dX[jt][r];
+          if constexpr (RDN) dks[r] -= gbt[r] * egs[r] * Z[jt][r];
+          val[r] = __builtin_fmaf(gbt[r], Z[jt][r], dX[jt][r]) * isig;   // dv = dX + diag(b) dY
+        }
+        store_acc_tile<TT>(blk(wDB_DKS), jt * 16, 16 * ww, dks);
+        store_acc_tile<TT>(blk(wDY), jt * 16, 16 * ww, Z[jt]);
+        // dv into the column-major stage: this lane's 4 tokens of its column
+        *reinterpret_cast<floatx4*>(dvst + (jt * 16 + acc_col()) * L::kDvLd + 16 * ww + acc_row(0)) = val;
+      }
+    } else {
+      if (c > 0) {
+        // the next rows, dO and gates have landed here: the first use of the
+        // rows waits for every memory operation of the phases before (the
+        // compiler does not count past an LDS-DMA), and for none after it
+        to_f16_rows(Kn);
+        to_f16_rows(Qn);
+        pin();
+        issue_mats(c - 1);   // in the chain's registers since phase 2
+      }
+    }
+    barrier_lds();
+
+    // ======== phase 4: dS at the chunk start; maxima ========
+    if constexpr (CH) {
+      typename MX::frag fk[JT][XS];
+      tok_frags(blk(wDB_DKS), fk);
+      mma_state(dS, kt, fk);
       publish_state_max();
     } else {
-      wait_vmem();   // the next chunk's DMA; the barrier below publishes it
-      if (c > 0) write_gates(c - 1);
+      if (c > 0) {   // the mask and MG are in the chain's registers since phases 2, 3
+        issue_mask(c - 1);
+        dma_mat(c - 1, kMatMG, 2);
+      }
+      pin();
+      store_dv(c);
+      store_ckpt(c, 0);
     }
     barrier_lds();
   }
 
   if constexpr (CH) {
-    if (p.dS0 || p.dR0) {
 #pragma unroll
-      for (int it = 0; it < IT; ++it)
+    for (int it = 0; it < IT; ++it)
 #pragma unroll
-        for (int jt = 0; jt < JT; ++jt)
-#pragma unroll
-          for (int r = 0; r < 4; ++r) {
-            const int i = ww * (DK / 4) + it * 16 + acc_row(r), j = j0 + jt * 16 + acc_col();
-            if (p.dS0) p.dS0[state_off + (int64_t)i * DV + j] = dS[it][jt][r] * isig;
-            if (p.dR0) p.dR0[state_off + (int64_t)i * DV + j] = dR[it][jt][r] * isig;
-          }
-    }
+      for (int jt = 0; jt < JT; ++jt) {
+        dS[it][jt] *= isig;
+        dR[it][jt] *= isig;
+      }
+    if (p.dS0) save_state_f32<IT, JT>(dS, p.dS0 + state_off + j0, DV, ww * (DK / 4));
+    if (p.dR0) save_state_f32<IT, JT>(dR, p.dR0 + state_off + j0, DV, ww * (DK / 4));
   } else if (nch > 0) {   // the first chunk's outputs
     store_block(0, 0);
     store_block(0, 1);
     store_block(0, 2);
-    store_ckpt(0);
-    store_dv(0);
+    store_ckpt(0, 1);
   }
   };
   if (chain) run(std::true_type{});

@@ -306,6 +306,12 @@ __host__ __device__ constexpr int tri_off(int t, int s) {
   return (((t >> 4) * ((t >> 4) + 1)) / 2 + (s >> 4)) * 256 + (t & 15) * 16 + (s & 15);
 }
 
+// A pointer into LDS as the 32-bit address that LDS instructions take.
+__device__ __forceinline__ uint32_t lds_addr(const void* p) {
+  typedef __attribute__((address_space(3))) const char* lds_ptr;
+  return (uint32_t)(uintptr_t)(lds_ptr)(reinterpret_cast<const char*>(p));
+}
+
 // LDS transpose read of 16-bit elements (gfx950 ds_read_b64_tr_b16).  In each
 // 16-lane group, the 8-byte pieces the lanes address form a 16 x 4 array D
 // (row j: the group's lane j); lane i of the group receives D[i / 4 + 4 e][i % 4]
@@ -375,6 +381,31 @@ __device__ __forceinline__ uint4 tile_token_rows16_sync(const void* base, int t0
                c[0] | ((uint32_t)c[1] << 16), c[2] | ((uint32_t)c[3] << 16)};
 }
 
+// The same for N tiles at once (tile[n], columns t0[n] ..), all reads issued
+// before the one wait.
+template <class TL, int N, typename T>
+__device__ __forceinline__ void tile_token_rows16_sync(T* const (&tile)[N], const int (&t0)[N], uint4 (&out)[N]) {
+  typedef __attribute__((address_space(3))) const char* lds_ptr;
+  const int lane = threadIdx.x & 63, jj = lane & 15, j = 8 * (lane >> 4) + (jj >> 2);
+  u16x4 a[N], c[N];
+#pragma unroll
+  for (int n = 0; n < N; ++n) {
+    const int t = t0[n] + 4 * (jj & 3);
+    const char* b = reinterpret_cast<const char*>(tile[n]);
+    const uint32_t a0 = (uint32_t)(uintptr_t)(lds_ptr)(b + TL::off(j, t));
+    const uint32_t a1 = (uint32_t)(uintptr_t)(lds_ptr)(b + TL::off(j + 4, t));
+    asm volatile("ds_read_b64_tr_b16 %0, %1" : "=v"(a[n]) : "v"(a0));
+    asm volatile("ds_read_b64_tr_b16 %0, %1" : "=v"(c[n]) : "v"(a1));
+  }
+  asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+#pragma unroll
+  for (int n = 0; n < N; ++n) {
+    asm volatile("" : "+v"(a[n]), "+v"(c[n]));
+    out[n] = uint4{a[n][0] | ((uint32_t)a[n][1] << 16), a[n][2] | ((uint32_t)a[n][3] << 16),
+                   c[n][0] | ((uint32_t)c[n][1] << 16), c[n][2] | ((uint32_t)c[n][3] << 16)};
+  }
+}
+
 // Four 4-byte LDS values at p, p + stride, p + 2 stride, p + 3 stride (bytes)
 // as 16 bytes, issued as inline assembly like lds_read16_sync (no drain of
 // in-flight LDS-DMA) and waited for by the function.
@@ -388,6 +419,17 @@ __device__ __forceinline__ uint4 lds_read4x1_sync(const void* p, int stride) {
   asm volatile("ds_read_b32 %0, %1" : "=v"(w) : "v"(a + 3 * stride));
   asm volatile("s_waitcnt lgkmcnt(0)" : "+v"(x), "+v"(y), "+v"(z), "+v"(w));
   return uint4{x, y, z, w};
+}
+
+// N 4-byte LDS values at p[0], p[idx[n]] .., issued and waited for alike.
+template <int N>
+__device__ __forceinline__ void lds_read_f32_sync(const float* p, const int (&idx)[N], float (&out)[N]) {
+  const uint32_t a = lds_addr(p);
+#pragma unroll
+  for (int n = 0; n < N; ++n) asm volatile("ds_read_b32 %0, %1" : "=v"(out[n]) : "v"(a + 4 * idx[n]));
+  asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+#pragma unroll
+  for (int n = 0; n < N; ++n) asm volatile("" : "+v"(out[n]));
 }
 
 // 16 bytes from LDS, issued as inline assembly so that the compiler does not
@@ -700,38 +742,40 @@ __device__ __forceinline__ MatFrags<f16> packed_rows_frags(const f16* M, int bi,
   return a;
 }
 
-// A-operand fragments of rows 16 bj .. 16 bj + 15 of the transpose of a
-// packed fp16 matrix in LDS (its columns 16 bj ..), from transpose reads as
-// in swz_cols_frags_sync (inline assembly, waited for inside, so that the
-// compiler does not drain in-flight LDS-DMA first); `zero` is 16 zero bytes
-// in LDS.  Lane (q, j) of the read for k-rows 32 s + 8 q + 4 n .. addresses
+// A-operand fragments of rows 16 bj .. 16 bj + 15 of the transposes of N
+// packed fp16 matrices in LDS (their columns 16 bj ..), from transpose reads
+// as in swz_cols_frags_sync (inline assembly, all issued, then waited for
+// inside, so that the compiler does not drain in-flight LDS-DMA first);
+// matrices and `zero`, 16 zero bytes, by their LDS addresses (lds_addr).  Lane (q, j) of the read for k-rows 32 s + 8 q + 4 n .. addresses
 // 4 elements of matrix row 32 s + 8 q + (j >> 2) + 4 n at column
 // 16 bj + 4 (j & 3).
-__device__ __forceinline__ MatFrags<f16> packed_cols_frags_sync(const f16* M, int bj, const f16* zero) {
-  typedef __attribute__((address_space(3))) const char* lds_ptr;
+template <int N>
+__device__ __forceinline__ void packed_cols_frags_sync(const uint32_t (&M)[N], int bj, uint32_t zero,
+                                                       MatFrags<f16>* const (&out)[N]) {
   const int lane = threadIdx.x & 63, j = lane & 15, q = lane >> 4;
   const int h = (j & 3) >> 1, sub = (j & 1) * 8;
-  const char* b = reinterpret_cast<const char*>(M);
-  u16x4 x[2], y[2];
+  u16x4 x[N][2], y[N][2];
 #pragma unroll
-  for (int s = 0; s < 2; ++s) {
-    const int bi = 2 * s + (q >> 1), r = 8 * (q & 1) + (j >> 2);
-    const int blk = (bi * (bi + 1) / 2 + bj) * 512;
-    const char* p0 = bj <= bi ? b + blk + pk_pos<true>(r, h) * 16 + sub : reinterpret_cast<const char*>(zero);
-    const char* p1 = bj <= bi ? b + blk + pk_pos<true>(r + 4, h) * 16 + sub : reinterpret_cast<const char*>(zero);
-    const uint32_t a0 = (uint32_t)(uintptr_t)(lds_ptr)(p0);
-    const uint32_t a1 = (uint32_t)(uintptr_t)(lds_ptr)(p1);
-    asm volatile("ds_read_b64_tr_b16 %0, %1" : "=v"(x[s]) : "v"(a0));
-    asm volatile("ds_read_b64_tr_b16 %0, %1" : "=v"(y[s]) : "v"(a1));
-  }
-  asm volatile("s_waitcnt lgkmcnt(0)" : "+v"(x[0]), "+v"(y[0]), "+v"(x[1]), "+v"(y[1]));
-  MatFrags<f16> a;
+  for (int n = 0; n < N; ++n) {
 #pragma unroll
-  for (int s = 0; s < 2; ++s) {
-    const u16x8 v = {x[s][0], x[s][1], x[s][2], x[s][3], y[s][0], y[s][1], y[s][2], y[s][3]};
-    a.f[s] = __builtin_bit_cast(typename Mfma<f16>::frag, v);
+    for (int s = 0; s < 2; ++s) {
+      const int bi = 2 * s + (q >> 1), r = 8 * (q & 1) + (j >> 2);
+      const int blk = (bi * (bi + 1) / 2 + bj) * 512;
+      const uint32_t a0 = bj <= bi ? M[n] + blk + pk_pos<true>(r, h) * 16 + sub : zero;
+      const uint32_t a1 = bj <= bi ? M[n] + blk + pk_pos<true>(r + 4, h) * 16 + sub : zero;
+      asm volatile("ds_read_b64_tr_b16 %0, %1" : "=v"(x[n][s]) : "v"(a0));
+      asm volatile("ds_read_b64_tr_b16 %0, %1" : "=v"(y[n][s]) : "v"(a1));
+    }
   }
-  return a;
+  asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+#pragma unroll
+  for (int n = 0; n < N; ++n)
+#pragma unroll
+    for (int s = 0; s < 2; ++s) {
+      asm volatile("" : "+v"(x[n][s]), "+v"(y[n][s]));
+      const u16x8 v = {x[n][s][0], x[n][s][1], x[n][s][2], x[n][s][3], y[n][s][0], y[n][s][1], y[n][s][2], y[n][s][3]};
+      out[n]->f[s] = __builtin_bit_cast(typename Mfma<f16>::frag, v);
+    }
 }
 
 template <typename T>
@@ -966,6 +1010,47 @@ __device__ __forceinline__ uint32_t cvt_pk_f16(float a, float b) {
   return __builtin_bit_cast(uint32_t, f16x2{to_f16(a), to_f16(b)});
 }
 
+// The clip mask of a (chunk, head) is stored value-major, [DV][64] bytes (a
+// lane's four accumulator rows of one column are one 4-byte word), 1 where
+// |x| <= clip; rows past a sequence's end hold anything.
+__host__ __device__ inline int64_t mask_off(int64_t gc, int h, int H, int DV) { return (gc * H + h) * (int64_t)DV * kChunk; }
+
+// Four mask bytes from a lane's four residuals.
+__device__ __forceinline__ uint32_t mask_word(const floatx4& x, float clip) {
+  uint32_t m = 0;
+#pragma unroll
+  for (int r = 0; r < 4; ++r) m |= (clip < 0.f || fabsf(x[r]) <= clip) ? 1u << (8 * r) : 0u;
+  return m;
+}
+
+// x where byte r of the mask word is 1, else 0.
+__device__ __forceinline__ float mask_keep(uint32_t m, int r, float x) {
+  return __uint_as_float(__float_as_uint(x) & (uint32_t)__builtin_amdgcn_sbfe((int)m, 8 * r, 1));
+}
+
+// LDS-DMA of the mask of BV value columns (global: mask_off + 64 j0) by wave w
+// of the BV / 16 waves that move 1 KiB each: column j's 16-byte piece p goes
+// to position p ^ ((j >> 2) & 3) of its 64 bytes, so that the words that the
+// 16 columns of an accumulator tile read fall in distinct banks.
+__device__ __forceinline__ void dma_mask(const uint8_t* src, uint8_t* lds, int w) {
+  const int P = w * 64 + (threadIdx.x & 63), j = P >> 2, p = (P & 3) ^ ((j >> 2) & 3);
+  dma16(src + (uint32_t)(j * kChunk + p * 16), lds + w * 1024);
+}
+// The mask word of column j, rows t0 .. t0 + 3 (t0 a multiple of 4).
+__device__ __forceinline__ uint32_t mask_at(const uint8_t* lds, int j, int t0) {
+  return *reinterpret_cast<const uint32_t*>(lds + j * kChunk + (((t0 >> 4) ^ ((j >> 2) & 3)) << 4) + (t0 & 15));
+}
+
+// Unsigned maxima of the two 16-bit halves.
+__device__ __forceinline__ uint32_t pk_max_u16(uint32_t a, uint32_t b) {
+  typedef u16 u16x2 __attribute__((ext_vector_type(2)));
+  const u16x2 x = __builtin_bit_cast(u16x2, a), y = __builtin_bit_cast(u16x2, b);
+  return __builtin_bit_cast(uint32_t, __builtin_elementwise_max(x, y));
+}
+
+// Instruction-scheduling fence: nothing moves across it.
+__device__ __forceinline__ void sched_fence() { __builtin_amdgcn_sched_barrier(0); }
+
 // Two fp32 values given as bits, rounded to a bf16 pair.
 __device__ __forceinline__ uint32_t cvt_pk_bf16(uint32_t a, uint32_t b) {
   return __builtin_bit_cast(uint32_t, bf16x2{(__bf16)__uint_as_float(a), (__bf16)__uint_as_float(b)});
@@ -1080,6 +1165,27 @@ __device__ __forceinline__ void save_state_f32(const floatx4 (&acc)[IT][JT], flo
 #pragma unroll
       for (int r = 0; r < 4; ++r)
         dst[(int64_t)(row0 + 16 * it + acc_row(r)) * ld + 16 * jt + acc_col()] = acc[it][jt][r];
+}
+
+// A state's accumulator tiles from fp32 rows (base + off: its first row's
+// first column; row stride ld), rows row0 ..; zeros without a state.  One
+// branch for all of them, so that the loads are in flight together (a
+// condition per element costs a branch and a wait for each).
+template <int IT, int JT>
+__device__ __forceinline__ void load_acc_state(floatx4 (&acc)[IT][JT], const float* base, int64_t off, int64_t ld,
+                                               int row0) {
+#pragma unroll
+  for (int it = 0; it < IT; ++it)
+#pragma unroll
+    for (int jt = 0; jt < JT; ++jt) acc[it][jt] = zero4();
+  if (!base) return;
+#pragma unroll
+  for (int it = 0; it < IT; ++it)
+#pragma unroll
+    for (int jt = 0; jt < JT; ++jt)
+#pragma unroll
+      for (int r = 0; r < 4; ++r)
+        acc[it][jt][r] = base[off + (int64_t)(row0 + 16 * it + acc_row(r)) * ld + 16 * jt + acc_col()];
 }
 
 // Stores the 4 accumulator rows of this lane, column-major into LDS as a
@@ -1209,6 +1315,26 @@ __device__ __forceinline__ float wave_inclusive_scan(float x) {
   return x;
 }
 
+// The scans' gate vectors of a chunk from its gate block in LDS, by one wave
+// (lane = token): dst[k * 64 + t] = beta, gamma, e^{g_t}, e^{g_{t-1}}, e^{h_t},
+// e^{g_C - g_t}, e^{h_C - h_t} for k = 0 .. 6, then e^{g_C}, e^{h_C} at k = 7.  The
+// block is read as inline assembly: the wave's LDS-DMA may be in flight.
+__device__ __forceinline__ void write_gate_vectors(const float* graw, float* dst) {
+  const int t = threadIdx.x & 63;
+  const int idx[7] = {t, t > 0 ? t - 1 : 0, kChunk - 1, 64 + t, 64 + kChunk - 1, 128 + t, 192 + t};
+  float x[7];
+  lds_read_f32_sync<7>(graw, idx, x);
+  dst[t] = x[5];
+  dst[kChunk + t] = x[6];
+  dst[2 * kChunk + t] = __expf(x[0]);
+  dst[3 * kChunk + t] = t > 0 ? __expf(x[1]) : 1.f;
+  dst[4 * kChunk + t] = __expf(x[3]);
+  dst[5 * kChunk + t] = __expf(x[2] - x[0]);
+  dst[6 * kChunk + t] = __expf(x[4] - x[3]);
+  dst[7 * kChunk + 0] = __expf(x[2]);   // every lane stores the same value
+  dst[7 * kChunk + 1] = __expf(x[4]);
+}
+
 // Gate block of one (chunk, head), as written by the prep kernel:
 //   [0..63] g  : inclusive cumulative log-decay of S inside the chunk
 //   [64..]  h  : same for R
@@ -1220,10 +1346,10 @@ constexpr int kGateBlock = 4 * kChunk;
 // 16 x 16 blocks, stored packed (tri_off):
 enum : int {
   kMatTS = 0,   // T^S = (I + A^S)^{-1}                     (RDN only)
-  kMatMG = 1,   // e^{g_{t-1} - g_s} (k_t . k_s)       s < t
-  kMatMP = 2,   // e^{g_t - g_s}     (q_t . k_s)       s < t
+  kMatMG = 1,   // MG T^S, MG = e^{g_{t-1} - g_s} (k_t . k_s)  s < t    (RLA: T = I)
+  kMatMP = 2,   // MP T^S, MP = e^{g_t - g_s}     (q_t . k_s)  s < t
   kMatTR = 3,   // T^R = (I + A^R)^{-1}                     (RDN only)
-  kMatMR = 4,   // e^{h_t - h_s}     (q_t . k_s)       s <= t
+  kMatMR = 4,   // MR T^R, MR = e^{h_t - h_s}     (q_t . k_s)  s <= t
   kNumMats = 5
 };
 

@@ -5,14 +5,16 @@
 //
 // The workgroup walks the sequence chunk by chunk.  S and R (d_k x BV fp32,
 // stored transposed like the ABI) stay in MFMA accumulators for the whole
-// sequence.  Per chunk, with the prep kernel's gate sums and matrices:
+// sequence.  Per chunk, with the prep kernel's gate sums and matrices (its
+// MG, MP, MR are multiplied by T^S, T^S, T^R already, so that U = T^S Y and
+// what depends on it come out of Y together; RLA: T = I):
 //   KS = K S0, QS = Q S0, KR = K R0, QR = Q R0                 (MFMA)
-//   RDN: U = T^S diag(b) (V - e^{g} KS)     RLA: U = diag(b) V
-//   p   = e^{g_{t-1}} KS + MG U         = S_{t-1} k_t         (Sec. 3.4)
+//   RDN: Y = diag(b) (V - e^{g} KS)     RLA: Y = diag(b) V;    U = T^S Y
+//   p   = e^{g_{t-1}} KS + MG T^S Y     = S_{t-1} k_t         (Sec. 3.4)
 //   r   = clip(V - p)                   fused, never written to HBM
-//   b_t = e^{g} QS + MP U               = aS_t S_{t-1} q_t
-//   RDN: UR = T^R diag(gamma) (r - e^{h} KR)   RLA: UR = diag(gamma) r
-//   c_t = e^{h} QR + MR UR              = R_t q_t
+//   b_t = e^{g} QS + MP T^S Y           = aS_t S_{t-1} q_t
+//   RDN: YR = diag(gamma) (r - e^{h} KR)   RLA: YR = diag(gamma) r;   UR = T^R YR
+//   c_t = e^{h} QR + MR T^R YR          = R_t q_t
 //   o   = b + diag(gamma) c
 //   S  <- e^{g_C} S + K^T diag(e^{g_C - g}) U,  R likewise with (h, UR)
 // Variants: decayed residual p = e^{g} KS + MG U (= aS_t S_{t-1} k_t, MG with
@@ -59,17 +61,18 @@ struct FwdLayout {
   static constexpr int kMats = kCopies + kNumCopies * kCopyBytes;
   static constexpr int kBufs = kMats + kNumSlots * Swz<XT>::kBytes;
   static constexpr int kBufBytes = BV * TT::kRowB;
-  static constexpr int kVc = kBufs + 5 * kBufBytes;
+  static constexpr int kVc = kBufs + 6 * kBufBytes;
   static constexpr int kVBytes = kChunk * BV * (int)sizeof(IN);
   static constexpr int kGraw = kVc + kVBytes;
   static constexpr int kGates = kGraw + kGateBlock * 4;
   // output staging, so that o, the clip mask and r leave in 16-byte stores:
-  // r value-major (token tile), mask token-major [64][BV] bytes, o
+  // r value-major (token tile), mask value-major [BV][kMstLd] bytes, o
   // token-major [64][BV + 4] fp32
   static constexpr int kRst = kGates + 10 * kChunk * 4;
   static constexpr int kMst = kRst + kBufBytes;
   static constexpr int kLdO = BV + 4;
-  static constexpr int kOst = kMst + kChunk * BV;
+  static constexpr int kMstLd = kChunk + 16;
+  static constexpr int kOst = kMst + BV * kMstLd;
   static constexpr int kBytes = kOst + kChunk * kLdO * 4;
   static_assert(kVBytes == 4 * 1024, "V block = one DMA instruction per wave");
   static_assert(kBytes <= 160 * 1024, "forward scan LDS");
@@ -131,11 +134,13 @@ __global__ __launch_bounds__(kThreads) void fwd_scan_kernel(OpParams p) {
   auto mat = [&](int m, int buf) {
     return reinterpret_cast<XT*>(smem + L::kMats + L::slot(m, buf) * Swz<XT>::kBytes);
   };
-  XT* Yt = reinterpret_cast<XT*>(smem + L::kBufs);               // Y, later YR
-  XT* Ut = reinterpret_cast<XT*>(smem + L::kBufs + 1 * L::kBufBytes);
-  XT* URt = reinterpret_cast<XT*>(smem + L::kBufs + 2 * L::kBufBytes);
-  XT* DUt = reinterpret_cast<XT*>(smem + L::kBufs + 3 * L::kBufBytes);
-  XT* DURt = reinterpret_cast<XT*>(smem + L::kBufs + 4 * L::kBufBytes);
+  XT* Yt = reinterpret_cast<XT*>(smem + L::kBufs);
+  XT* YRt = reinterpret_cast<XT*>(smem + L::kBufs + 1 * L::kBufBytes);
+  XT* DUt = reinterpret_cast<XT*>(smem + L::kBufs + 2 * L::kBufBytes);
+  XT* DURt = reinterpret_cast<XT*>(smem + L::kBufs + 3 * L::kBufBytes);
+  // U, UR for the saved blocks (RLA: Y, YR themselves)
+  XT* Ut = RDN ? reinterpret_cast<XT*>(smem + L::kBufs + 4 * L::kBufBytes) : Yt;
+  XT* URt = RDN ? reinterpret_cast<XT*>(smem + L::kBufs + 5 * L::kBufBytes) : YRt;
   IN* Vc = reinterpret_cast<IN*>(smem + L::kVc);
   float* graw = reinterpret_cast<float*>(smem + L::kGraw);   // prep's gate block
   float* gbt = reinterpret_cast<float*>(smem + L::kGates);   // beta
@@ -174,16 +179,8 @@ __global__ __launch_bounds__(kThreads) void fwd_scan_kernel(OpParams p) {
 
   // ---- initial states into accumulators (wave w: rows [w*DK/4, (w+1)*DK/4)) ----
   floatx4 Sacc[IT][JT], Racc[IT][JT];
-#pragma unroll
-  for (int it = 0; it < IT; ++it)
-#pragma unroll
-    for (int jt = 0; jt < JT; ++jt)
-#pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const int i = w * (DK / 4) + it * 16 + acc_row(r), j = j0 + jt * 16 + acc_col();
-        Sacc[it][jt][r] = p.S0 ? p.S0[state_off + (int64_t)i * DV + j] : 0.f;
-        Racc[it][jt][r] = p.R0 ? p.R0[state_off + (int64_t)i * DV + j] : 0.f;
-      }
+  load_acc_state<IT, JT>(Sacc, p.S0, state_off + j0, DV, w * (DK / 4));
+  load_acc_state<IT, JT>(Racc, p.R0, state_off + j0, DV, w * (DK / 4));
   auto write_state_copies = [&]() {
 #pragma unroll
     for (int it = 0; it < IT; ++it)
@@ -205,7 +202,7 @@ __global__ __launch_bounds__(kThreads) void fwd_scan_kernel(OpParams p) {
   // ---- staging of chunk c+1 while chunk c computes ----
   //   K, Q fragments: register prefetch (issued after P1, when chunk c's are dead)
   //   V block, gate block, T^R, MR: LDS-DMA after P1 (V, gates dead; T^R/MR
-  //     double-buffered); T^S, MG, MP: LDS-DMA after P3 (their last use)
+  //     double-buffered); T^S, MG, MP: LDS-DMA after P2 (their last use)
   // Completion: every wave waits for its vector memory operations and the
   // whole workgroup passes a barrier at the end of chunk c.
   typename MI::frag Kn[KS_STEPS], Qn[KS_STEPS];
@@ -373,13 +370,11 @@ __global__ __launch_bounds__(kThreads) void fwd_scan_kernel(OpParams p) {
         if constexpr (!BF) vloc[jt][r] = to_f<IN>(Vc[t * BV + jt * 16 + acc_col()]);
         y[r] = RDN ? gbt[t] * __builtin_fmaf(-egs[t], KS[jt][r], vloc[jt][r]) : gbt[t] * vloc[jt][r];
       }
-      if constexpr (RDN) {
-        store_acc_tile<TT>(Yt, jt * 16, 16 * w, y);
-      } else {
+      store_acc_tile<TT>(Yt, jt * 16, 16 * w, y);
+      if constexpr (!RDN) {
         floatx4 du;
 #pragma unroll
         for (int r = 0; r < 4; ++r) du[r] = dls[16 * w + acc_row(r)] * y[r];
-        store_acc_tile<TT>(Ut, jt * 16, 16 * w, y);
         store_acc_tile<TT>(DUt, jt * 16, 16 * w, du);
       }
     }
@@ -387,62 +382,53 @@ __global__ __launch_bounds__(kThreads) void fwd_scan_kernel(OpParams p) {
     // products (each matrix landed in an earlier chunk)
     MatFrags<XT> aTS, aMG, aMP;
     if constexpr (RDN) aTS = swz_rows_frags<XT>(mat(kMatTS, 0), 16 * w);
-    else {
-      aMG = swz_rows_frags<XT>(mat(kMatMG, 0), 16 * w);
-      aMP = swz_rows_frags<XT>(mat(kMatMP, 0), 16 * w);
-    }
+    aMG = swz_rows_frags<XT>(mat(kMatMG, 0), 16 * w);
+    aMP = swz_rows_frags<XT>(mat(kMatMP, 0), 16 * w);
     barrier_lds();
     if (c + 1 < nch) {
       issue_regs(c + 1);
       issue_early(c + 1);
     }
 
-    if constexpr (RDN) {   // ---- P2: U = T^S Y ----
-#pragma unroll
-      for (int jt = 0; jt < JT; ++jt) {
-        floatx4 u = zero4();
-        mma_frags<XT>(u, aTS, Yt, jt * 16);
-        floatx4 du;
-#pragma unroll
-        for (int r = 0; r < 4; ++r) du[r] = dls[16 * w + acc_row(r)] * u[r];
-        store_acc_tile<TT>(Ut, jt * 16, 16 * w, u);
-        store_acc_tile<TT>(DUt, jt * 16, 16 * w, du);
-      }
-      aMG = swz_rows_frags<XT>(mat(kMatMG, 0), 16 * w);
-      aMP = swz_rows_frags<XT>(mat(kMatMP, 0), 16 * w);
-      barrier_lds();
-    }
-
-    // ---- P3: residual, clip, base read-out ----
+    // ---- P2: U = T^S Y; residual, clip, base read-out ----
     // (explicit fmas: every instantiation, saving or not, rounds alike)
     floatx4 base[JT];
 #pragma unroll
     for (int jt = 0; jt < JT; ++jt) {
       floatx4 mgu = zero4(), mpu = zero4();
-      mma_frags<XT>(mgu, aMG, Ut, jt * 16);
-      mma_frags<XT>(mpu, aMP, Ut, jt * 16);
-      floatx4 y, rv;
+      mma_frags<XT>(mgu, aMG, Yt, jt * 16);
+      mma_frags<XT>(mpu, aMP, Yt, jt * 16);
+      if constexpr (RDN) {
+        floatx4 u = zero4(), du;
+        mma_frags<XT>(u, aTS, Yt, jt * 16);
+#pragma unroll
+        for (int r = 0; r < 4; ++r) du[r] = dls[16 * w + acc_row(r)] * u[r];
+        if constexpr (CKPT) store_acc_tile<TT>(Ut, jt * 16, 16 * w, u);
+        store_acc_tile<TT>(DUt, jt * 16, 16 * w, du);
+      }
+      floatx4 y, rv, xv;
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
         const int t = 16 * w + acc_row(r);
         const float x = __builtin_fmaf(-ekp[t], KS[jt][r], vloc[jt][r]) - mgu[r];
+        xv[r] = x;
         const float rr = tanh_resid ? resid_tanh(x, clip)
                                     : (clip < 0.f ? x : fminf(fmaxf(x, -clip), clip));
         rv[r] = rr;
-        if constexpr (CKPT) Mst[t * BV + jt * 16 + acc_col()] = (clip < 0.f || fabsf(x) <= clip) ? 1 : 0;
         base[jt][r] = __builtin_fmaf(eqb[t], QS[jt][r], mpu[r]);
         y[r] = RDN ? ggm[t] * __builtin_fmaf(-egr[t], KR[jt][r], rr) : ggm[t] * rr;
       }
-      if constexpr (RDN) {
-        store_acc_tile<TT>(Yt, jt * 16, 16 * w, y);
-      } else {
+      store_acc_tile<TT>(YRt, jt * 16, 16 * w, y);
+      if constexpr (!RDN) {
         floatx4 du;
 #pragma unroll
         for (int r = 0; r < 4; ++r) du[r] = dlr[16 * w + acc_row(r)] * y[r];
-        store_acc_tile<TT>(URt, jt * 16, 16 * w, y);
         store_acc_tile<TT>(DURt, jt * 16, 16 * w, du);
       }
-      if constexpr (CKPT) store_acc_tile<TT>(Rst, jt * 16, 16 * w, rv);
+      if constexpr (CKPT) {
+        store_acc_tile<TT>(Rst, jt * 16, 16 * w, rv);
+        *reinterpret_cast<uint32_t*>(Mst + (jt * 16 + acc_col()) * L::kMstLd + 16 * w + acc_row(0)) = mask_word(xv, clip);
+      }
     }
     MatFrags<XT> aTR, aMR;
     if constexpr (L::kDB) {   // double-buffered: landed in the previous chunk
@@ -474,27 +460,27 @@ __global__ __launch_bounds__(kThreads) void fwd_scan_kernel(OpParams p) {
       else aMR = swz_rows_frags<XT>(mat(kMatMR, buf), 16 * w);
     }
 
-    if constexpr (RDN) {   // ---- P4: UR = T^R YR ----
+    if constexpr (RDN) {   // ---- P3: UR = T^R YR ----
 #pragma unroll
       for (int jt = 0; jt < JT; ++jt) {
         floatx4 u = zero4();
-        mma_frags<XT>(u, aTR, Yt, jt * 16);
+        mma_frags<XT>(u, aTR, YRt, jt * 16);
         floatx4 du;
 #pragma unroll
         for (int r = 0; r < 4; ++r) du[r] = dlr[16 * w + acc_row(r)] * u[r];
-        store_acc_tile<TT>(URt, jt * 16, 16 * w, u);
+        if constexpr (CKPT) store_acc_tile<TT>(URt, jt * 16, 16 * w, u);
         store_acc_tile<TT>(DURt, jt * 16, 16 * w, du);
       }
       aMR = swz_rows_frags<XT>(mat(kMatMR, buf), 16 * w);
       barrier_lds();
     }
 
-    // ---- P5: correction read-out; o staged, stored after the end barrier ----
+    // ---- P4: correction read-out; o staged, stored after the end barrier ----
     if constexpr (WRITE_O) {
 #pragma unroll
       for (int jt = 0; jt < JT; ++jt) {
         floatx4 mru = zero4();
-        mma_frags<XT>(mru, aMR, URt, jt * 16);
+        mma_frags<XT>(mru, aMR, YRt, jt * 16);
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
           const int t = 16 * w + acc_row(r);
@@ -551,7 +537,7 @@ __global__ __launch_bounds__(kThreads) void fwd_scan_kernel(OpParams p) {
     // flight
     wait_vmem_but<CKPT ? kCkptStores : 0>();
     barrier_lds();
-    if (c + 1 < nch) issue_tail(c + 1);   // single-buffered T^R / MR: waited at P3
+    if (c + 1 < nch) issue_tail(c + 1);   // single-buffered T^R / MR: waited at P2
     // ---- this chunk's staged outputs, in 16-byte stores (the buffers are
     //      next written after the coming chunk's first barrier) ----
     if constexpr (WRITE_O) {
@@ -576,13 +562,10 @@ __global__ __launch_bounds__(kThreads) void fwd_scan_kernel(OpParams p) {
       }
     }
     if constexpr (CKPT) {
-      {   // clip mask rows
-        constexpr int kVPR = BV / 16;
-        const int t = tid / kVPR, v = tid % kVPR;
-        if (tid < kChunk * kVPR && t < len)
-          *reinterpret_cast<uint4*>(p.ck_mask + ((tok + t) * H + h) * (int64_t)DV + j0 + v * 16) =
-              *reinterpret_cast<const uint4*>(Mst + t * BV + v * 16);
-      }
+      // clip mask columns, 16 bytes per thread
+      if (tid < BV * kChunk / 16)
+        *reinterpret_cast<uint4*>(p.ck_mask + mask_off(gc, h, H, DV) + (j0 + (tid >> 2)) * kChunk + (tid & 3) * 16) =
+            *reinterpret_cast<const uint4*>(Mst + (tid >> 2) * L::kMstLd + (tid & 3) * 16);
       // U, UR, r rows (value-major in LDS): rows past the end are zero
       constexpr int kVE = 16 / (int)sizeof(XT);
       constexpr int kVPR = BV / kVE;
@@ -606,18 +589,8 @@ __global__ __launch_bounds__(kThreads) void fwd_scan_kernel(OpParams p) {
     write_state_copies();
   }
 
-  if (p.S_fin || p.R_fin) {
-#pragma unroll
-    for (int it = 0; it < IT; ++it)
-#pragma unroll
-      for (int jt = 0; jt < JT; ++jt)
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          const int i = w * (DK / 4) + it * 16 + acc_row(r), j = j0 + jt * 16 + acc_col();
-          if (p.S_fin) p.S_fin[state_off + (int64_t)i * DV + j] = Sacc[it][jt][r];
-          if (p.R_fin) p.R_fin[state_off + (int64_t)i * DV + j] = Racc[it][jt][r];
-        }
-  }
+  if (p.S_fin) save_state_f32<IT, JT>(Sacc, p.S_fin + state_off + j0, DV, w * (DK / 4));
+  if (p.R_fin) save_state_f32<IT, JT>(Racc, p.R_fin + state_off + j0, DV, w * (DK / 4));
 }
 
 // ---------------------------------------------------------------------------
@@ -635,19 +608,31 @@ __global__ __launch_bounds__(kThreads) void fwd_scan_kernel(OpParams p) {
 //     matrices, the gate values) — so it overlaps the chain instead of
 //     stalling it.
 // Per chunk (phase: chain waves | side waves):
-//   1: K^T commit; KS, KR, QS, QR;               | the previous chunk's o rows;
-//      Y = diag(b)(V - e^g KS)                     DMA of the next chunk's V, MG,
-//                                                   MP, T^R, MR; its gate values;
-//                                                   S checkpoint
-//   2: U = T^S Y; next K, Q rows                  | DMA of the next T^S
-//   3: p, r = clip(V - p), mask, Y^R;             | R checkpoint; U rows
-//      base = e^g QS + MP U
-//   4: U^R = T^R Y^R                              | r rows, mask
-//   5: S, R update; o = base + diag(gamma) c      | wait for the DMA; next gate
-//      into free LDS; state copies                  vectors; U^R rows
-// V, MG, MP, T^R and MR are double-buffered; T^S (read into registers
-// before the first barrier) is refilled from phase 2.  The precision scheme
-// and the arithmetic are those of fwd_scan_kernel, except that the split-
+//   1: K^T commit; KS, KR, QS, QR;               | DMA of the next V, gates; the
+//      Y = diag(b)(V - e^g KS)                      previous o, r rows and mask; S
+//                                                   checkpoint
+//   2: U = T^S Y; p, r = clip(V - p), mask, Y^R;  | the previous U^R rows
+//      base = e^g QS + MP T^S Y; next K, Q rows
+//   3: U^R = T^R Y^R; o = base + diag(gamma) c;   | DMA of the next T^S, MG, MP; R
+//      S update, its copies                         checkpoint; U rows
+//   4: R update, its copies                       | DMA of the next T^R, MR; gate
+//                                                   vectors
+// RLA (U = Y, U^R = Y^R) has no barrier between phases 3 and 4 and refills
+// all its matrices in phase 3.  Within a phase the chain issues what it reads
+// from LDS first and its products in the order in which the next phase waits
+// for them; everything else fills their latencies.  A matrix is read into
+// registers at the start of the phase that multiplies by it and refilled in
+// the next, and its copy is waited for just before that phase in the next
+// chunk: the memory operations are spread over the chunk (all of a chunk's
+// traffic, 100 KiB, goes through one CU's path; in bursts it stalls both roles)
+// and each has most of a chunk to land.
+// A chunk is bound by the serial chain (one workgroup per CU), about 6600
+// cycles, and when it saves for the backward pass on every CU by the chain and
+// the side waves about alike, about 8100.  With U, p and base from Y in one
+// phase instead of two (128 x 128, 16 heads): 1 x 16384 tokens, 64 workgroups,
+// 824 -> 656 us; saving, 4 x 4096 tokens, 256 workgroups, 287 -> 267 us;
+// normalised rows, saving, 16000 tokens packed, 414 -> 344 us.
+// V is double-buffered.  The precision scheme and the arithmetic are those of fwd_scan_kernel, except that the split-
 // state products sum the hi and lo terms per k-step and the checkpoints are
 // formed from the bf16 hi + lo state copies (the fp32 state to ~16 bits)
 // instead of the accumulators.  Q16 rows are split as bf16 hi + lo in the
@@ -659,7 +644,7 @@ struct FwdWsLayout {
   typedef Tile<XT, kChunk> TT;
   typedef TrTile<XT, DK> TK;
   typedef Tile<IN, DK> TSC;
-  static constexpr int kNumSlots = RDN ? 9 : 6;
+  static constexpr int kNumSlots = RDN ? 5 : 3;
   static constexpr int kKT = 0;
   static constexpr int kCopies = kKT + kChunk * TK::kRowB;
   static constexpr int kCopyBytes = BV * TSC::kRowB;
@@ -667,12 +652,13 @@ struct FwdWsLayout {
   static constexpr int kBufs = kMats + kNumSlots * kPkBytes;   // matrices as their ten lower blocks
   static constexpr int kBufBytes = BV * TT::kRowB;
   static constexpr int kVBytes = kChunk * BV * (int)sizeof(IN);
-  static constexpr int kVc = kBufs + 5 * kBufBytes;   // two V blocks (chunk parity)
+  static constexpr int kVc = kBufs + 6 * kBufBytes;   // two V blocks (chunk parity)
   static constexpr int kGateVec = 8 * kChunk;         // floats per chunk's gate vectors
   static constexpr int kGates = kVc + 2 * kVBytes;    // two sets (chunk parity)
   static constexpr int kRst = kGates + 2 * kGateVec * 4;
   static constexpr int kMst = kRst + kBufBytes;
-  static constexpr int kGraw = kMst + kChunk * BV;      // the gate block (one side wave's DMA)
+  static constexpr int kMstLd = kChunk + 16;            // clip mask, value-major [BV][kMstLd] bytes
+  static constexpr int kGraw = kMst + BV * kMstLd;      // the gate block (one side wave's DMA)
   static constexpr int kZero = kGraw + kGateBlock * 4;   // 16 zero bytes (blocks above the diagonal)
   // o of a chunk in fp32, column-major [BV][kOstLd] (the pad keeps the side's
   // 4-byte gathers of one token's 4 columns in distinct banks)
@@ -682,18 +668,10 @@ struct FwdWsLayout {
   static_assert(sizeof(IN) == 2 && BV == 32, "bf16, 32 columns");
   static_assert(kVBytes == 4 * 1024, "V block = one DMA instruction per side wave");
   static_assert(kBytes <= 160 * 1024, "forward scan LDS");
-  // RDN: T^S, then MG, MP, T^R, MR each double-buffered; RLA: MG, MP, MR
-  __device__ static constexpr int slot(int mat, int buf) {
-    if (RDN) {
-      if (mat == kMatTS) return 0;
-      if (mat == kMatMG) return 1 + buf;
-      if (mat == kMatMP) return 3 + buf;
-      if (mat == kMatTR) return 5 + buf;
-      return 7 + buf;
-    }
-    if (mat == kMatMG) return buf;
-    if (mat == kMatMP) return 2 + buf;
-    return 4 + buf;
+  // RDN: T^S, MG, MP, T^R, MR; RLA: MG, MP, MR
+  __device__ static constexpr int slot(int mat) {
+    if (!RDN) return mat == kMatMG ? 0 : mat == kMatMP ? 1 : 2;
+    return mat == kMatTS ? 0 : mat == kMatMG ? 1 : mat == kMatMP ? 2 : mat == kMatTR ? 3 : 4;
   }
 };
 
@@ -714,15 +692,15 @@ __global__ __launch_bounds__(2 * kThreads) void fwd_scan_ws_kernel(OpParams p) {
   IN* Rhi = reinterpret_cast<IN*>(smem + L::kCopies + 1 * L::kCopyBytes);
   IN* Slo = reinterpret_cast<IN*>(smem + L::kCopies + 2 * L::kCopyBytes);
   IN* Rlo = reinterpret_cast<IN*>(smem + L::kCopies + 3 * L::kCopyBytes);
-  auto mat = [&](int m, int buf) {
-    return reinterpret_cast<XT*>(smem + L::kMats + L::slot(m, buf) * kPkBytes);
-  };
+  auto mat = [&](int m) { return reinterpret_cast<XT*>(smem + L::kMats + L::slot(m) * kPkBytes); };
   const XT* zero16 = reinterpret_cast<const XT*>(smem + L::kZero);
-  XT* Yt = reinterpret_cast<XT*>(smem + L::kBufs);               // Y, later YR
-  XT* Ut = reinterpret_cast<XT*>(smem + L::kBufs + 1 * L::kBufBytes);
-  XT* URt = reinterpret_cast<XT*>(smem + L::kBufs + 2 * L::kBufBytes);
-  XT* DUt = reinterpret_cast<XT*>(smem + L::kBufs + 3 * L::kBufBytes);
-  XT* DURt = reinterpret_cast<XT*>(smem + L::kBufs + 4 * L::kBufBytes);
+  XT* Yt = reinterpret_cast<XT*>(smem + L::kBufs);
+  XT* YRt = reinterpret_cast<XT*>(smem + L::kBufs + 1 * L::kBufBytes);
+  XT* DUt = reinterpret_cast<XT*>(smem + L::kBufs + 2 * L::kBufBytes);
+  XT* DURt = reinterpret_cast<XT*>(smem + L::kBufs + 3 * L::kBufBytes);
+  // U, UR for the saved blocks (RLA: Y, YR themselves)
+  XT* Ut = RDN ? reinterpret_cast<XT*>(smem + L::kBufs + 4 * L::kBufBytes) : Yt;
+  XT* URt = RDN ? reinterpret_cast<XT*>(smem + L::kBufs + 5 * L::kBufBytes) : YRt;
   auto vblk = [&](int c) { return reinterpret_cast<IN*>(smem + L::kVc + (c & 1) * L::kVBytes); };
   float* gates = reinterpret_cast<float*>(smem + L::kGates);
   XT* Rst = reinterpret_cast<XT*>(smem + L::kRst);            // r (saving mode)
@@ -766,41 +744,28 @@ __global__ __launch_bounds__(2 * kThreads) void fwd_scan_ws_kernel(OpParams p) {
   floatx4 Sacc[IT][JT], Racc[IT][JT];  // chain: the states
   typename MI::frag Kn[KS_STEPS], Qn[KS_STEPS];   // chain: next chunk's K, Q rows 16 ww + (lane & 15)
   if constexpr (CH) {
-#pragma unroll
-    for (int it = 0; it < IT; ++it)
-#pragma unroll
-      for (int jt = 0; jt < JT; ++jt)
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          const int i = ww * (DK / 4) + it * 16 + acc_row(r), j = j0 + jt * 16 + acc_col();
-          Sacc[it][jt][r] = p.S0 ? p.S0[state_off + (int64_t)i * DV + j] : 0.f;
-          Racc[it][jt][r] = p.R0 ? p.R0[state_off + (int64_t)i * DV + j] : 0.f;
-        }
+    load_acc_state<IT, JT>(Sacc, p.S0, state_off + j0, DV, ww * (DK / 4));
+    load_acc_state<IT, JT>(Racc, p.R0, state_off + j0, DV, ww * (DK / 4));
   }
-  auto write_state_copies = [&]() {
+  auto write_state_copies = [&](const floatx4 (&acc)[IT][JT], IN* hi, IN* lo) {
 #pragma unroll
     for (int it = 0; it < IT; ++it)
 #pragma unroll
-      for (int jt = 0; jt < JT; ++jt) {
-        store_state_copy<TSC>(Shi, Slo, jt * 16, ww * (DK / 4) + it * 16, Sacc[it][jt]);
-        store_state_copy<TSC>(Rhi, Rlo, jt * 16, ww * (DK / 4) + it * 16, Racc[it][jt]);
-      }
+      for (int jt = 0; jt < JT; ++jt) store_state_copy<TSC>(hi, lo, jt * 16, ww * (DK / 4) + it * 16, acc[it][jt]);
   };
   // Global addresses are a chunk's uniform base plus a 32-bit lane offset
   // that does not change from chunk to chunk, so the memory instructions take
   // a scalar base and the lane part is formed once.
   auto issue_rows = [&](typename MI::frag (&dst)[KS_STEPS], const IN* src, int c) {
     const int64_t tok = si.start + (int64_t)c * kChunk;
-    const int t = 16 * ww + (lane & 15);
-    const bool ok = t < chunk_len(c);
+    // padding rows: the last row (their beta, gamma are 0, so every product
+    // with them is multiplied by 0 or not stored)
+    const int t = min(16 * ww + (lane & 15), chunk_len(c) - 1);
     const IN* base = src + (tok * H + h) * (int64_t)DK;
     const uint32_t o = (uint32_t)(t * H * DK + (lane >> 4) * 8);
 #pragma unroll
-    for (int s2 = 0; s2 < KS_STEPS; ++s2) {
-      u16x8 v = {0, 0, 0, 0, 0, 0, 0, 0};
-      if (ok) v = *reinterpret_cast<const u16x8*>(base + o + s2 * 32);
-      dst[s2] = __builtin_bit_cast(typename MI::frag, v);
-    }
+    for (int s2 = 0; s2 < KS_STEPS; ++s2)
+      dst[s2] = __builtin_bit_cast(typename MI::frag, *reinterpret_cast<const u16x8*>(base + o + s2 * 32));
   };
   // side wave 0 moves chunk c's gate block (g, h, beta, gamma) into LDS with
   // one DMA instruction and, after its wait, forms every gate vector
@@ -808,27 +773,15 @@ __global__ __launch_bounds__(2 * kThreads) void fwd_scan_ws_kernel(OpParams p) {
     if (ww == 0) dma_linear_wave(p.gate_ws + ((int64_t)(si.chunk0 + c) * H + h) * kGateBlock, graw, kGateBlock * 4);
   };
   auto write_gates = [&](int c) {
-    if (ww != 0) return;
-    const int t = lane;
-    const float g = graw[t], gp = graw[max(t - 1, 0)], gl = graw[kChunk - 1];
-    const float hr = graw[64 + t], hl = graw[64 + kChunk - 1];
-    gvec(c, 0)[t] = graw[128 + t];
-    gvec(c, 1)[t] = graw[192 + t];
-    gvec(c, 2)[t] = __expf(g);
-    gvec(c, 3)[t] = t > 0 ? __expf(gp) : 1.f;
-    gvec(c, 4)[t] = __expf(hr);
-    gvec(c, 5)[t] = __expf(gl - g);
-    gvec(c, 6)[t] = __expf(hl - hr);
-    gvec(c, 7)[0] = __expf(gl);   // every lane stores the same value
-    gvec(c, 7)[1] = __expf(hl);
+    if (ww == 0) write_gate_vectors(graw, gvec(c, 0));
   };
   // side waves: the five DMA instructions of the g-th matrix of a group are
   // dealt round-robin over the four side waves (the group's instruction k
-  // to wave k mod 4)
-  auto dma_mat = [&](int c, int m, int slot_buf, int g) {
-    dma_mat_packed<false>(mat_src(c, m), mat(m, slot_buf), ((ww - 5 * g) % 4 + 4) % 4, kWaves);
+  // to wave k mod 4): a wave issues at least 2 of a group of two, 3 of three
+  auto dma_mat = [&](int c, int m, int g) {
+    dma_mat_packed<false>(mat_src(c, m), mat(m), ((ww - 5 * g) % 4 + 4) % 4, kWaves);
   };
-  auto issue_early = [&](int c) {   // V, MG, MP, T^R, MR of chunk c (double-buffered)
+  auto issue_v = [&](int c) {   // V of chunk c (double-buffered)
     const int64_t tok = si.start + (int64_t)c * kChunk;
     const int len = chunk_len(c);
     constexpr int kChunksPerRow = BV * (int)sizeof(IN) / 16;
@@ -836,15 +789,23 @@ __global__ __launch_bounds__(2 * kThreads) void fwd_scan_ws_kernel(OpParams p) {
     const int ts = t < len ? t : len - 1;   // padding rows: any valid row (multiplied by 0)
     dma16(vg + (tok * H + h) * (int64_t)DV + j0 + (uint32_t)(ts * H * DV + cc * (16 / (int)sizeof(IN))),
           reinterpret_cast<char*>(vblk(c)) + ww * 1024);
-    int g = 0;
-    dma_mat(c, kMatMG, c & 1, g++);
-    dma_mat(c, kMatMP, c & 1, g++);
-    if constexpr (RDN) dma_mat(c, kMatTR, c & 1, g++);
-    dma_mat(c, kMatMR, c & 1, g++);
   };
-  auto issue_ts = [&](int c) {   // T^S (single-buffered)
-    if constexpr (RDN) dma_mat(c, kMatTS, 0, 0);
+  auto issue_s_mats = [&](int c) {   // T^S, MG, MP (RLA: MG, MP, MR)
+    dma_mat(c, RDN ? (int)kMatTS : (int)kMatMR, 0);
+    dma_mat(c, kMatMG, 1);
+    dma_mat(c, kMatMP, 2);
   };
+  auto issue_r_mats = [&](int c) {   // T^R, MR
+    if constexpr (RDN) {
+      dma_mat(c, kMatTR, 0);
+      dma_mat(c, kMatMR, 1);
+    }
+  };
+  // The side's waits leave its newest memory operations in flight, so the
+  // order in which it issues groups of them is pinned.
+  auto pin = [] { asm volatile("" ::: "memory"); };
+  constexpr int kCk = CKPT ? IT + 1 : 0;   // stores of one checkpoint
+  constexpr int kBl = CKPT ? 1 : 0;        // store of one block
   // side waves: tokens 16 ww .. 16 ww + 15 of a token-major block, one
   // 64-byte segment per token (lane (g, i): token 16 ww + i, values 8 g ..
   // 8 g + 7); rows past the end are zero
@@ -854,6 +815,16 @@ __global__ __launch_bounds__(2 * kThreads) void fwd_scan_ws_kernel(OpParams p) {
     const int t = 16 * ww + (lane & 15);
     const uint4 x = keep_if(tile_token_rows16_sync<TT>(src, 16 * ww), t < chunk_len(c));
     *reinterpret_cast<uint4*>(fblk + blk_off(gc, h, H, b, DV) + j0 + (uint32_t)(t * DV + 8 * (lane >> 4))) = x;
+  };
+  // side waves: chunk c's r rows and clip mask columns (waves 2, 3; one
+  // 16-byte piece per lane)
+  auto store_resid = [&](int c) {
+    store_block(c, 2, Rst);
+    if (ww >= 2) {
+      const int e = (ww - 2) * 64 + lane;
+      *reinterpret_cast<uint4*>(p.ck_mask + mask_off(si.chunk0 + c, h, H, DV) + j0 * kChunk + (uint32_t)(e * 16)) =
+          lds_read16_sync(Mst + (e >> 2) * L::kMstLd + (e & 3) * 16);
+    }
   };
   // side waves: chunk-start state X (st: 0 = S, 1 = R) from its copies
   // (hi + lo), rows 32 ww .. 32 ww + 31, fp16 blocked [DV / 32][DK][32] with
@@ -867,23 +838,43 @@ __global__ __launch_bounds__(2 * kThreads) void fwd_scan_ws_kernel(OpParams p) {
     const IN* lo = st ? Rlo : Slo;
     f16* dst = reinterpret_cast<f16*>(st ? p.ck_R : p.ck_S) + ((int64_t)gc * H + h) * DK * DV + (int64_t)j0 * DK;
     float sc[IT];
+    uint4 xh[IT], xl[IT];
+    {
+      const IN* src[2 * IT];
+      int t0[2 * IT];
+      uint4 x[2 * IT];
+#pragma unroll
+      for (int it = 0; it < IT; ++it) {
+        src[2 * it] = hi;
+        src[2 * it + 1] = lo;
+        t0[2 * it] = t0[2 * it + 1] = ww * (DK / 4) + 16 * it;
+      }
+      tile_token_rows16_sync<TSC>(src, t0, x);
+#pragma unroll
+      for (int it = 0; it < IT; ++it) {
+        xh[it] = x[2 * it];
+        xl[it] = x[2 * it + 1];
+      }
+    }
+    // the tile's scale from its hi parts: |hi + lo| <= (1 + 2^-8) |hi|, so the
+    // stored magnitudes stay below 2^14 (1 + 2^-8)
 #pragma unroll
     for (int it = 0; it < IT; ++it) {
-      const int t0 = ww * (DK / 4) + 16 * it;
-      const uint4 xh = tile_token_rows16_sync<TSC>(hi, t0), xl = tile_token_rows16_sync<TSC>(lo, t0);
-      const uint32_t wh[4] = {xh.x, xh.y, xh.z, xh.w}, wl[4] = {xl.x, xl.y, xl.z, xl.w};
-      floatx4 a, b;
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        const float v0 = __uint_as_float(wh[e] << 16) + __uint_as_float(wl[e] << 16);
-        const float v1 = __uint_as_float(wh[e] & 0xFFFF0000u) + __uint_as_float(wl[e] & 0xFFFF0000u);
-        if (e < 2) { a[2 * e] = v0; a[2 * e + 1] = v1; } else { b[2 * e - 4] = v0; b[2 * e - 3] = v1; }
-      }
-      const int ex = pow2_scale_exp(wave_absmax_bits(lane_absmax_bits(a, b)));
-      const float f = exp2_int(-ex);
-      const uint4 v = {cvt_pk_f16(a[0] * f, a[1] * f), cvt_pk_f16(a[2] * f, a[3] * f),
-                       cvt_pk_f16(b[0] * f, b[1] * f), cvt_pk_f16(b[2] * f, b[3] * f)};
-      *reinterpret_cast<uint4*>(dst + (uint32_t)((t0 + (lane & 15)) * 32 + 8 * (lane >> 4))) = v;
+      const uint32_t m = pk_max_u16(pk_max_u16(xh[it].x & 0x7FFF7FFFu, xh[it].y & 0x7FFF7FFFu),
+                                    pk_max_u16(xh[it].z & 0x7FFF7FFFu, xh[it].w & 0x7FFF7FFFu));
+      const int ex = pow2_scale_exp(wave_absmax_bits(max(m << 16, m & 0xFFFF0000u)));
+      const uint32_t f = __float_as_uint(exp2_int(-ex));   // a power of two: its bf16 bits are the upper half
+      const bf16x2 f0 = __builtin_bit_cast(bf16x2, f >> 16), f1 = __builtin_bit_cast(bf16x2, f);
+      // (hi + lo) f of an element: two bf16 dot products (exact but for the fp32 sum)
+      auto scaled = [&](uint32_t h2, uint32_t l2) {
+        const bf16x2 h = __builtin_bit_cast(bf16x2, h2), l = __builtin_bit_cast(bf16x2, l2);
+        const float v0 = __builtin_amdgcn_fdot2_f32_bf16(h, f0, __builtin_amdgcn_fdot2_f32_bf16(l, f0, 0.f, false), false);
+        const float v1 = __builtin_amdgcn_fdot2_f32_bf16(h, f1, __builtin_amdgcn_fdot2_f32_bf16(l, f1, 0.f, false), false);
+        return cvt_pk_f16(v0, v1);
+      };
+      const uint4 v = {scaled(xh[it].x, xl[it].x), scaled(xh[it].y, xl[it].y), scaled(xh[it].z, xl[it].z),
+                       scaled(xh[it].w, xl[it].w)};
+      *reinterpret_cast<uint4*>(dst + (uint32_t)((ww * (DK / 4) + 16 * it + (lane & 15)) * 32 + 8 * (lane >> 4))) = v;
       sc[it] = exp2_int(ex);
     }
     static_assert(IT <= 2, "one or two tiles per wave");
@@ -892,41 +883,36 @@ __global__ __launch_bounds__(2 * kThreads) void fwd_scan_ws_kernel(OpParams p) {
       (st ? p.ck_R_sc : p.ck_S_sc)[so + (int64_t)(ww * IT + lane) * (DV / 32)] = lane ? sc[IT - 1] : sc[0];
   };
 
-  // KS, KR, QS, QR for this wave's 16 token rows (K, Q as A fragments)
-  // from the state copies: each B fragment read once serves the K and the Q
-  // product; eight independent MFMA chains (value tile x state x K/Q), each
-  // adding the hi and the lo product of every k-step (Q16: also the residual
-  // of the rows times hi)
   constexpr int KL_STEPS = Q16 ? KS_STEPS : 1;
-  auto split_products = [&](const typename MI::frag (&kf)[KS_STEPS], const typename MI::frag (&qf)[KS_STEPS],
-                            const typename MI::frag (&kl)[KL_STEPS], const typename MI::frag (&ql)[KL_STEPS],
-                            floatx4 (&ks)[JT], floatx4 (&kr)[JT], floatx4 (&qs)[JT], floatx4 (&qr)[JT]) {
+  typedef Mfma<XT> MX;
+  constexpr int XS = kChunk / MX::kStep;   // k-steps over the chunk's tokens
+  // the fragments of a token tile's JT column blocks
+  auto tok_frags = [&](const XT* tile, typename MX::frag (&f)[JT][XS]) {
 #pragma unroll
-    for (int jt = 0; jt < JT; ++jt) ks[jt] = kr[jt] = qs[jt] = qr[jt] = zero4();
+    for (int ks = 0; ks < XS; ++ks)
 #pragma unroll
-    for (int s2 = 0; s2 < KS_STEPS; ++s2)
+      for (int jt = 0; jt < JT; ++jt) f[jt][ks] = TT::template frag<MX>(tile, jt * 16, ks * MX::kStep);
+  };
+  // acc[jt] += a * tile, the column blocks' chains interleaved
+  auto mma_tok = [&](floatx4 (&acc)[JT], const MatFrags<XT>& a, const typename MX::frag (&f)[JT][XS]) {
 #pragma unroll
-      for (int jt = 0; jt < JT; ++jt) {
-        const int k0 = s2 * MI::kStep;
-        const typename MI::frag sh = TSC::template frag<MI>(Shi, jt * 16, k0);
-        const typename MI::frag rh = TSC::template frag<MI>(Rhi, jt * 16, k0);
-        const typename MI::frag sl = TSC::template frag<MI>(Slo, jt * 16, k0);
-        const typename MI::frag rl = TSC::template frag<MI>(Rlo, jt * 16, k0);
-        ks[jt] = MI::mma(kf[s2], sh, ks[jt]);
-        qs[jt] = MI::mma(qf[s2], sh, qs[jt]);
-        kr[jt] = MI::mma(kf[s2], rh, kr[jt]);
-        qr[jt] = MI::mma(qf[s2], rh, qr[jt]);
-        ks[jt] = MI::mma(kf[s2], sl, ks[jt]);
-        qs[jt] = MI::mma(qf[s2], sl, qs[jt]);
-        kr[jt] = MI::mma(kf[s2], rl, kr[jt]);
-        qr[jt] = MI::mma(qf[s2], rl, qr[jt]);
-        if constexpr (Q16) {
-          ks[jt] = MI::mma(kl[s2], sh, ks[jt]);
-          qs[jt] = MI::mma(ql[s2], sh, qs[jt]);
-          kr[jt] = MI::mma(kl[s2], rh, kr[jt]);
-          qr[jt] = MI::mma(ql[s2], rh, qr[jt]);
-        }
-      }
+    for (int ks = 0; ks < XS; ++ks)
+#pragma unroll
+      for (int jt = 0; jt < JT; ++jt) acc[jt] = MX::mma(a.f[ks], f[jt][ks], acc[jt]);
+  };
+  // X <- e X + K^T dX (the chunk's decayed corrections)
+  auto update_state = [&](floatx4 (&acc)[IT][JT], float e, const typename MX::frag (&kt)[IT * XS],
+                          const typename MX::frag (&f)[JT][XS]) {
+#pragma unroll
+    for (int it = 0; it < IT; ++it)
+#pragma unroll
+      for (int jt = 0; jt < JT; ++jt) acc[it][jt] *= e;
+#pragma unroll
+    for (int ks = 0; ks < XS; ++ks)
+#pragma unroll
+      for (int it = 0; it < IT; ++it)
+#pragma unroll
+        for (int jt = 0; jt < JT; ++jt) acc[it][jt] = MX::mma(kt[it * XS + ks], f[jt][ks], acc[it][jt]);
   };
 
   // o from the column-major stage: four 4-byte reads give a lane 4 columns of
@@ -963,253 +949,286 @@ __global__ __launch_bounds__(2 * kThreads) void fwd_scan_ws_kernel(OpParams p) {
       issue_rows(Qn, qg, 0);
     } else {
       issue_gates(0);
-      issue_early(0);
-      issue_ts(0);
+      issue_v(0);
+      issue_s_mats(0);
+      issue_r_mats(0);
       wait_vmem();
       write_gates(0);
     }
   }
-  if constexpr (CH) write_state_copies();
+  if constexpr (CH) {
+    write_state_copies(Sacc, Shi, Slo);
+    write_state_copies(Racc, Rhi, Rlo);
+  }
   barrier_lds();
 
-  floatx4 KS[JT], KR[JT], QS[JT], QR[JT], base[JT];
-  float vloc[JT][4];
+  floatx4 KS[JT], KR[JT], QS[JT], QR[JT], vloc[JT], base[JT];
   MatFrags<XT> aTS, aMG, aMP, aTR, aMR;
+  typename MX::frag kt[IT * XS];   // this wave's state rows of K^T
   for (int c = 0; c < nch; ++c) {
     const int len = chunk_len(c);
-    const int buf = c & 1;
     const bool more = c + 1 < nch;
-    const float* gbt = gvec(c, 0);
-    const float* ggm = gvec(c, 1);
-    const float* egs = gvec(c, 2);
-    const float* egsp = gvec(c, 3);
-    const float* egr = gvec(c, 4);
-    const float* dls = gvec(c, 5);
-    const float* dlr = gvec(c, 6);
-    const float* edge = gvec(c, 7);
-    const int64_t tok = si.start + (int64_t)c * kChunk;
+    // this lane's four tokens of gate vector k
+    auto gate4 = [&](int k) { return *reinterpret_cast<const floatx4*>(gvec(c, k) + 16 * ww + acc_row(0)); };
+    floatx4 gbt, ggm, egs, egsp, egr, dls, dlr;
+    float eS, eR;
 
-    // ======== phase 1 ========
+    // ======== phase 1: KS, KR, QS, QR; Y = diag(b) (V - e^g KS) (RLA: diag(b) V) ========
     if constexpr (CH) {
-      typename MI::frag Kf[KS_STEPS], Qf[KS_STEPS], Kl[KL_STEPS], Ql[KL_STEPS];
-      const int t = 16 * ww + (lane & 15);
+      // fragments of the state copies, one k-step ahead of their products
+      typename MI::frag f[2][4][JT];
+      auto load_states = [&](int s2) {
+        const IN* src[4] = {Shi, Rhi, Slo, Rlo};
 #pragma unroll
-      for (int s2 = 0; s2 < KS_STEPS; ++s2) {   // K^T commit: row t, 8 columns per store
+        for (int x = 0; x < 4; ++x)
+#pragma unroll
+          for (int jt = 0; jt < JT; ++jt) f[s2 & 1][x][jt] = TSC::template frag<MI>(src[x], jt * 16, s2 * MI::kStep);
+      };
+      load_states(0);
+      sched_fence();
+#pragma unroll
+      for (int jt = 0; jt < JT; ++jt) KS[jt] = KR[jt] = QS[jt] = QR[jt] = zero4();
+#pragma unroll
+      for (int s2 = 0; s2 < KS_STEPS; ++s2) {
+        if (s2 + 1 < KS_STEPS) load_states(s2 + 1);
+        else {   // what the end of the phase and the next one need
+          gbt = gate4(0);
+          egs = gate4(2);
+#pragma unroll
+          for (int jt = 0; jt < JT; ++jt) {
+            const u16x4 v4 = acc_tile_tr<PadRows<IN, BV, 0>>(vblk(c), 16 * ww, jt * 16);
+#pragma unroll
+            for (int r = 0; r < 4; ++r) vloc[jt][r] = bf2f(v4[r]);
+          }
+          if constexpr (!RDN) dls = gate4(5);
+        }
+        sched_fence();
+        // K^T commit: row 16 ww + (lane & 15), 8 columns per store
+        typename MI::frag kf = Kn[s2], qf = Qn[s2], kl, ql;
         f16x8 kh;
         if constexpr (Q16) {
           kh = __builtin_bit_cast(f16x8, Kn[s2]);
-          f16_split8(kh, Kf[s2], Kl[s2]);
-          f16_split8(__builtin_bit_cast(f16x8, Qn[s2]), Qf[s2], Ql[s2]);
+          f16_split8(kh, kf, kl);
+          f16_split8(__builtin_bit_cast(f16x8, Qn[s2]), qf, ql);
         } else {
-          Kf[s2] = Kn[s2];
-          Qf[s2] = Qn[s2];
-          const u16x8 kv = __builtin_bit_cast(u16x8, Kf[s2]);
+          const u16x8 kv = __builtin_bit_cast(u16x8, kf);
 #pragma unroll
           for (int e = 0; e < 8; ++e) kh[e] = (f16)bf2f(kv[e]);
         }
-        *reinterpret_cast<f16x8*>(TK::ptr(KT, t, s2 * 32 + (lane >> 4) * 8)) = kh;
+        auto& fs = f[s2 & 1];
+        // eight independent chains (value tile x state x K/Q), each adding
+        // the hi and the lo product of every k-step (Q16: also the rows'
+        // residual times hi)
+#pragma unroll
+        for (int x = 0; x < 4; ++x)
+#pragma unroll
+          for (int jt = 0; jt < JT; ++jt) {
+            floatx4& k = (x & 1) ? KR[jt] : KS[jt];
+            floatx4& q = (x & 1) ? QR[jt] : QS[jt];
+            k = MI::mma(kf, fs[x][jt], k);
+            if constexpr (WRITE_O) q = MI::mma(qf, fs[x][jt], q);
+          }
+        if constexpr (Q16) {
+#pragma unroll
+          for (int x = 0; x < 2; ++x)
+#pragma unroll
+            for (int jt = 0; jt < JT; ++jt) {
+              floatx4& k = (x & 1) ? KR[jt] : KS[jt];
+              floatx4& q = (x & 1) ? QR[jt] : QS[jt];
+              k = MI::mma(kl, fs[x][jt], k);
+              if constexpr (WRITE_O) q = MI::mma(ql, fs[x][jt], q);
+            }
+        }
+        *reinterpret_cast<f16x8*>(TK::ptr(KT, 16 * ww + (lane & 15), s2 * 32 + (lane >> 4) * 8)) = kh;
       }
-      split_products(Kf, Qf, Kl, Ql, KS, KR, QS, QR);
 #pragma unroll
       for (int jt = 0; jt < JT; ++jt) {
-        const u16x4 v4 = acc_tile_tr<PadRows<IN, BV, 0>>(vblk(c), 16 * ww, jt * 16);
         floatx4 y;
 #pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          const int tr = 16 * ww + acc_row(r);
-          vloc[jt][r] = bf2f(v4[r]);
-          y[r] = RDN ? gbt[tr] * __builtin_fmaf(-egs[tr], KS[jt][r], vloc[jt][r]) : gbt[tr] * vloc[jt][r];
-        }
-        if constexpr (RDN) {
-          store_acc_tile<TT>(Yt, jt * 16, 16 * ww, y);
-        } else {
-          floatx4 du;
-#pragma unroll
-          for (int r = 0; r < 4; ++r) du[r] = dls[16 * ww + acc_row(r)] * y[r];
-          store_acc_tile<TT>(Ut, jt * 16, 16 * ww, y);
-          store_acc_tile<TT>(DUt, jt * 16, 16 * ww, du);
-        }
+        for (int r = 0; r < 4; ++r)
+          y[r] = RDN ? gbt[r] * __builtin_fmaf(-egs[r], KS[jt][r], vloc[jt][r]) : gbt[r] * vloc[jt][r];
+        store_acc_tile<TT>(Yt, jt * 16, 16 * ww, y);
+        if constexpr (!RDN) store_acc_tile<TT>(DUt, jt * 16, 16 * ww, dls * y);
       }
-      if constexpr (RDN) aTS = packed_rows_frags(mat(kMatTS, 0), ww, zero16);
-      else aMG = packed_rows_frags(mat(kMatMG, buf), ww, zero16);
+      sched_fence();
+      ggm = gate4(1);
+      egsp = gate4(3);
+      egr = gate4(4);
+      if constexpr (RDN) dls = gate4(5);
+      dlr = gate4(6);
+      eS = gvec(c, 7)[0];
+      eR = gvec(c, 7)[1];
     } else {
+      if (more) {
+        issue_gates(c + 1);
+        issue_v(c + 1);
+      }
+      pin();
       if constexpr (WRITE_O) {
         if (c > 0) store_o(c - 1);
       }
-      if (more) {
-        issue_early(c + 1);
-        issue_gates(c + 1);
+      if constexpr (CKPT) {
+        if (c > 0) store_resid(c - 1);
+        if constexpr (RDN) store_ckpt(c, 0);   // chunk-start S
       }
-      if constexpr (CKPT) store_ckpt(c, 0);   // chunk-start S
+      // this chunk's T^S, MG, MP (from phase 3); since then: RDN T^R, MR, the
+      // R checkpoint, U and what is above; RLA U, U^R and what is above (the
+      // previous chunk's o and r; chunk 0 waited for everything)
+      wait_vmem_but<RDN ? 2 + 2 * kCk + kBl : CKPT ? 3 : 1>();
     }
     barrier_lds();
 
-    // ======== phase 2 ========
+    // ======== phase 2: U; residual, clip, Y^R (explicit fmas as fwd_scan_kernel); base read-out ========
     if constexpr (CH) {
-      if constexpr (RDN) {   // U = T^S Y
-#pragma unroll
-        for (int jt = 0; jt < JT; ++jt) {
-          floatx4 u = zero4();
-          mma_frags<XT>(u, aTS, Yt, jt * 16);
-          floatx4 du;
-#pragma unroll
-          for (int r = 0; r < 4; ++r) du[r] = dls[16 * ww + acc_row(r)] * u[r];
-          store_acc_tile<TT>(Ut, jt * 16, 16 * ww, u);
-          store_acc_tile<TT>(DUt, jt * 16, 16 * ww, du);
-        }
-        aMG = packed_rows_frags(mat(kMatMG, buf), ww, zero16);
-      }
-      if constexpr (WRITE_O) aMP = packed_rows_frags(mat(kMatMP, buf), ww, zero16);
+      typename MX::frag fy[JT][XS];
+      tok_frags(Yt, fy);
+      aMG = packed_rows_frags(mat(kMatMG), ww, zero16);
+      if constexpr (RDN) aTS = packed_rows_frags(mat(kMatTS), ww, zero16);
+      if constexpr (WRITE_O) aMP = packed_rows_frags(mat(kMatMP), ww, zero16);
+      if constexpr (WRITE_O && !RDN) aMR = packed_rows_frags(mat(kMatMR), ww, zero16);
+      sched_fence();
       if (more) {   // the next K, Q rows, while the side waves issue little
         issue_rows(Kn, kg, c + 1);
         issue_rows(Qn, qg, c + 1);
       }
-    } else {
-      if (more) issue_ts(c + 1);   // T^S was read into registers before the first barrier
-    }
-    barrier_lds();
-
-    // ======== phase 3 ========
-    if constexpr (CH) {   // residual, clip, Y^R (explicit fmas as fwd_scan_kernel)
+      floatx4 pre[JT], mgu[JT], u[JT];
 #pragma unroll
       for (int jt = 0; jt < JT; ++jt) {
-        floatx4 mgu = zero4();
-        mma_frags<XT>(mgu, aMG, Ut, jt * 16);
+#pragma unroll
+        for (int r = 0; r < 4; ++r) pre[jt][r] = __builtin_fmaf(-egsp[r], KS[jt][r], vloc[jt][r]);
+        mgu[jt] = u[jt] = base[jt] = zero4();
+      }
+      sched_fence();
+      mma_tok(mgu, aMG, fy);
+      if constexpr (RDN) mma_tok(u, aTS, fy);
+      if constexpr (WRITE_O) mma_tok(base, aMP, fy);
+#pragma unroll
+      for (int jt = 0; jt < JT; ++jt) {
+        const floatx4 x = pre[jt] - mgu[jt];
         floatx4 y, rv;
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
-          const int t = 16 * ww + acc_row(r);
-          const float x = __builtin_fmaf(-egsp[t], KS[jt][r], vloc[jt][r]) - mgu[r];
-          const float rr = clip < 0.f ? x : fminf(fmaxf(x, -clip), clip);
+          const float rr = clip < 0.f ? x[r] : fminf(fmaxf(x[r], -clip), clip);
           rv[r] = rr;
-          if constexpr (CKPT) Mst[t * BV + jt * 16 + acc_col()] = (clip < 0.f || fabsf(x) <= clip) ? 1 : 0;
-          y[r] = RDN ? ggm[t] * __builtin_fmaf(-egr[t], KR[jt][r], rr) : ggm[t] * rr;
+          y[r] = RDN ? ggm[r] * __builtin_fmaf(-egr[r], KR[jt][r], rr) : ggm[r] * rr;
         }
-        if constexpr (RDN) {
-          store_acc_tile<TT>(Yt, jt * 16, 16 * ww, y);
-        } else {
-          floatx4 du;
-#pragma unroll
-          for (int r = 0; r < 4; ++r) du[r] = dlr[16 * ww + acc_row(r)] * y[r];
-          store_acc_tile<TT>(URt, jt * 16, 16 * ww, y);
-          store_acc_tile<TT>(DURt, jt * 16, 16 * ww, du);
+        store_acc_tile<TT>(YRt, jt * 16, 16 * ww, y);
+        if constexpr (!RDN) store_acc_tile<TT>(DURt, jt * 16, 16 * ww, dlr * y);
+        if constexpr (CKPT) {
+          store_acc_tile<TT>(Rst, jt * 16, 16 * ww, rv);
+          *reinterpret_cast<uint32_t*>(Mst + (jt * 16 + acc_col()) * L::kMstLd + 16 * ww + acc_row(0)) = mask_word(x, clip);
         }
-        if constexpr (CKPT) store_acc_tile<TT>(Rst, jt * 16, 16 * ww, rv);
       }
-      if constexpr (WRITE_O) {   // base = e^g QS + MP U
+      if constexpr (RDN) {
 #pragma unroll
         for (int jt = 0; jt < JT; ++jt) {
-          floatx4 mpu = zero4();
-          mma_frags<XT>(mpu, aMP, Ut, jt * 16);
-#pragma unroll
-          for (int r = 0; r < 4; ++r) base[jt][r] = __builtin_fmaf(egs[16 * ww + acc_row(r)], QS[jt][r], mpu[r]);
+          store_acc_tile<TT>(DUt, jt * 16, 16 * ww, dls * u[jt]);
+          if constexpr (CKPT) store_acc_tile<TT>(Ut, jt * 16, 16 * ww, u[jt]);
         }
       }
-      if constexpr (RDN) aTR = packed_rows_frags(mat(kMatTR, buf), ww, zero16);
-    } else {
-      if constexpr (CKPT) store_ckpt(c, 1);   // chunk-start R
-      if constexpr (CKPT) store_block(c, 0, Ut);
-    }
-    barrier_lds();
-
-    // ======== phase 4 ========
-    if constexpr (CH) {
-      if constexpr (RDN) {   // U^R = T^R Y^R
+      if constexpr (WRITE_O) {
 #pragma unroll
-        for (int jt = 0; jt < JT; ++jt) {
-          floatx4 u = zero4();
-          mma_frags<XT>(u, aTR, Yt, jt * 16);
-          floatx4 du;
+        for (int jt = 0; jt < JT; ++jt)
 #pragma unroll
-          for (int r = 0; r < 4; ++r) du[r] = dlr[16 * ww + acc_row(r)] * u[r];
-          store_acc_tile<TT>(URt, jt * 16, 16 * ww, u);
-          store_acc_tile<TT>(DURt, jt * 16, 16 * ww, du);
-        }
+          for (int r = 0; r < 4; ++r) base[jt][r] = __builtin_fmaf(egs[r], QS[jt][r], base[jt][r]);
       }
-      if constexpr (WRITE_O) aMR = packed_rows_frags(mat(kMatMR, buf), ww, zero16);
+      int fr0[IT * XS], fk0[IT * XS];
+#pragma unroll
+      for (int x = 0; x < IT * XS; ++x) {
+        fr0[x] = ww * (DK / 4) + (x / XS) * 16;
+        fk0[x] = (x % XS) * MX::kStep;
+      }
+      frags_tr_sync<TK, XT, IT * XS>(KT, fr0, fk0, kt);
     } else {
       if constexpr (CKPT) {
-        store_block(c, 2, Rst);
-        {   // clip mask rows (side waves 0 and 1, one 16-byte piece per lane);
-            // past the end, a lane rewrites the last row's own bytes, so the
-            // store needs no lane condition
-          constexpr int kVPR = BV / 16;
-          const int e = (ww & 1) * 64 + lane, t = min(e / kVPR, len - 1), v = e % kVPR;
-          if (ww < 2)
-            *reinterpret_cast<uint4*>(p.ck_mask + (tok * H + h) * (int64_t)DV + j0 + (uint32_t)(t * H * DV + v * 16)) =
-                lds_read16_sync(Mst + t * BV + v * 16);
+        if constexpr (RDN) {
+          if (c > 0) store_block(c - 1, 1, URt);
+        } else {
+          store_ckpt(c, 0);
+          store_ckpt(c, 1);
         }
       }
+      // this chunk's T^R, MR (from phase 4); since then the S checkpoint or,
+      // not saving, the previous chunk's o
+      if constexpr (RDN) wait_vmem_but<CKPT ? kCk + kBl : 1>();
     }
     barrier_lds();
 
-    // ======== phase 5 ========
-    if constexpr (CH) {   // S <- e^{g_C} S + K^T DU, R <- e^{h_C} R + K^T DUR
-      const float eS = edge[0], eR = edge[1];
-      typedef Mfma<XT> MX;
-      constexpr int NF = IT * (kChunk / MX::kStep);
-      int fr0[NF], fk0[NF];
+    // ======== phase 3: U^R = T^R Y^R; o = base + diag(gamma) (e^h QR + MR T^R Y^R); S update ========
+    if constexpr (CH) {
+      typename MX::frag fy[JT][XS], fd[JT][XS];
+      tok_frags(YRt, fy);
+      if constexpr (RDN) aTR = packed_rows_frags(mat(kMatTR), ww, zero16);
+      if constexpr (WRITE_O && RDN) aMR = packed_rows_frags(mat(kMatMR), ww, zero16);
+      tok_frags(DUt, fd);
+      sched_fence();
+      floatx4 u[JT], mru[JT];
 #pragma unroll
-      for (int f = 0; f < NF; ++f) {
-        fr0[f] = ww * (DK / 4) + (f / (kChunk / MX::kStep)) * 16;
-        fk0[f] = (f % (kChunk / MX::kStep)) * MX::kStep;
-      }
-      typename MX::frag kt[NF];
-      frags_tr_sync<TK, XT, NF>(KT, fr0, fk0, kt);
-#pragma unroll
-      for (int it = 0; it < IT; ++it)
+      for (int jt = 0; jt < JT; ++jt) u[jt] = mru[jt] = zero4();
+      if constexpr (RDN) mma_tok(u, aTR, fy);
+      if constexpr (WRITE_O) mma_tok(mru, aMR, fy);
+      update_state(Sacc, eS, kt, fd);
+      if constexpr (RDN) {
 #pragma unroll
         for (int jt = 0; jt < JT; ++jt) {
-          Sacc[it][jt] *= eS;
-          Racc[it][jt] *= eR;
-#pragma unroll
-          for (int ks = 0; ks < kChunk / MX::kStep; ++ks) {
-            const int f = it * (kChunk / MX::kStep) + ks;
-            Sacc[it][jt] = MX::mma(kt[f], TT::template frag<MX>(DUt, jt * 16, ks * MX::kStep), Sacc[it][jt]);
-            Racc[it][jt] = MX::mma(kt[f], TT::template frag<MX>(DURt, jt * 16, ks * MX::kStep), Racc[it][jt]);
-          }
+          store_acc_tile<TT>(DURt, jt * 16, 16 * ww, dlr * u[jt]);
+          if constexpr (CKPT) store_acc_tile<TT>(URt, jt * 16, 16 * ww, u[jt]);
         }
-      if constexpr (WRITE_O) {   // o = base + diag(gamma) (e^h QR + MR UR), this wave's rows
+      }
+      if constexpr (WRITE_O) {
 #pragma unroll
         for (int jt = 0; jt < JT; ++jt) {
-          floatx4 mru = zero4(), ov;
-          mma_frags<XT>(mru, aMR, URt, jt * 16);
+          floatx4 ov;
 #pragma unroll
-          for (int r = 0; r < 4; ++r) {
-            const int t = 16 * ww + acc_row(r);
-            ov[r] = __builtin_fmaf(ggm[t], __builtin_fmaf(egr[t], QR[jt][r], mru[r]), base[jt][r]);
-          }
+          for (int r = 0; r < 4; ++r)
+            ov[r] = __builtin_fmaf(ggm[r], __builtin_fmaf(egr[r], QR[jt][r], mru[jt][r]), base[jt][r]);
           // this lane's 4 tokens of its column, one store
           *reinterpret_cast<floatx4*>(ost + (jt * 16 + acc_col()) * L::kOstLd + 16 * ww + acc_row(0)) = ov;
         }
       }
-      write_state_copies();
+      write_state_copies(Sacc, Shi, Slo);
     } else {
-      // the next chunk's DMA (and this wave's earlier stores) complete; the
-      // barrier below publishes the DMA data
-      wait_vmem();
-      if (more) write_gates(c + 1);
-      if constexpr (CKPT) store_block(c, 1, URt);
+      if (more) issue_s_mats(c + 1);   // in the chain's registers since phase 2
+      pin();
+      if constexpr (CKPT) {
+        if constexpr (RDN) store_ckpt(c, 1);   // chunk-start R (rewritten in phase 4)
+        store_block(c, 0, Ut);
+        if constexpr (!RDN) store_block(c, 1, URt);
+      }
+    }
+    if constexpr (RDN) barrier_lds();
+
+    // ======== phase 4: R update ========
+    if constexpr (CH) {
+      typename MX::frag fd[JT][XS];
+      tok_frags(DURt, fd);
+      update_state(Racc, eR, kt, fd);
+      write_state_copies(Racc, Rhi, Rlo);
+    } else {
+      if (more) {
+        pin();
+        issue_r_mats(c + 1);   // in the chain's registers since phase 3
+        // the next V and gates (from phase 1); since then at least a
+        // checkpoint or two, the matrices, U
+        wait_vmem_but<RDN ? 2 * kCk + kBl + 5 : 2 * kCk + 2 * kBl + 3>();
+        write_gates(c + 1);
+      }
     }
     barrier_lds();
   }
 
-  if constexpr (!CH && WRITE_O) {
-    if (nch > 0) store_o(nch - 1);
+  if constexpr (!CH) {
+    if (nch > 0) {
+      if constexpr (WRITE_O) store_o(nch - 1);
+      if constexpr (CKPT) {
+        store_resid(nch - 1);
+        if constexpr (RDN) store_block(nch - 1, 1, URt);
+      }
+    }
   }
   if constexpr (CH) {
-    if (p.S_fin || p.R_fin) {
-#pragma unroll
-      for (int it = 0; it < IT; ++it)
-#pragma unroll
-        for (int jt = 0; jt < JT; ++jt)
-#pragma unroll
-          for (int r = 0; r < 4; ++r) {
-            const int i = ww * (DK / 4) + it * 16 + acc_row(r), j = j0 + jt * 16 + acc_col();
-            if (p.S_fin) p.S_fin[state_off + (int64_t)i * DV + j] = Sacc[it][jt][r];
-            if (p.R_fin) p.R_fin[state_off + (int64_t)i * DV + j] = Racc[it][jt][r];
-          }
-    }
+    if (p.S_fin) save_state_f32<IT, JT>(Sacc, p.S_fin + state_off + j0, DV, ww * (DK / 4));
+    if (p.R_fin) save_state_f32<IT, JT>(Racc, p.R_fin + state_off + j0, DV, ww * (DK / 4));
   }
   };
   if (chain) run(std::true_type{});

@@ -68,7 +68,7 @@ struct OpParams {
   float* ck_R_sc = nullptr;
   float* dS_sc = nullptr;
   float* dR_sc = nullptr;
-  uint8_t* ck_mask = nullptr;   // [ntok][H][DV] 1 where |x| <= clip
+  uint8_t* ck_mask = nullptr;   // [max_chunks][H][DV][64] 1 where |x| <= clip (mask_off)
   // per-token blocks saved for the gradient kernel, [max_chunks][H][3][64][DV]
   // (mm type, token-major, rows past the end of a sequence are zero):
   void* fwd_blk = nullptr;      // U, UR, r (clipped residual) from the forward scan

@@ -17,6 +17,13 @@
 //   A^S[t][s] = b_t e^{g_t-g_s} G[t][s] (s < t); likewise A^R with (gamma, h).
 //   T^S = (I + A^S)^{-1} and T^R = (I + A^R)^{-1} are formed here in fp32 by
 //   blocked forward substitution (16 x 16 diagonal blocks, then block rows).
+//   What the scans apply to U = T^S Y and UR = T^R YR is formed here as well,
+//     MG T^S, MP T^S and MR T^R   (lower block-triangular like their factors),
+//   and stored in place of MG, MP, MR (kMatMG, kMatMP, kMatMR): with Y (the
+//   chunk's residual of V) at hand a scan then has U, the residual's and the
+//   read-out's products all at once instead of one after the other (two
+//   dependent phases of a chunk less in the reverse, one in the forward).  RLA
+//   has T = I and U = Y: MG, MP, MR themselves.
 // All exponents are of differences g_t - g_s <= 0 (never e^{g} e^{-g}).
 #include <type_traits>
 
@@ -210,133 +217,113 @@ __global__ __launch_bounds__(kThreads) void prep_kernel(OpParams p) {
     gate_out[192 + tid] = gm[tid];
   }
 
-  // ---- G = K K^T and P = Q K^T: wave w owns rows 16w..16w+15 (fp16 MFMA
-  //      when q, k are the pre-processing's fp16 rows) ----
-  const int w = tid >> 6;
+  // ---- G = K K^T and P = Q K^T, the blocks on and below the diagonal: wave w
+  //      owns token rows t = 16w .. 16w+15 and computes them transposed (key
+  //      rows as the A operand), so that lane (g, i) holds row t = 16w + i at
+  //      the columns s = 16 ct + 4g + 0..3: four consecutive elements to store,
+  //      per-lane decays of t, and an operand layout for the products below
+  //      (fp16 MFMA when q, k are the pre-processing's fp16 rows) ----
+  const int w = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, g4 = 4 * (lane >> 4);
+  const int t = 16 * w + (lane & 15);
   floatx4 G[4], P[4];
 #pragma unroll
   for (int ct = 0; ct < 4; ++ct) {
     G[ct] = zero4();
     P[ct] = zero4();
-    if (sizeof(T) == 2 && p.qk_f16) {
-      const f16* Kh = reinterpret_cast<const f16*>(Kc);
-      const f16* Qh = reinterpret_cast<const f16*>(Qc);
-      mma_tile<f16, DK, true, true>(G[ct], Kh + 16 * w * L::kLdK, L::kLdK, Kh + 16 * ct * L::kLdK, L::kLdK);
-      mma_tile<f16, DK, true, true>(P[ct], Qh + 16 * w * L::kLdK, L::kLdK, Kh + 16 * ct * L::kLdK, L::kLdK);
-    } else {
-      mma_tile<T, DK, true, true>(G[ct], Kc + 16 * w * L::kLdK, L::kLdK, Kc + 16 * ct * L::kLdK, L::kLdK);
-      mma_tile<T, DK, true, true>(P[ct], Qc + 16 * w * L::kLdK, L::kLdK, Kc + 16 * ct * L::kLdK, L::kLdK);
+  }
+  auto gram = [&](auto tag) {
+    typedef decltype(tag) E;
+    typedef Mfma<E> M;
+    const E* Ke = reinterpret_cast<const E*>(Kc);
+    const E* Qe = reinterpret_cast<const E*>(Qc);
+#pragma unroll
+    for (int k0 = 0; k0 < DK; k0 += M::kStep) {
+      const typename M::frag fk = M::template load<true>(Ke + 16 * w * L::kLdK, L::kLdK, k0);
+      const typename M::frag fq = M::template load<true>(Qe + 16 * w * L::kLdK, L::kLdK, k0);
+#pragma unroll
+      for (int ct = 0; ct < 4; ++ct) {
+        if (ct > w) continue;
+        const typename M::frag fs = M::template load<true>(Ke + 16 * ct * L::kLdK, L::kLdK, k0);
+        G[ct] = M::mma(fs, fk, G[ct]);
+        P[ct] = M::mma(fs, fq, P[ct]);
+      }
     }
+  };
+  if constexpr (sizeof(T) == 2) {
+    if (p.qk_f16) gram(f16{});
+    else gram(T{});
+  } else {
+    gram(T{});
   }
   __syncthreads();   // Kc/Qc dead: region 0 becomes As/Ar
 
   XT* mats = reinterpret_cast<XT*>(p.mat_ws) + ((int64_t)c * H + h) * kNumMats * kMatElems;
   if (tid < kNumMats)   // each matrix's zero pad (the scans' DMA source above the diagonal)
     *reinterpret_cast<uint4*>(mats + tid * kMatElems + kMatPacked) = make_uint4(0, 0, 0, 0);
-  floatx4 mg[4], mp[4], mr[4];   // this wave's 16-row strips of MG, MP, MR
-  // the gate values of this lane's rows and columns, read once up front (a
-  // read needed only under a condition would become a branch with its own
-  // wait); masked entries are multiplied by 0
-  float gs_t[4], gsp_t[4], gr_t[4], bt_t[4], gm_t[4], gs_s[4], gr_s[4];
-#pragma unroll
-  for (int r = 0; r < 4; ++r) {
-    const int t = 16 * w + acc_row(r);
-    gs_t[r] = gs[t];
-    gsp_t[r] = gsp[t];
-    gr_t[r] = gr[t];
-    bt_t[r] = bt[t];
-    gm_t[r] = gm[t];
-  }
-#pragma unroll
-  for (int ct = 0; ct < 4; ++ct) {
-    const int s = 16 * ct + acc_col();
-    gs_s[ct] = gs[s];
-    gr_s[ct] = gr[s];
-  }
-#pragma unroll
-  for (int ct = 0; ct < 4; ++ct) {
-    const int s = 16 * ct + acc_col();
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      const int t = 16 * w + acc_row(r);
-      const float g = G[ct][r], pq = P[ct][r];
-      const float es = __expf(fminf(gs_t[r] - gs_s[ct], 0.f));
-      const float esp = __expf(fminf(gsp_t[r] - gs_s[ct], 0.f));
-      const float er = __expf(fminf(gr_t[r] - gr_s[ct], 0.f));
-      const bool lower = s < t;
-      const float lm = lower ? 1.f : 0.f;
-      const float eg = (p.vflags & kVarDecayed) ? es : esp;
-      const float ep = (p.vflags & kVarUngated) ? esp : es;
-      mg[ct][r] = lower ? eg * g : 0.f;
-      mp[ct][r] = lower ? ep * pq : 0.f;
-      mr[ct][r] = s <= t ? er * pq : 0.f;
-      if constexpr (RDN) {
-        As[t * L::kLdA + s] = lm * (bt_t[r] * es * g);
-        Ar[t * L::kLdA + s] = lm * (gm_t[r] * er * g);
-      }
-    }
-  }
-  // the blocks on and below the diagonal, packed (tri_off): wave w holds
-  // block row w
-  if constexpr (sizeof(XT) == 2) {
-    // fp16 rows leave in 16-byte stores: each 16 x 32 half strip goes through
-    // this wave's block-product scratch (1 KiB, unused until the inversion),
-    // written column-major (one 8-byte store of 4 rows per tile and lane) and
-    // read back with transpose reads that give lane (g, i) row 16 w + i at
-    // columns 8 g .. 8 g + 7 of the half strip
-    typedef PadRows<XT, 16, 0> TS;   // [32 columns][16 rows]
-    XT* stg = reinterpret_cast<XT*>(W + w * 256);
-    const int g = (tid & 63) >> 4, i = tid & 15;
-#pragma unroll
-    for (int m = 0; m < 3; ++m) {
-      const floatx4* x = m == 0 ? mg : m == 1 ? mp : mr;
-      XT* base = mats + (m == 0 ? kMatMG : m == 1 ? kMatMP : kMatMR) * kMatElems;
-#pragma unroll
-      for (int half = 0; half < 2; ++half) {
-        if (2 * half > w) continue;   // both blocks of the strip pair above the diagonal
-        asm volatile("" ::: "memory");   // the previous half strip's reads come first
-#pragma unroll
-        for (int k = 0; k < 2; ++k) {
-          f16x4 v4;
-#pragma unroll
-          for (int r = 0; r < 4; ++r) v4[r] = (f16)x[2 * half + k][r];
-          *reinterpret_cast<f16x4*>(TS::ptr(stg, 16 * k + acc_col(), acc_row(0))) = v4;
-        }
-        asm volatile("" ::: "memory");   // the stores above come before the reads
-        const uint4 v = tile_token_rows16_sync<TS>(stg, 0);
-        const int s0 = 32 * half + 8 * g;
-        if ((s0 >> 4) <= w) *reinterpret_cast<uint4*>(base + tri_off(16 * w + i, s0)) = v;
-      }
-    }
-    asm volatile("" ::: "memory");
-  } else {
-#pragma unroll
-    for (int ct = 0; ct < 4; ++ct) {
-      if (ct > w) continue;
+  // ---- decayed, masked strips: MG, MP, MR in the operand type (registers),
+  //      A^S, A^R into region 0 ----
+  typedef XT X4 __attribute__((ext_vector_type(4)));
+  X4 mg[4], mp[4], mr[4];
+  {
+    const float gs_t = gs[t], gsp_t = gsp[t], gr_t = gr[t], bt_t = bt[t], gm_t = gm[t];
+    const bool dec = (p.vflags & kVarDecayed) != 0, ung = (p.vflags & kVarUngated) != 0;
+    auto strip = [&](int ct, auto strict) {
+      constexpr bool SL = decltype(strict)::value;   // strictly below the diagonal: no masks, exponents <= 0
+      const floatx4 gs_s = *reinterpret_cast<const floatx4*>(gs + 16 * ct + g4);
+      const floatx4 gr_s = *reinterpret_cast<const floatx4*>(gr + 16 * ct + g4);
+      floatx4 as, ar;
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
-        const int t = 16 * w + acc_row(r), s = 16 * ct + acc_col();
-        mats[kMatMG * kMatElems + tri_off(t, s)] = mg[ct][r];
-        mats[kMatMP * kMatElems + tri_off(t, s)] = mp[ct][r];
-        mats[kMatMR * kMatElems + tri_off(t, s)] = mr[ct][r];
+        const int s = 16 * ct + g4 + r;
+        const bool lower = SL || s < t, diag = SL || s <= t;
+        const float g = G[ct][r], pq = P[ct][r];
+        const float es = __expf(SL ? gs_t - gs_s[r] : fminf(gs_t - gs_s[r], 0.f));
+        const float esp = __expf(SL ? gsp_t - gs_s[r] : fminf(gsp_t - gs_s[r], 0.f));
+        const float er = __expf(SL ? gr_t - gr_s[r] : fminf(gr_t - gr_s[r], 0.f));
+        mg[ct][r] = from_f<XT>(lower ? (dec ? es : esp) * g : 0.f);
+        mp[ct][r] = from_f<XT>(lower ? (ung ? esp : es) * pq : 0.f);
+        mr[ct][r] = from_f<XT>(diag ? er * pq : 0.f);
+        as[r] = lower ? bt_t * es * g : 0.f;
+        ar[r] = lower ? gm_t * er * g : 0.f;
       }
+      if constexpr (RDN) {
+        *reinterpret_cast<floatx4*>(As + t * L::kLdA + 16 * ct + g4) = as;
+        *reinterpret_cast<floatx4*>(Ar + t * L::kLdA + 16 * ct + g4) = ar;
+      }
+    };
+#pragma unroll
+    for (int ct = 0; ct < 4; ++ct) {
+      if (ct < w) strip(ct, std::true_type{});
+      else if (ct == w) strip(ct, std::false_type{});
     }
   }
-  if constexpr (RDN) {
+  // this lane's four elements of block (w, j) of matrix m
+  auto put = [&](int m, int j, X4 v) {
+    *reinterpret_cast<X4*>(mats + m * kMatElems + tri_off(t, 16 * j + g4)) = v;
+  };
+  if constexpr (!RDN) {
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      if (j > w) continue;
+      put(kMatMG, j, mg[j]);
+      put(kMatMP, j, mp[j]);
+      put(kMatMR, j, mr[j]);
+    }
+  } else {
     __syncthreads();
     invert_unit_lower_pair(As, Ar, W);
     __syncthreads();
     // 8 consecutive elements per thread and step (16-byte fp16 stores), the
     // blocks on and below the diagonal packed (tri_off)
     for (int e = 8 * tid; e < kChunk * kChunk; e += 8 * kThreads) {
-      const int t = e / kChunk, s = e % kChunk;
-      const bool upper = (s >> 4) > (t >> 4);   // blocks above the diagonal are zero
+      const int tr = e / kChunk, s = e % kChunk;
+      const bool upper = (s >> 4) > (tr >> 4);   // blocks above the diagonal are zero
 #pragma unroll
       for (int m = 0; m < 2; ++m) {
         // two 16-byte reads (blocks of T above the diagonal are zero: the
         // bits read there are cleared with a mask, not read under a
         // condition)
-        const float* src = (m ? Ar : As) + tblk(t >> 4, s >> 4) + (t & 15) * L::kLdA + (s & 15);
+        const float* src = (m ? Ar : As) + tblk(tr >> 4, s >> 4) + (tr & 15) * L::kLdA + (s & 15);
         const uint4 b0 = keep_if(*reinterpret_cast<const uint4*>(src), !upper);
         const uint4 b1 = keep_if(*reinterpret_cast<const uint4*>(src + 4), !upper);
         const floatx4 f0 = __builtin_bit_cast(floatx4, b0), f1 = __builtin_bit_cast(floatx4, b1);
@@ -346,7 +333,7 @@ __global__ __launch_bounds__(kThreads) void prep_kernel(OpParams p) {
           vals[k] = from_f<XT>(f0[k]);
           vals[4 + k] = from_f<XT>(f1[k]);
         }
-        XT* dst = mats + (m ? kMatTR : kMatTS) * kMatElems + tri_off(t, s);
+        XT* dst = mats + (m ? kMatTR : kMatTS) * kMatElems + tri_off(tr, s);
         if (upper) continue;
         if constexpr (sizeof(XT) == 2) {
           *reinterpret_cast<uint4*>(dst) = *reinterpret_cast<const uint4*>(vals);
@@ -355,6 +342,50 @@ __global__ __launch_bounds__(kThreads) void prep_kernel(OpParams p) {
           for (int k = 0; k < 8; ++k) dst[k] = vals[k];
         }
       }
+    }
+    // ---- MG T^S, MP T^S, MR T^R: block row w, transposed again (D[j][t] =
+    //      sum_s T[s][j] M[t][s]): the strips in registers are the B operand,
+    //      T's columns, read from region 0, the A operand; lane (g, i) gets
+    //      row t at the four columns 16 j + 4g + 0..3 ----
+    typedef MfmaK16<XT> M;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      if (j > w) continue;
+      floatx4 dg = zero4(), dp = zero4(), dr = zero4();
+#pragma unroll
+      for (int m = j; m < 4; ++m) {
+        if (m > w) continue;
+        const float* ts = As + tblk(m, j) + g4 * L::kLdA + (lane & 15);
+        const float* tr = Ar + tblk(m, j) + g4 * L::kLdA + (lane & 15);
+        if constexpr (sizeof(XT) == 2) {
+          f16x4 fs, fr;
+#pragma unroll
+          for (int r = 0; r < 4; ++r) {
+            fs[r] = (f16)ts[r * L::kLdA];
+            fr[r] = (f16)tr[r * L::kLdA];
+          }
+          dg = M::mma(fs, mg[m], dg);
+          dp = M::mma(fs, mp[m], dp);
+          dr = M::mma(fr, mr[m], dr);
+        } else {   // four k-steps of 4: lane group g's s = 16 m + 4g + r in step r
+#pragma unroll
+          for (int r = 0; r < 4; ++r) {
+            dg = M::mma(ts[r * L::kLdA], mg[m][r], dg);
+            dp = M::mma(ts[r * L::kLdA], mp[m][r], dp);
+            dr = M::mma(tr[r * L::kLdA], mr[m][r], dr);
+          }
+        }
+      }
+      X4 og, op, orr;
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        og[r] = from_f<XT>(dg[r]);
+        op[r] = from_f<XT>(dp[r]);
+        orr[r] = from_f<XT>(dr[r]);
+      }
+      put(kMatMG, j, og);
+      put(kMatMP, j, op);
+      put(kMatMR, j, orr);
     }
   }
 }
