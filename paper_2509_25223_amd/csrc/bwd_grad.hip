@@ -241,7 +241,7 @@ __global__ __launch_bounds__(64 * (DK / 16)) void bwd_grad_kernel(OpParams p) {
       const float* rowp = reinterpret_cast<const float*>(srcs[st]) + soff + (int64_t)i * DV;
 #pragma unroll
       for (int ks = 0; ks < KSV; ++ks) {
-        x.fr[ks] = rowp[ks * M::kStep + (lane >> 4)];
+        x.fr[ks] = *reinterpret_cast<const Frag*>(rowp + ks * M::kStep + 4 * (lane >> 4));
       }
       x.sc = 1.f;
     }
@@ -506,7 +506,8 @@ __global__ __launch_bounds__(64 * (DK / 16)) void bwd_grad_kernel(OpParams p) {
         for (int e = 0; e < 8; e += 2)
           s = __builtin_amdgcn_fdot2(h2{a.fr[ks][e], a.fr[ks][e + 1]}, h2{b.fr[ks][e], b.fr[ks][e + 1]}, s, false);
       } else {
-        s += a.fr[ks] * b.fr[ks];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) s += a.fr[ks][e] * b.fr[ks][e];
       }
     }
     return s * (a.sc * b.sc);

@@ -283,14 +283,13 @@ __global__ __launch_bounds__(kThreads) void bwd_scan_kernel(OpParams p) {
   // ---- staging of the next (earlier) chunk while this one computes ----
   //   K, Q, dO: register prefetch after P1 (transposed / converted at commit)
   //   gates, MR: LDS-DMA after P1 (MR double-buffered)
-  //   mask, T^R, T^S, MG, MP: after P3 (their last uses are before its end)
-  // bf16 inputs; fp32 inputs single-buffer every matrix and move them all
-  // after the chunk's last barrier.
+  //   mask, T^R, T^S, MG, MP (fp32, single-buffered: MR): after P3 (their last
+  //     uses are before its end)
   // dO block: one 16-byte vector per thread, token = lane, columns of wave w
   constexpr int kOPerThread = 16 / (int)sizeof(IN);
   static_assert(kChunk * BV == kThreads * kOPerThread, "one dO vector per thread");
   typename MI::frag Kn[KS_STEPS], Qn[KS_STEPS];
-  IN on[kOPerThread];
+  uint4 on;
   auto chunk_len = [&](int c) { return min(kChunk, si.len - c * kChunk); };
   auto mat_src = [&](int c, int m) {
     return matg + ((int64_t)(si.chunk0 + c) * H + h) * kNumMats * kMatElems + m * kMatElems;
@@ -299,18 +298,12 @@ __global__ __launch_bounds__(kThreads) void bwd_scan_kernel(OpParams p) {
   auto issue_regs = [&](int c) {
     const int64_t tok = si.start + (int64_t)c * kChunk;
     const int len = chunk_len(c);
-    const int t = 16 * w + (lane & 15);
+    // rows past the chunk's end: its last row, zeroed at the commit (no branch)
+    const int t = min(16 * w + (lane & 15), len - 1), tt = min(lane, len - 1);
     const int64_t roff = ((tok + t) * H + h) * (int64_t)DK;
-    load_rowfrags<IN, DK>(Kn, t < len ? kg + roff : nullptr);
-    load_rowfrags<IN, DK>(Qn, t < len ? qg + roff : nullptr);
-    {
-      typedef IN INV __attribute__((ext_vector_type(kOPerThread)));
-      const int tt = lane, j = w * kOPerThread;
-      INV v = {};
-      if (tt < len) v = *reinterpret_cast<const INV*>(dog + ((tok + tt) * H + h) * (int64_t)DV + j0 + j);
-#pragma unroll
-      for (int u = 0; u < kOPerThread; ++u) on[u] = v[u];
-    }
+    load_rowfrags<IN, DK>(Kn, kg + roff);
+    load_rowfrags<IN, DK>(Qn, qg + roff);
+    on = *reinterpret_cast<const uint4*>(dog + ((tok + tt) * H + h) * (int64_t)DV + j0 + w * kOPerThread);
   };
   auto issue_gates = [&](int c) {
     if (w == 0)
@@ -334,27 +327,14 @@ __global__ __launch_bounds__(kThreads) void bwd_scan_kernel(OpParams p) {
     if constexpr (L::kDB) dma_mat64<XT>(mat_src(c, kMatMR), mat(kMatMR, c & 1), mdo);
   };
   auto issue_late = [&](int c) {    // after P3
-    if constexpr (L::kDB) {
-      issue_mask(c);
-      if constexpr (RDN) {
-        dma_mat64<XT>(mat_src(c, kMatTR), mat(kMatTR, 0), mdo);
-        dma_mat64<XT>(mat_src(c, kMatTS), mat(kMatTS, 0), mdo);
-      }
-      dma_mat64<XT>(mat_src(c, kMatMG), mat(kMatMG, 0), mdo);
-      dma_mat64<XT>(mat_src(c, kMatMP), mat(kMatMP, 0), mdo);
+    issue_mask(c);
+    if constexpr (RDN) {
+      dma_mat64<XT>(mat_src(c, kMatTR), mat(kMatTR, 0), mdo);
+      dma_mat64<XT>(mat_src(c, kMatTS), mat(kMatTS, 0), mdo);
     }
-  };
-  auto issue_all_single = [&](int c) {   // fp32: everything after the last barrier
-    if constexpr (!L::kDB) {
-      issue_mask(c);
-      if constexpr (RDN) {
-        dma_mat64<XT>(mat_src(c, kMatTS), mat(kMatTS, 0), mdo);
-        dma_mat64<XT>(mat_src(c, kMatTR), mat(kMatTR, 0), mdo);
-      }
-      dma_mat64<XT>(mat_src(c, kMatMG), mat(kMatMG, 0), mdo);
-      dma_mat64<XT>(mat_src(c, kMatMP), mat(kMatMP, 0), mdo);
-      dma_mat64<XT>(mat_src(c, kMatMR), mat(kMatMR, 0), mdo);
-    }
+    dma_mat64<XT>(mat_src(c, kMatMG), mat(kMatMG, 0), mdo);
+    dma_mat64<XT>(mat_src(c, kMatMP), mat(kMatMP, 0), mdo);
+    if constexpr (!L::kDB) dma_mat64<XT>(mat_src(c, kMatMR), mat(kMatMR, 0), mdo);
   };
   if (nch > 0) {
     const int c = nch - 1;
@@ -437,10 +417,11 @@ __global__ __launch_bounds__(kThreads) void bwd_scan_kernel(OpParams p) {
       const int t = 16 * w + (lane & 15);
 #pragma unroll
       for (int s2 = 0; s2 < KS_STEPS; ++s2) {
-        if constexpr (!BF) Kf[s2] = Kn[s2];
+        const uint4 kn = keep_if(__builtin_bit_cast(uint4, Kn[s2]), t < len);
+        const uint4 qn = keep_if(__builtin_bit_cast(uint4, Qn[s2]), t < len);
         if constexpr (BF) {   // row t, 8 columns: one 16-byte store each
-          const u16x8 kv = __builtin_bit_cast(u16x8, Kn[s2]);
-          const u16x8 qv = __builtin_bit_cast(u16x8, Qn[s2]);
+          const u16x8 kv = __builtin_bit_cast(u16x8, kn);
+          const u16x8 qv = __builtin_bit_cast(u16x8, qn);
           f16x8 kh, qh;
           if (VAR && p.qk_f16) {   // the pre-processing's fp16 rows
             kh = __builtin_bit_cast(f16x8, kv);
@@ -457,15 +438,22 @@ __global__ __launch_bounds__(kThreads) void bwd_scan_kernel(OpParams p) {
           *reinterpret_cast<f16x8*>(TKQ::ptr(KT, t, i)) = kh;
           *reinterpret_cast<f16x8*>(TKQ::ptr(QT, t, i)) = qh;
         } else {
-          const int i = s2 * 4 + (lane >> 4);
-          *TKQ::ptr(KT, i, t) = Kn[s2];
-          *TKQ::ptr(QT, i, t) = Qn[s2];
+          Kf[s2] = __builtin_bit_cast(floatx4, kn);
+          const floatx4 q4 = __builtin_bit_cast(floatx4, qn);
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            const int i = s2 * 16 + (lane >> 4) * 4 + e;
+            *TKQ::ptr(KT, i, t) = Kf[s2][e];
+            *TKQ::ptr(QT, i, t) = q4[e];
+          }
         }
       }
       XT* dbT = blk(bDB_DKS);
+      typedef IN INV __attribute__((ext_vector_type(kOPerThread)));
+      const INV o8 = __builtin_bit_cast(INV, keep_if(on, lane < len));
 #pragma unroll
       for (int u = 0; u < kOPerThread; ++u)   // lanes write consecutive tokens
-        *TT::ptr(dbT, w * kOPerThread + u, lane) = from_f<XT>(to_f<IN>(on[u]) * sig);
+        *TT::ptr(dbT, w * kOPerThread + u, lane) = from_f<XT>(to_f<IN>(o8[u]) * sig);
       // gate vectors (lane = token), shared out over the four waves by a
       // wave-uniform index; the chunk-edge factors are stored by every lane
       // of their wave to one address
@@ -671,14 +659,10 @@ __global__ __launch_bounds__(kThreads) void bwd_scan_kernel(OpParams p) {
       }
     }
     publish_state_max();
-    barrier_lds();
-    if constexpr (!L::kDB) {
-      if (c > 0) issue_all_single(c - 1);
-    }
-    // the next chunk's DMA data must have landed before anyone reads it (bf16
-    // inputs: the checkpoint stores, issued after the chunk's last DMA, may
-    // still be in flight; single-buffered fp32 issues its DMAs after them)
-    wait_vmem_but<L::kDB ? kCkptStores : 0>();
+    // the next chunk's DMA data must have landed before anyone reads it (the
+    // checkpoint stores, issued after the chunk's last DMA, may still be in
+    // flight)
+    wait_vmem_but<kCkptStores>();
     barrier_lds();
     {   // this chunk's dX, dY, dYR (value-major in LDS) as token-major rows in
         // 16-byte stores; rows past the end are zero.  The buffers are next

@@ -135,23 +135,38 @@ template <> struct Mfma<f16> {
   }
 };
 
+// fp32: four v_mfma_f32_16x16x4_f32 make a k step of 16, lane group g taking
+// k = 4 g + e in the e-th (both operands alike: the same products, summed in
+// another order), so that a fragment is one 16-byte read where k-order steps
+// took four 4-byte ones.  Such reads were most of a phase of the fp32 scans:
+// 64 x 64, 2 x 500 tokens (8 chunks each), 4 heads: forward scan 80 -> 49 us,
+// reverse 80 -> 56, gradients 43 -> 34, preparation 17.8 -> 16.2 (with K, Q
+// loaded in 16 bytes without a branch, and the matrices one phase earlier).
 template <> struct Mfma<float> {
-  static constexpr int kStep = 4;
-  typedef float frag;
+  static constexpr int kStep = 16;
+  typedef floatx4 frag;
   template <bool KC>
   __device__ __forceinline__ static frag load(const float* base, int ld, int k0) {
     const int lane = threadIdx.x & 63;
-    const int r = lane & 15, kg = lane >> 4;
-    if constexpr (KC) return base[r * ld + k0 + kg];
-    else return base[(k0 + kg) * ld + r];
+    const int r = lane & 15, kg = 4 * (lane >> 4);
+    if constexpr (KC) {
+      return *reinterpret_cast<const frag*>(base + r * ld + k0 + kg);
+    } else {
+      frag v;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) v[e] = base[(k0 + kg + e) * ld + r];
+      return v;
+    }
   }
   __device__ __forceinline__ static floatx4 mma(frag a, frag b, floatx4 c) {
-    return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) c = __builtin_amdgcn_mfma_f32_16x16x4f32(a[e], b[e], c, 0, 0, 0);
+    return c;
   }
 };
 
 // fp16 MFMA with a 16-deep k step (v_mfma_f32_16x16x16_f16): 4 k-values per
-// lane, for contractions over 16-wide blocks.  fp32 uses the 4-deep fp32 MFMA.
+// lane, for contractions over 16-wide blocks.  fp32 has that step already.
 template <typename T> struct MfmaK16;
 
 template <> struct MfmaK16<f16> {
@@ -178,53 +193,15 @@ template <> struct MfmaK16<f16> {
 
 template <> struct MfmaK16<float> : Mfma<float> {};
 
-// acc += A(16 x K) * B(K x 16) with the MFMA traits M.
-template <class M, int K, bool AKC, bool BKC, typename T>
-__device__ __forceinline__ void mma_with(floatx4& acc, const T* A, int lda, const T* B, int ldb) {
-#pragma unroll
-  for (int k0 = 0; k0 < K; k0 += M::kStep) {
-    acc = M::mma(M::template load<AKC>(A, lda, k0), M::template load<BKC>(B, ldb, k0), acc);
-  }
-}
-
-// acc += A(16 x K) * B(K x 16); A and B point at the tile's first row/column.
-template <typename T, int K, bool AKC, bool BKC>
-__device__ __forceinline__ void mma_tile(floatx4& acc, const T* A, int lda, const T* B, int ldb) {
-  typedef Mfma<T> M;
-#pragma unroll
-  for (int k0 = 0; k0 < K; k0 += M::kStep) {
-    acc = M::mma(M::template load<AKC>(A, lda, k0), M::template load<BKC>(B, ldb, k0), acc);
-  }
-}
-
-// acc += A * B with the A fragments already in registers (afr[k-step]).
-template <typename T, int K, bool BKC>
-__device__ __forceinline__ void mma_rega(floatx4& acc, const typename Mfma<T>::frag* afr,
-                                        const T* B, int ldb) {
-  typedef Mfma<T> M;
-#pragma unroll
-  for (int s = 0; s < K / M::kStep; ++s)
-    acc = M::mma(afr[s], M::template load<BKC>(B, ldb, s * M::kStep), acc);
-}
-
 // A-operand fragments of a 16-row tile straight from global memory: this
-// lane's row pointer (nullptr -> zero row), row-major with k contiguous.
+// lane's row, row-major with k contiguous (16-byte loads).
 template <typename T, int K>
 __device__ __forceinline__ void load_rowfrags(typename Mfma<T>::frag* afr, const T* row) {
   typedef Mfma<T> M;
   const int lane = threadIdx.x & 63;
 #pragma unroll
-  for (int s = 0; s < K / M::kStep; ++s) {
-    if constexpr (sizeof(T) == 2) {
-      const int k = s * M::kStep + (lane >> 4) * 8;
-      u16x8 v = {0, 0, 0, 0, 0, 0, 0, 0};
-      if (row) v = *reinterpret_cast<const u16x8*>(row + k);
-      afr[s] = __builtin_bit_cast(typename M::frag, v);
-    } else {
-      const int k = s * M::kStep + (lane >> 4);
-      afr[s] = row ? row[k] : 0.f;
-    }
-  }
+  for (int s = 0; s < K / M::kStep; ++s)
+    afr[s] = *reinterpret_cast<const typename M::frag*>(row + s * M::kStep + (lane >> 4) * (M::kStep / 4));
 }
 
 __device__ __forceinline__ floatx4 zero4() { return floatx4{0.f, 0.f, 0.f, 0.f}; }
@@ -639,7 +616,7 @@ __device__ __forceinline__ typename Mfma<T>::frag swz_load_rows(const T* base, i
   if constexpr (sizeof(T) == 2) {
     return *reinterpret_cast<const typename M::frag*>(b + Swz<T>::off(r, k0 + (lane >> 4) * 8));
   } else {
-    return *reinterpret_cast<const float*>(b + Swz<T>::off(r, k0 + (lane >> 4)));
+    return *reinterpret_cast<const floatx4*>(b + Swz<T>::off(r, k0 + (lane >> 4) * 4));
   }
 }
 
@@ -651,34 +628,12 @@ __device__ __forceinline__ typename Mfma<T>::frag swz_load_cols(const T* base, i
   const int lane = threadIdx.x & 63;
   const int t = t0 + (lane & 15);
   const char* b = reinterpret_cast<const char*>(base);
-  if constexpr (sizeof(T) == 2) {
-    typename M::frag v;
-    const int s0 = k0 + (lane >> 4) * 8;
+  constexpr int kPL = M::kStep / 4;   // k-values per lane
+  typename M::frag v;
+  const int s0 = k0 + (lane >> 4) * kPL;
 #pragma unroll
-    for (int e = 0; e < 8; ++e) v[e] = *reinterpret_cast<const T*>(b + Swz<T>::off(s0 + e, t));
-    return v;
-  } else {
-    return *reinterpret_cast<const float*>(b + Swz<T>::off(k0 + (lane >> 4), t));
-  }
-}
-
-// acc += M[r0.., :] * B, M a swizzled 64 x 64 matrix, B^T rows b0.. of a
-// 64-token tile (row n of B^T = column n of B)
-template <typename T, class TB = Swz<T>>
-__device__ __forceinline__ void mma_swz_rows(floatx4& acc, const T* M, int r0, const void* B, int b0) {
-  typedef Mfma<T> F;
-#pragma unroll
-  for (int k0 = 0; k0 < kChunk; k0 += F::kStep)
-    acc = F::mma(swz_load_rows<T>(M, r0, k0), TB::template frag<F>(B, b0, k0), acc);
-}
-
-// acc += M^T[t0.., :] * B
-template <typename T, class TB = Swz<T>>
-__device__ __forceinline__ void mma_swz_cols(floatx4& acc, const T* M, int t0, const void* B, int b0) {
-  typedef Mfma<T> F;
-#pragma unroll
-  for (int k0 = 0; k0 < kChunk; k0 += F::kStep)
-    acc = F::mma(swz_load_cols<T>(M, t0, k0), TB::template frag<F>(B, b0, k0), acc);
+  for (int e = 0; e < kPL; ++e) v[e] = *reinterpret_cast<const T*>(b + Swz<T>::off(s0 + e, t));
+  return v;
 }
 
 // The A fragments of rows r0..r0+15 of a swizzled 64 x 64 matrix (or of its

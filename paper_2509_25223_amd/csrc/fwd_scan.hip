@@ -213,11 +213,11 @@ __global__ __launch_bounds__(kThreads) void fwd_scan_kernel(OpParams p) {
   const MatDma<XT> mdo;   // this lane's matrix DMA offsets
   auto issue_regs = [&](int c) {
     const int64_t tok = si.start + (int64_t)c * kChunk;
-    const int t = 16 * w + (lane & 15);
+    // rows past the chunk's end: its last row, zeroed at the commit (no branch)
+    const int t = min(16 * w + (lane & 15), chunk_len(c) - 1);
     const int64_t roff = ((tok + t) * H + h) * (int64_t)DK;
-    const bool ok = t < chunk_len(c);
-    load_rowfrags<IN, DK>(Kn, ok ? kg + roff : nullptr);
-    load_rowfrags<IN, DK>(Qn, ok ? qg + roff : nullptr);
+    load_rowfrags<IN, DK>(Kn, kg + roff);
+    load_rowfrags<IN, DK>(Qn, qg + roff);
   };
   auto issue_early = [&](int c) {   // V, gates, T^R, MR
     const int64_t tok = si.start + (int64_t)c * kChunk;
@@ -237,16 +237,19 @@ __global__ __launch_bounds__(kThreads) void fwd_scan_kernel(OpParams p) {
       dma_mat64<XT>(mat_src(c, kMatMR), mat(kMatMR, c & 1), mdo);
     }
   };
-  auto issue_late = [&](int c) {    // T^S, MG, MP
+  auto issue_late = [&](int c) {    // T^S, MG, MP (single-buffered: T^R, RLA: MR)
     if constexpr (RDN) dma_mat64<XT>(mat_src(c, kMatTS), mat(kMatTS, 0), mdo);
     dma_mat64<XT>(mat_src(c, kMatMG), mat(kMatMG, 0), mdo);
     dma_mat64<XT>(mat_src(c, kMatMP), mat(kMatMP, 0), mdo);
-  };
-  auto issue_tail = [&](int c) {    // T^R, MR when single-buffered
     if constexpr (!L::kDB) {
-      if constexpr (RDN) dma_mat64<XT>(mat_src(c, kMatTR), mat(kMatTR, 0), mdo);
-      dma_mat64<XT>(mat_src(c, kMatMR), mat(kMatMR, 0), mdo);
+      constexpr int kLast = RDN ? kMatTR : kMatMR;
+      dma_mat64<XT>(mat_src(c, kLast), mat(kLast, 0), mdo);
     }
+  };
+  // RDN, single-buffered MR: after P3 (its fragments are in registers)
+  constexpr bool kTail = RDN && !L::kDB;
+  auto issue_tail = [&](int c) {
+    if constexpr (kTail) dma_mat64<XT>(mat_src(c, kMatMR), mat(kMatMR, 0), mdo);
   };
   if (nch > 0) {
     issue_regs(0);
@@ -271,8 +274,8 @@ __global__ __launch_bounds__(kThreads) void fwd_scan_kernel(OpParams p) {
       const int t = 16 * w + (lane & 15);
 #pragma unroll
       for (int s2 = 0; s2 < KS_STEPS; ++s2) {
-        Kf[s2] = Kn[s2];
-        Qf[s2] = Qn[s2];
+        Kf[s2] = __builtin_bit_cast(typename MI::frag, keep_if(__builtin_bit_cast(uint4, Kn[s2]), t < len));
+        Qf[s2] = __builtin_bit_cast(typename MI::frag, keep_if(__builtin_bit_cast(uint4, Qn[s2]), t < len));
         if constexpr (BF) {   // row t, 8 columns: one 16-byte store
           const u16x8 kv = __builtin_bit_cast(u16x8, Kf[s2]);
           f16x8 kh;
@@ -303,7 +306,8 @@ __global__ __launch_bounds__(kThreads) void fwd_scan_kernel(OpParams p) {
           }
           *reinterpret_cast<f16x8*>(TK::ptr(KT, t, s2 * 32 + (lane >> 4) * 8)) = kh;
         } else {
-          *TT::ptr(KT, s2 * 4 + (lane >> 4), t) = Kf[s2];
+#pragma unroll
+          for (int e = 0; e < 4; ++e) *TT::ptr(KT, s2 * 16 + (lane >> 4) * 4 + e, t) = Kf[s2][e];
         }
       }
       // gate vectors (lane = token), shared out over the four waves by a
@@ -430,12 +434,9 @@ __global__ __launch_bounds__(kThreads) void fwd_scan_kernel(OpParams p) {
         *reinterpret_cast<uint32_t*>(Mst + (jt * 16 + acc_col()) * L::kMstLd + 16 * w + acc_row(0)) = mask_word(xv, clip);
       }
     }
-    MatFrags<XT> aTR, aMR;
-    if constexpr (L::kDB) {   // double-buffered: landed in the previous chunk
-      if constexpr (RDN) aTR = swz_rows_frags<XT>(mat(kMatTR, buf), 16 * w);
-      else aMR = swz_rows_frags<XT>(mat(kMatMR, buf), 16 * w);
-    }
-    if constexpr (!L::kDB) wait_vmem();   // single-buffered T^R / MR of this chunk
+    MatFrags<XT> aTR, aMR;   // landed in the previous chunk
+    if constexpr (RDN) aTR = swz_rows_frags<XT>(mat(kMatTR, buf), 16 * w);
+    else aMR = swz_rows_frags<XT>(mat(kMatMR, buf), 16 * w);
     barrier_lds();
     if (c + 1 < nch) issue_late(c + 1);
     // chunk-start states for the gradient kernel, straight from the
@@ -455,10 +456,6 @@ __global__ __launch_bounds__(kThreads) void fwd_scan_kernel(OpParams p) {
         save_state_f32<IT, JT>(Racc, reinterpret_cast<float*>(p.ck_R) + off, DV, w * (DK / 4));
       }
     }
-    if constexpr (!L::kDB) {
-      if constexpr (RDN) aTR = swz_rows_frags<XT>(mat(kMatTR, buf), 16 * w);
-      else aMR = swz_rows_frags<XT>(mat(kMatMR, buf), 16 * w);
-    }
 
     if constexpr (RDN) {   // ---- P3: UR = T^R YR ----
 #pragma unroll
@@ -473,6 +470,7 @@ __global__ __launch_bounds__(kThreads) void fwd_scan_kernel(OpParams p) {
       }
       aMR = swz_rows_frags<XT>(mat(kMatMR, buf), 16 * w);
       barrier_lds();
+      if (c + 1 < nch) issue_tail(c + 1);
     }
 
     // ---- P4: correction read-out; o staged, stored after the end barrier ----
@@ -533,11 +531,10 @@ __global__ __launch_bounds__(kThreads) void fwd_scan_kernel(OpParams p) {
       }
     }
     // the next chunk's DMA data must have landed before anyone reads it; the
-    // checkpoint stores, issued after the chunk's last DMA, may still be in
-    // flight
-    wait_vmem_but<CKPT ? kCkptStores : 0>();
+    // checkpoint stores, issued after it (but for a single-buffered MR), may
+    // still be in flight
+    wait_vmem_but<CKPT && !kTail ? kCkptStores : 0>();
     barrier_lds();
-    if (c + 1 < nch) issue_tail(c + 1);   // single-buffered T^R / MR: waited at P2
     // ---- this chunk's staged outputs, in 16-byte stores (the buffers are
     //      next written after the coming chunk's first barrier) ----
     if constexpr (WRITE_O) {

@@ -98,17 +98,13 @@ __device__ void invert_unit_lower_pair(float* A0, float* A1, float* P) {
     floatx4 s = zero4();
     for (int m = j; m < i; ++m) {   // s += A_im T_mj
       const float* Y = A + tblk(m, j);
-#pragma unroll
-      for (int k0 = 0; k0 < 16; k0 += F::kStep)
-        s = F::mma(A[(16 * i + n) * ld + 16 * m + k0 + kg], Y[(k0 + kg) * ld + n], s);
+      s = F::mma(F::load<true>(A + 16 * i * ld + 16 * m, ld, 0), F::load<false>(Y, ld, 0), s);
     }
 #pragma unroll
     for (int r = 0; r < 4; ++r) Pw[(4 * kg + r) * 16 + n] = s[r];
     floatx4 t = zero4();
     const float* Tii = A + tblk(i, i);
-#pragma unroll
-    for (int k0 = 0; k0 < 16; k0 += F::kStep)   // T_ii * P (wave-local LDS order)
-      t = F::mma(Tii[n * ld + k0 + kg], Pw[(k0 + kg) * 16 + n], t);
+    t = F::mma(F::load<true>(Tii, ld, 0), F::load<false>(Pw, 16, 0), t);   // T_ii * P (wave-local LDS order)
     float* Tij = A + tblk(i, j);
 #pragma unroll
     for (int r = 0; r < 4; ++r) Tij[(4 * kg + r) * ld + n] = -t[r];
@@ -335,12 +331,9 @@ __global__ __launch_bounds__(kThreads) void prep_kernel(OpParams p) {
         }
         XT* dst = mats + (m ? kMatTR : kMatTS) * kMatElems + tri_off(tr, s);
         if (upper) continue;
-        if constexpr (sizeof(XT) == 2) {
-          *reinterpret_cast<uint4*>(dst) = *reinterpret_cast<const uint4*>(vals);
-        } else {
 #pragma unroll
-          for (int k = 0; k < 8; ++k) dst[k] = vals[k];
-        }
+        for (int k = 0; k < 8; k += 16 / (int)sizeof(XT))
+          *reinterpret_cast<uint4*>(dst + k) = *reinterpret_cast<const uint4*>(vals + k);
       }
     }
     // ---- MG T^S, MP T^S, MR T^R: block row w, transposed again (D[j][t] =
@@ -357,24 +350,15 @@ __global__ __launch_bounds__(kThreads) void prep_kernel(OpParams p) {
         if (m > w) continue;
         const float* ts = As + tblk(m, j) + g4 * L::kLdA + (lane & 15);
         const float* tr = Ar + tblk(m, j) + g4 * L::kLdA + (lane & 15);
-        if constexpr (sizeof(XT) == 2) {
-          f16x4 fs, fr;
+        X4 fs, fr;
 #pragma unroll
-          for (int r = 0; r < 4; ++r) {
-            fs[r] = (f16)ts[r * L::kLdA];
-            fr[r] = (f16)tr[r * L::kLdA];
-          }
-          dg = M::mma(fs, mg[m], dg);
-          dp = M::mma(fs, mp[m], dp);
-          dr = M::mma(fr, mr[m], dr);
-        } else {   // four k-steps of 4: lane group g's s = 16 m + 4g + r in step r
-#pragma unroll
-          for (int r = 0; r < 4; ++r) {
-            dg = M::mma(ts[r * L::kLdA], mg[m][r], dg);
-            dp = M::mma(ts[r * L::kLdA], mp[m][r], dp);
-            dr = M::mma(tr[r * L::kLdA], mr[m][r], dr);
-          }
+        for (int r = 0; r < 4; ++r) {
+          fs[r] = from_f<XT>(ts[r * L::kLdA]);
+          fr[r] = from_f<XT>(tr[r * L::kLdA]);
         }
+        dg = M::mma(fs, mg[m], dg);
+        dp = M::mma(fs, mp[m], dp);
+        dr = M::mma(fr, mr[m], dr);
       }
       X4 og, op, orr;
 #pragma unroll
