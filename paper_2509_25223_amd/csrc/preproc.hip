@@ -2,7 +2,7 @@
 // SiLU and L2 normalisation of queries and keys) and the reduction of the
 // decay re-parameterisation's per-head gradients.
 //
-// qk_norm_fwd: one wave per token-head row, y = SiLU(x) = x sigmoid(x),
+// qk_norm_fwd: per token-head row, y = SiLU(x) = x sigmoid(x),
 //   x_hat = y / max(||y||, 1e-12), stored as fp32 for fp32 inputs and as fp16
 //   for bf16 inputs (|x_hat| <= 1, so fp16's 11 significant bits lose
 //   nothing to range; bf16's 8 would cost about 2e-2 of max|error|/RMS on o
@@ -28,33 +28,60 @@ __device__ __forceinline__ float silu_sig(float x, float& s) {
   return x * s;
 }
 
-__device__ __forceinline__ float wave_allsum(float v) {
-#pragma unroll
-  for (int m = 1; m < 64; m <<= 1) v += __shfl_xor(v, m);
-  return v;
-}
+// Both kernels are bound by HBM: a row is taken in 16-byte pieces of the raw
+// input, DK / VL lanes a row (VL = 8 bf16 or 4 fp32 values), several rows a
+// wave and kRowSets of them in flight.  Measured at 320176 rows of 128 bf16, q
+// and k: with a wave per row and 4-byte accesses 137 us, here 62; the
+// gradient at 256000 rows 129 us, here 90.
+constexpr int kRowSets = 2;
+template <typename IN, int DK> struct NormRows {
+  static constexpr int VL = 16 / (int)sizeof(IN);   // values per lane
+  static constexpr int LPR = DK / VL;               // lanes per row
+  static constexpr int RPW = 64 / LPR;              // rows per wave and set
+  static constexpr int kRowsPerBlock = kWaves * RPW * kRowSets;
+  typedef IN InV __attribute__((ext_vector_type(VL)));
+  static_assert(LPR * VL == DK && LPR <= 32, "whole rows of lanes");
+  // this lane's row of set u, and its first value
+  __device__ __forceinline__ static int64_t row(int u) {
+    return ((int64_t)blockIdx.x * kWaves + (threadIdx.x >> 6)) * (RPW * kRowSets) + u * RPW + (threadIdx.x & 63) / LPR;
+  }
+  __device__ __forceinline__ static int col() { return (threadIdx.x & (LPR - 1)) * VL; }
+  __device__ __forceinline__ static float allsum(float v) {   // over the row's lanes
+    v = group_sum<LPR < 16 ? LPR : 16>(v);
+    if constexpr (LPR == 32) v += __shfl_xor(v, 16);
+    return v;
+  }
+};
 
 template <typename IN, typename NT, int DK>
 __global__ __launch_bounds__(kThreads) void qk_norm_fwd_kernel(const IN* __restrict__ q,
                                                                const IN* __restrict__ k,
                                                                NT* __restrict__ qh, NT* __restrict__ kh,
                                                                int64_t rows) {
-  constexpr int PL = DK / 64;   // values per lane
-  const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  const int64_t row = (int64_t)blockIdx.x * kWaves + w;
-  if (row >= rows) return;
-  const IN* src = (blockIdx.y == 0 ? q : k) + row * DK + lane * PL;
-  NT* dst = (blockIdx.y == 0 ? qh : kh) + row * DK + lane * PL;
-  float y[PL], ss = 0.f;
+  typedef NormRows<IN, DK> R;
+  constexpr int VL = R::VL;
+  typedef NT OutV __attribute__((ext_vector_type(VL)));
+  const IN* src = blockIdx.y == 0 ? q : k;
+  NT* dst = blockIdx.y == 0 ? qh : kh;
+  typename R::InV x[kRowSets];
 #pragma unroll
-  for (int e = 0; e < PL; ++e) {
-    float s;
-    y[e] = silu_sig(to_f<IN>(src[e]), s);
-    ss = __builtin_fmaf(y[e], y[e], ss);
+  for (int u = 0; u < kRowSets; ++u)   // rows past the end: the last row, not stored
+    x[u] = *reinterpret_cast<const typename R::InV*>(src + min(R::row(u), rows - 1) * DK + R::col());
+#pragma unroll
+  for (int u = 0; u < kRowSets; ++u) {
+    float y[VL], ss = 0.f;
+#pragma unroll
+    for (int e = 0; e < VL; ++e) {
+      float s;
+      y[e] = silu_sig(to_f<IN>(x[u][e]), s);
+      ss = __builtin_fmaf(y[e], y[e], ss);
+    }
+    const float inv = 1.f / fmaxf(sqrtf(R::allsum(ss)), kNormEps);
+    OutV o;
+#pragma unroll
+    for (int e = 0; e < VL; ++e) o[e] = from_f<NT>(y[e] * inv);
+    if (R::row(u) < rows) *reinterpret_cast<OutV*>(dst + R::row(u) * DK + R::col()) = o;
   }
-  const float inv = 1.f / fmaxf(sqrtf(wave_allsum(ss)), kNormEps);
-#pragma unroll
-  for (int e = 0; e < PL; ++e) dst[e] = from_f<NT>(y[e] * inv);
 }
 
 template <typename IN, typename OT, int DK>
@@ -64,33 +91,44 @@ __global__ __launch_bounds__(kThreads) void qk_norm_bwd_kernel(const IN* __restr
                                                                const float* __restrict__ dkh,
                                                                OT* __restrict__ dq, OT* __restrict__ dk,
                                                                int64_t rows) {
-  constexpr int PL = DK / 64;
-  const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  const int64_t row = (int64_t)blockIdx.x * kWaves + w;
-  if (row >= rows) return;
-  const int64_t off = row * DK + lane * PL;
-  const IN* src = (blockIdx.y == 0 ? q : k) + off;
-  const float* g = (blockIdx.y == 0 ? dqh : dkh) + off;
-  OT* dst = (blockIdx.y == 0 ? dq : dk) + off;
-  float x[PL], s[PL], y[PL], gh[PL], ss = 0.f;
+  typedef NormRows<IN, DK> R;
+  constexpr int VL = R::VL;
+  typedef float GV __attribute__((ext_vector_type(VL)));
+  typedef OT OutV __attribute__((ext_vector_type(VL)));
+  const IN* src = blockIdx.y == 0 ? q : k;
+  const float* g = blockIdx.y == 0 ? dqh : dkh;
+  OT* dst = blockIdx.y == 0 ? dq : dk;
+  typename R::InV xv[kRowSets];
+  GV gh[kRowSets];
 #pragma unroll
-  for (int e = 0; e < PL; ++e) {
-    x[e] = to_f<IN>(src[e]);
-    y[e] = silu_sig(x[e], s[e]);
-    gh[e] = g[e];
-    ss = __builtin_fmaf(y[e], y[e], ss);
+  for (int u = 0; u < kRowSets; ++u) {   // rows past the end: the last row, not stored
+    const int64_t off = min(R::row(u), rows - 1) * DK + R::col();
+    xv[u] = *reinterpret_cast<const typename R::InV*>(src + off);
+    gh[u] = *reinterpret_cast<const GV*>(g + off);
   }
-  const float nrm = sqrtf(wave_allsum(ss));
-  const bool floor = nrm < kNormEps;
-  const float inv = 1.f / fmaxf(nrm, kNormEps);
-  float dot = 0.f;
 #pragma unroll
-  for (int e = 0; e < PL; ++e) dot = __builtin_fmaf(y[e] * inv, gh[e], dot);
-  dot = wave_allsum(dot);
+  for (int u = 0; u < kRowSets; ++u) {
+    float x[VL], s[VL], y[VL], ss = 0.f;
 #pragma unroll
-  for (int e = 0; e < PL; ++e) {
-    const float dy = floor ? gh[e] * inv : (gh[e] - y[e] * inv * dot) * inv;
-    dst[e] = from_f<OT>(dy * s[e] * __builtin_fmaf(x[e], 1.f - s[e], 1.f));
+    for (int e = 0; e < VL; ++e) {
+      x[e] = to_f<IN>(xv[u][e]);
+      y[e] = silu_sig(x[e], s[e]);
+      ss = __builtin_fmaf(y[e], y[e], ss);
+    }
+    const float nrm = sqrtf(R::allsum(ss));
+    const bool floor = nrm < kNormEps;
+    const float inv = 1.f / fmaxf(nrm, kNormEps);
+    float dot = 0.f;
+#pragma unroll
+    for (int e = 0; e < VL; ++e) dot = __builtin_fmaf(y[e] * inv, gh[u][e], dot);
+    dot = R::allsum(dot);
+    OutV o;
+#pragma unroll
+    for (int e = 0; e < VL; ++e) {
+      const float dy = floor ? gh[u][e] * inv : (gh[u][e] - y[e] * inv * dot) * inv;
+      o[e] = from_f<OT>(dy * s[e] * __builtin_fmaf(x[e], 1.f - s[e], 1.f));
+    }
+    if (R::row(u) < rows) *reinterpret_cast<OutV*>(dst + R::row(u) * DK + R::col()) = o;
   }
 }
 
@@ -125,7 +163,8 @@ __global__ __launch_bounds__(kThreads) void decay_grad_reduce_kernel(const float
 template <typename IN, int DK>
 hipError_t qk_fwd_t(const void* q, const void* k, void* qh, void* kh, int64_t rows, hipStream_t s) {
   typedef typename std::conditional<sizeof(IN) == 2, f16, float>::type NT;
-  const dim3 grid((unsigned)((rows + kWaves - 1) / kWaves), 2);
+  constexpr int kRows = NormRows<IN, DK>::kRowsPerBlock;
+  const dim3 grid((unsigned)((rows + kRows - 1) / kRows), 2);
   hipLaunchKernelGGL((qk_norm_fwd_kernel<IN, NT, DK>), grid, dim3(kThreads), 0, s,
                      reinterpret_cast<const IN*>(q), reinterpret_cast<const IN*>(k),
                      reinterpret_cast<NT*>(qh), reinterpret_cast<NT*>(kh), rows);
@@ -135,7 +174,8 @@ hipError_t qk_fwd_t(const void* q, const void* k, void* qh, void* kh, int64_t ro
 template <typename IN, typename OT, int DK>
 hipError_t qk_bwd_t(const void* q, const void* k, const float* dqh, const float* dkh, void* dq,
                     void* dk, int64_t rows, hipStream_t s) {
-  const dim3 grid((unsigned)((rows + kWaves - 1) / kWaves), 2);
+  constexpr int kRows = NormRows<IN, DK>::kRowsPerBlock;
+  const dim3 grid((unsigned)((rows + kRows - 1) / kRows), 2);
   hipLaunchKernelGGL((qk_norm_bwd_kernel<IN, OT, DK>), grid, dim3(kThreads), 0, s,
                      reinterpret_cast<const IN*>(q), reinterpret_cast<const IN*>(k), dqh, dkh,
                      reinterpret_cast<OT*>(dq), reinterpret_cast<OT*>(dk), rows);
