@@ -591,7 +591,7 @@ __global__ __launch_bounds__(kThreads) void fwd_scan_kernel(OpParams p) {
 }
 
 // ---------------------------------------------------------------------------
-// Wave-specialised forward scan: bf16 inputs, 32 value columns, the boxed
+// Wave-specialised forward scan: bf16 inputs, 32 or 16 value columns, the boxed
 // operator (no variant flags); Q16: q, k are the fp16 rows of the in-operator
 // normalisation.  Eight waves per workgroup in two
 // groups of four that pass the same barriers in the same order:
@@ -605,15 +605,15 @@ __global__ __launch_bounds__(kThreads) void fwd_scan_kernel(OpParams p) {
 //     matrices, the gate values) — so it overlaps the chain instead of
 //     stalling it.
 // Per chunk (phase: chain waves | side waves):
-//   1: K^T commit; KS, KR, QS, QR;               | DMA of the next V, gates; the
+//   1: K^T commit; KS, KR, QS, QR;               | DMA of the next V; the
 //      Y = diag(b)(V - e^g KS)                      previous o, r rows and mask; S
 //                                                   checkpoint
 //   2: U = T^S Y; p, r = clip(V - p), mask, Y^R;  | the previous U^R rows
-//      base = e^g QS + MP T^S Y; next K, Q rows
+//      base = e^g QS + MP T^S Y; next K, Q rows     and gate vectors; DMA of the
+//                                                   gates after the next
 //   3: U^R = T^R Y^R; o = base + diag(gamma) c;   | DMA of the next T^S, MG, MP; R
 //      S update, its copies                         checkpoint; U rows
-//   4: R update, its copies                       | DMA of the next T^R, MR; gate
-//                                                   vectors
+//   4: R update, its copies                       | DMA of the next T^R, MR
 // RLA (U = Y, U^R = Y^R) has no barrier between phases 3 and 4 and refills
 // all its matrices in phase 3.  Within a phase the chain issues what it reads
 // from LDS first and its products in the order in which the next phase waits
@@ -629,13 +629,18 @@ __global__ __launch_bounds__(kThreads) void fwd_scan_kernel(OpParams p) {
 // phase instead of two (128 x 128, 16 heads): 1 x 16384 tokens, 64 workgroups,
 // 824 -> 656 us; saving, 4 x 4096 tokens, 256 workgroups, 287 -> 267 us;
 // normalised rows, saving, 16000 tokens packed, 414 -> 344 us.
-// V is double-buffered.  The precision scheme and the arithmetic are those of fwd_scan_kernel, except that the split-
-// state products sum the hi and lo terms per k-step and the checkpoints are
+// BV = 16 (not saving; a saved checkpoint's scales are per 32 columns): half
+// the columns per workgroup, for grids that leave CUs idle; a chunk is about
+// 4800 cycles (1 x 16384 tokens: 64 -> 128 workgroups, 651 -> 522 us, with the
+// gate vectors formed in phase 2).  Columns do not meet in any product, so the
+// bits are those of 32 columns.
+// V is double-buffered.  The precision scheme and the arithmetic are those of
+// fwd_scan_kernel, except that the split-state products sum the hi and lo terms per k-step and the checkpoints are
 // formed from the bf16 hi + lo state copies (the fp32 state to ~16 bits)
 // instead of the accumulators.  Q16 rows are split as bf16 hi + lo in the
 // chain's registers (a third MFMA adds lo x state-hi).
 // ---------------------------------------------------------------------------
-template <typename IN, int DK, int BV, bool RDN>
+template <typename IN, int DK, int BV, bool RDN, bool CKPT>
 struct FwdWsLayout {
   typedef f16 XT;
   typedef Tile<XT, kChunk> TT;
@@ -649,22 +654,21 @@ struct FwdWsLayout {
   static constexpr int kBufs = kMats + kNumSlots * kPkBytes;   // matrices as their ten lower blocks
   static constexpr int kBufBytes = BV * TT::kRowB;
   static constexpr int kVBytes = kChunk * BV * (int)sizeof(IN);
-  static constexpr int kVc = kBufs + 6 * kBufBytes;   // two V blocks (chunk parity)
+  static constexpr int kVc = kBufs + (CKPT ? 6 : 4) * kBufBytes;   // two V blocks (chunk parity)
   static constexpr int kGateVec = 8 * kChunk;         // floats per chunk's gate vectors
   static constexpr int kGates = kVc + 2 * kVBytes;    // two sets (chunk parity)
   static constexpr int kRst = kGates + 2 * kGateVec * 4;
-  static constexpr int kMst = kRst + kBufBytes;
+  static constexpr int kMst = kRst + (CKPT ? kBufBytes : 0);
   static constexpr int kMstLd = kChunk + 16;            // clip mask, value-major [BV][kMstLd] bytes
-  static constexpr int kGraw = kMst + BV * kMstLd;      // the gate block (one side wave's DMA)
+  static constexpr int kGraw = kMst + (CKPT ? BV * kMstLd : 0);   // the gate block (one side wave's DMA)
   static constexpr int kZero = kGraw + kGateBlock * 4;   // 16 zero bytes (blocks above the diagonal)
   // o of a chunk in fp32, column-major [BV][kOstLd] (the pad keeps the side's
   // 4-byte gathers of one token's 4 columns in distinct banks)
   static constexpr int kOstLd = kChunk + 4;
   static constexpr int kOst = kZero + 16;
   static constexpr int kBytes = kOst + BV * kOstLd * 4;
-  static_assert(sizeof(IN) == 2 && BV == 32, "bf16, 32 columns");
-  static_assert(kVBytes == 4 * 1024, "V block = one DMA instruction per side wave");
-  static_assert(kBytes <= 160 * 1024, "forward scan LDS");
+  static_assert(sizeof(IN) == 2 && (BV == 32 || (BV == 16 && !CKPT)), "bf16; saved blocks have 32 columns");
+  static_assert(kBytes <= (BV == 16 ? 80 : 160) * 1024, "forward scan LDS: one or two workgroups per CU");
   // RDN: T^S, MG, MP, T^R, MR; RLA: MG, MP, MR
   __device__ static constexpr int slot(int mat) {
     if (!RDN) return mat == kMatMG ? 0 : mat == kMatMP ? 1 : 2;
@@ -673,8 +677,8 @@ struct FwdWsLayout {
 };
 
 template <typename IN, int DK, int BV, bool RDN, bool WRITE_O, bool CKPT, bool Q16>
-__global__ __launch_bounds__(2 * kThreads) void fwd_scan_ws_kernel(OpParams p) {
-  typedef FwdWsLayout<IN, DK, BV, RDN> L;
+__global__ __launch_bounds__(2 * kThreads, 2) void fwd_scan_ws_kernel(OpParams p) {
+  typedef FwdWsLayout<IN, DK, BV, RDN, CKPT> L;
   typedef typename L::XT XT;
   typedef Mfma<IN> MI;
   typedef typename L::TT TT;
@@ -782,6 +786,7 @@ __global__ __launch_bounds__(2 * kThreads) void fwd_scan_ws_kernel(OpParams p) {
     const int64_t tok = si.start + (int64_t)c * kChunk;
     const int len = chunk_len(c);
     constexpr int kChunksPerRow = BV * (int)sizeof(IN) / 16;
+    if (ww >= L::kVBytes / 1024) return;    // one instruction per wave
     const int P = ww * 64 + lane, t = P / kChunksPerRow, cc = P % kChunksPerRow;
     const int ts = t < len ? t : len - 1;   // padding rows: any valid row (multiplied by 0)
     dma16(vg + (tok * H + h) * (int64_t)DV + j0 + (uint32_t)(ts * H * DV + cc * (16 / (int)sizeof(IN))),
@@ -807,7 +812,6 @@ __global__ __launch_bounds__(2 * kThreads) void fwd_scan_ws_kernel(OpParams p) {
   // 64-byte segment per token (lane (g, i): token 16 ww + i, values 8 g ..
   // 8 g + 7); rows past the end are zero
   auto store_block = [&](int c, int b, const XT* src) {
-    static_assert(BV == 32 && sizeof(XT) == 2, "four lanes per 32-value token row");
     const int64_t gc = si.chunk0 + c;
     const int t = 16 * ww + (lane & 15);
     const uint4 x = keep_if(tile_token_rows16_sync<TT>(src, 16 * ww), t < chunk_len(c));
@@ -921,12 +925,17 @@ __global__ __launch_bounds__(2 * kThreads) void fwd_scan_ws_kernel(OpParams p) {
     const int64_t ob = (tok * H + h) * (int64_t)DV + j0;
     const int t = 16 * ww + (lane >> 2);
     if (p.out_bf16) {
-      static_assert(BV == 32, "four lanes per bf16 row");
-      const int col = 8 * (lane & 3);
+      const int col = BV / 4 * (lane & 3);
+      u16* dst = reinterpret_cast<u16*>(p.o) + ob + (uint32_t)(t * H * DV + col);
       const uint4 a = lds_read4x1_sync(ost + col * L::kOstLd + t, L::kOstLd * 4);
-      const uint4 b = lds_read4x1_sync(ost + (col + 4) * L::kOstLd + t, L::kOstLd * 4);
-      const uint4 v = {cvt_pk_bf16(a.x, a.y), cvt_pk_bf16(a.z, a.w), cvt_pk_bf16(b.x, b.y), cvt_pk_bf16(b.z, b.w)};
-      if (t < len) *reinterpret_cast<uint4*>(reinterpret_cast<u16*>(p.o) + ob + (uint32_t)(t * H * DV + col)) = v;
+      if constexpr (BV == 32) {
+        const uint4 b = lds_read4x1_sync(ost + (col + 4) * L::kOstLd + t, L::kOstLd * 4);
+        const uint4 v = {cvt_pk_bf16(a.x, a.y), cvt_pk_bf16(a.z, a.w), cvt_pk_bf16(b.x, b.y), cvt_pk_bf16(b.z, b.w)};
+        if (t < len) *reinterpret_cast<uint4*>(dst) = v;
+      } else {
+        const uint2 v = {cvt_pk_bf16(a.x, a.y), cvt_pk_bf16(a.z, a.w)};
+        if (t < len) *reinterpret_cast<uint2*>(dst) = v;
+      }
     } else {
       const int col = 4 * (lane & 3);
 #pragma unroll
@@ -951,6 +960,7 @@ __global__ __launch_bounds__(2 * kThreads) void fwd_scan_ws_kernel(OpParams p) {
       issue_r_mats(0);
       wait_vmem();
       write_gates(0);
+      if (nch > 1) issue_gates(1);
     }
   }
   if constexpr (CH) {
@@ -1056,10 +1066,7 @@ __global__ __launch_bounds__(2 * kThreads) void fwd_scan_ws_kernel(OpParams p) {
       eS = gvec(c, 7)[0];
       eR = gvec(c, 7)[1];
     } else {
-      if (more) {
-        issue_gates(c + 1);
-        issue_v(c + 1);
-      }
+      if (more) issue_v(c + 1);
       pin();
       if constexpr (WRITE_O) {
         if (c > 0) store_o(c - 1);
@@ -1148,6 +1155,13 @@ __global__ __launch_bounds__(2 * kThreads) void fwd_scan_ws_kernel(OpParams p) {
       // this chunk's T^R, MR (from phase 4); since then the S checkpoint or,
       // not saving, the previous chunk's o
       if constexpr (RDN) wait_vmem_but<CKPT ? kCk + kBl : 1>();
+      // the next gates: their copy, issued here a chunk ago, has landed (phase
+      // 1 waited for what phase 3 issued after it; in chunk 0 for nothing)
+      if (more && ww == 0) {
+        if (c == 0) wait_vmem();
+        write_gates(c + 1);
+        if (c + 2 < nch) issue_gates(c + 2);
+      }
     }
     barrier_lds();
 
@@ -1205,10 +1219,9 @@ __global__ __launch_bounds__(2 * kThreads) void fwd_scan_ws_kernel(OpParams p) {
       if (more) {
         pin();
         issue_r_mats(c + 1);   // in the chain's registers since phase 3
-        // the next V and gates (from phase 1); since then at least a
-        // checkpoint or two, the matrices, U
+        // the next V (from phase 1); since then at least a checkpoint or two,
+        // the matrices, U
         wait_vmem_but<RDN ? 2 * kCk + kBl + 5 : 2 * kCk + 2 * kBl + 3>();
-        write_gates(c + 1);
       }
     }
     barrier_lds();
@@ -1250,14 +1263,26 @@ hipError_t launch_fwd_kernel(K kern, const OpParams& p, int BV, int threads, int
 // normalised rows, on the wave-specialised one (packed prefill of 20011
 // tokens from raw projections, H = 16, d = 128: 482 us with the four-wave
 // kernel, 397 us here).  fp32 inputs always take the four-wave kernel.
+// Not saving, 16 columns per workgroup as long as that leaves one workgroup
+// per CU: more would run in turns, one per CU (registers), at 4800 cycles a
+// chunk for 16 columns against 6600 for 32 (20011 tokens packed, 1200
+// workgroups of 32 columns: 279 us, in 16 columns 429).
+constexpr int kCUs = 256;
 template <typename IN, int DK, int BV, bool RDN, bool WRITE_O, bool CKPT>
 hipError_t launch_fwd_t(const OpParams& p, hipStream_t s) {
   typedef FwdLayout<IN, DK, BV, RDN> L;
   if constexpr (sizeof(IN) == 2) {
     if (!(p.vflags & kVarOperator)) {
+      if constexpr (!CKPT) {
+        if (p.st.nseq * p.H * (p.DV / 16) <= kCUs) {
+          auto kern = p.qk_f16 ? fwd_scan_ws_kernel<IN, DK, 16, RDN, WRITE_O, CKPT, true>
+                               : fwd_scan_ws_kernel<IN, DK, 16, RDN, WRITE_O, CKPT, false>;
+          return launch_fwd_kernel(kern, p, 16, 2 * kThreads, FwdWsLayout<IN, DK, 16, RDN, CKPT>::kBytes, s);
+        }
+      }
       auto kern = p.qk_f16 ? fwd_scan_ws_kernel<IN, DK, BV, RDN, WRITE_O, CKPT, true>
                            : fwd_scan_ws_kernel<IN, DK, BV, RDN, WRITE_O, CKPT, false>;
-      return launch_fwd_kernel(kern, p, BV, 2 * kThreads, FwdWsLayout<IN, DK, BV, RDN>::kBytes, s);
+      return launch_fwd_kernel(kern, p, BV, 2 * kThreads, FwdWsLayout<IN, DK, BV, RDN, CKPT>::kBytes, s);
     }
     auto kern = p.out_bf16 ? fwd_scan_kernel<IN, DK, BV, RDN, WRITE_O, CKPT, u16, true>
                            : fwd_scan_kernel<IN, DK, BV, RDN, WRITE_O, CKPT, float, true>;
