@@ -284,11 +284,11 @@ __global__ __launch_bounds__(64 * (DK / 16)) void bwd_grad_kernel(OpParams p) {
   const float gs = gb[lane], gsl = gb[kChunk - 1], gspr = gb[lane > 0 ? lane - 1 : 0];
   const float gr = gb[64 + lane], grl = gb[64 + kChunk - 1];
   const float gbe = gb[128 + lane], ggme = gb[192 + lane];
-  dma_tile64<TV, NW>(fb + blk_off(c, h, H, 0, DV), tokblk(bU));
-  dma_tile64<TV, NW>(fb + blk_off(c, h, H, 1, DV), tokblk(bUR));
-  dma_tile64<TV, NW>(bb + blk_off(c, h, H, 0, DV), tokblk(bDX));
-  dma_tile64<TV, NW>(bb + blk_off(c, h, H, 1, DV), tokblk(bDY));
-  dma_tile64<TV, NW>(bb + blk_off(c, h, H, 2, DV), tokblk(bDYR));
+  dma_block64<TV, NW>(fb + blk_off(c, h, H, 0, DV), tokblk(bU));
+  dma_block64<TV, NW>(fb + blk_off(c, h, H, 1, DV), tokblk(bUR));
+  dma_block64<TV, NW>(bb + blk_off(c, h, H, 0, DV), tokblk(bDX));
+  dma_block64<TV, NW>(bb + blk_off(c, h, H, 1, DV), tokblk(bDY));
+  dma_block64<TV, NW>(bb + blk_off(c, h, H, 2, DV), tokblk(bDYR));
 
   // V and r rows for the elementwise sums (consumed after the staging barrier)
   constexpr int kVV = kChunk * DV / kE / NT;
@@ -297,7 +297,7 @@ __global__ __launch_bounds__(64 * (DK / 16)) void bwd_grad_kernel(OpParams p) {
   for (int u = 0; u < kVV; ++u) {
     const int e = tid + u * NT, t = e / (DV / kE), j = (e % (DV / kE)) * kE;
     vrow[u] = *reinterpret_cast<const uint4*>(vg + (tok * H + h) * (int64_t)DV + (uint32_t)(in_row(t) * H * DV + j));
-    rrow[u] = *reinterpret_cast<const uint4*>(fb + blk_off(c, h, H, 2, DV) + (uint32_t)(t * DV + j));
+    rrow[u] = *reinterpret_cast<const uint4*>(fb + blk_off(c, h, H, 2, DV) + (uint32_t)blk_el(t, j));
   }
   // K, Q, dO rows: converted to the operand type (dO multiplied by the
   // upstream-gradient scale), stored swizzled

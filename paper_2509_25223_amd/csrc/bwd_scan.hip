@@ -316,7 +316,7 @@ __global__ __launch_bounds__(kThreads) void bwd_scan_kernel(OpParams p) {
       static_assert(kChunk * kPerRow == kThreads, "r block = one DMA instruction per wave");
       const int P = w * 64 + lane, t = P / kPerRow, cc = P % kPerRow;
       const XT* src = reinterpret_cast<const XT*>(p.fwd_blk) + blk_off(si.chunk0 + c, h, H, 2, DV) +
-                      (int64_t)t * DV + j0 + cc * (16 / (int)sizeof(XT));
+                      blk_el(t, j0 + cc * (16 / (int)sizeof(XT)));
       dma16(src, mask + w * 1024);
       return;
     }
@@ -683,7 +683,7 @@ __global__ __launch_bounds__(kThreads) void bwd_scan_kernel(OpParams p) {
           for (int k = 0; k < kVE; ++k) vals[k] = t < len ? TT::at(srcb, v * kVE + k, t) : from_f<XT>(0.f);
           x = *reinterpret_cast<const uint4*>(vals);
         }
-        *reinterpret_cast<uint4*>(bblk + blk_off(gc, h, H, b, DV) + (int64_t)t * DV + j0 + v * kVE) = x;
+        *reinterpret_cast<uint4*>(bblk + blk_off(gc, h, H, b, DV) + blk_el(t, j0 + v * kVE)) = x;
       }
     }
     write_copies();
@@ -945,7 +945,7 @@ __global__ __launch_bounds__(2 * kThreads) void bwd_scan_ws_kernel(OpParams p) {
     const XT* srcb = b == 0 ? blk(wDX) : b == 1 ? blk(wDY) : Yst;
     const int t = 16 * ww + (lane & 15);
     const uint4 x = keep_if(tile_token_rows16_sync<TT>(srcb, 16 * ww), t < chunk_len(c));
-    *reinterpret_cast<uint4*>(bblk + blk_off(gc, h, H, b, DV) + j0 + (uint32_t)(t * DV + 8 * (lane >> 4))) = x;
+    *reinterpret_cast<uint4*>(bblk + blk_off(gc, h, H, b, DV) + j0 * kChunk + (uint32_t)(t * 32 + 8 * (lane >> 4))) = x;
   };
   // side: dv rows 16 ww + 8 u + lane / 8, columns 4 (lane % 8) .. from the
   // column-major stage (four reads per 16 bytes)

@@ -580,7 +580,7 @@ __global__ __launch_bounds__(kThreads) void fwd_scan_kernel(OpParams p) {
           for (int k = 0; k < kVE; ++k) vals[k] = t < len ? TT::at(srcb, v * kVE + k, t) : from_f<XT>(0.f);
           x = *reinterpret_cast<const uint4*>(vals);
         }
-        *reinterpret_cast<uint4*>(fblk + blk_off(gc, h, H, b, DV) + (int64_t)t * DV + j0 + v * kVE) = x;
+        *reinterpret_cast<uint4*>(fblk + blk_off(gc, h, H, b, DV) + blk_el(t, j0 + v * kVE)) = x;
       }
     }
     write_state_copies();
@@ -815,7 +815,7 @@ __global__ __launch_bounds__(2 * kThreads, 2) void fwd_scan_ws_kernel(OpParams p
     const int64_t gc = si.chunk0 + c;
     const int t = 16 * ww + (lane & 15);
     const uint4 x = keep_if(tile_token_rows16_sync<TT>(src, 16 * ww), t < chunk_len(c));
-    *reinterpret_cast<uint4*>(fblk + blk_off(gc, h, H, b, DV) + j0 + (uint32_t)(t * DV + 8 * (lane >> 4))) = x;
+    *reinterpret_cast<uint4*>(fblk + blk_off(gc, h, H, b, DV) + j0 * kChunk + (uint32_t)(t * 32 + 8 * (lane >> 4))) = x;
   };
   // side waves: chunk c's r rows and clip mask columns (waves 2, 3; one
   // 16-byte piece per lane)

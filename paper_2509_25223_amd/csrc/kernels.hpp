@@ -69,8 +69,8 @@ struct OpParams {
   float* dS_sc = nullptr;
   float* dR_sc = nullptr;
   uint8_t* ck_mask = nullptr;   // [max_chunks][H][DV][64] 1 where |x| <= clip (mask_off)
-  // per-token blocks saved for the gradient kernel, [max_chunks][H][3][64][DV]
-  // (mm type, token-major, rows past the end of a sequence are zero):
+  // per-token blocks saved for the gradient kernel, [max_chunks][H][3] blocks
+  // of 64 x DV (mm type, blk_el layout, rows past the end of a sequence are zero):
   void* fwd_blk = nullptr;      // U, UR, r (clipped residual) from the forward scan
   void* bwd_blk = nullptr;      // dX, dY (RLA: dU), dYR (RLA: dUR) from the reverse scan
 
