@@ -945,7 +945,7 @@ __global__ __launch_bounds__(2 * kThreads) void bwd_scan_ws_kernel(OpParams p) {
     const XT* srcb = b == 0 ? blk(wDX) : b == 1 ? blk(wDY) : Yst;
     const int t = 16 * ww + (lane & 15);
     const uint4 x = keep_if(tile_token_rows16_sync<TT>(srcb, 16 * ww), t < chunk_len(c));
-    *reinterpret_cast<uint4*>(bblk + blk_off(gc, h, H, b, DV) + j0 * kChunk + (uint32_t)(t * 32 + 8 * (lane >> 4))) = x;
+    store_stream16(bblk + blk_off(gc, h, H, b, DV) + j0 * kChunk + (uint32_t)(t * 32 + 8 * (lane >> 4)), x);
   };
   // side: dv rows 16 ww + 8 u + lane / 8, columns 4 (lane % 8) .. from the
   // column-major stage (four reads per 16 bytes)
@@ -983,7 +983,7 @@ __global__ __launch_bounds__(2 * kThreads) void bwd_scan_ws_kernel(OpParams p) {
     for (int u = 0; u < IT; ++u) {
       const int t0 = ww * (DK / 4) + 16 * u;
       const uint4 x = tile_token_rows16_sync<TSC>(ckst + st * BV * (TSC::kRowB / 2), t0);
-      *reinterpret_cast<uint4*>(dst + (uint32_t)((t0 + (lane & 15)) * BV + 8 * (lane >> 4))) = x;
+      store_stream16(dst + (uint32_t)((t0 + (lane & 15)) * BV + 8 * (lane >> 4)), x);
     }
     if (st && lane < 2 * IT) {   // one lane per tile scale, both states in one store
       const int s2 = lane / IT, it = lane % IT;

@@ -410,6 +410,19 @@ __device__ __forceinline__ void lds_read_f32_sync(const float* p, const int (&id
   for (int n = 0; n < N; ++n) asm volatile("" : "+v"(out[n]));
 }
 
+// 16 bytes written once for a later kernel, non-temporally: a saving forward
+// and its backward move more than the caches hold, and lines left dirty by
+// one kernel are written back while the next reads.  Checkpoints and blocks
+// of the scans stored like this, 4 x 4096 tokens, 16 heads, 128 x 128: saving
+// forward scan 256 -> 266 us, but the kernels after it 24 -> 20 (absmax), 300 ->
+// 284 (reverse scan) and 350 -> 341 (gradients), a step 993 -> 973; a step of 16000
+// tokens from raw rows 1300 -> 1273.  Whole lines only: the gradients' 32-byte
+// pieces of a row took 356 us instead of 352 like this.
+__device__ __forceinline__ void store_stream16(void* p, uint4 v) {
+  typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+  __builtin_nontemporal_store(__builtin_bit_cast(u32x4, v), reinterpret_cast<u32x4*>(p));
+}
+
 // 16 bytes from LDS, issued as inline assembly so that the compiler does not
 // drain the wave's in-flight LDS-DMA before it (it cannot always prove the
 // addresses disjoint); waits for its own read.

@@ -815,7 +815,7 @@ __global__ __launch_bounds__(2 * kThreads, 2) void fwd_scan_ws_kernel(OpParams p
     const int64_t gc = si.chunk0 + c;
     const int t = 16 * ww + (lane & 15);
     const uint4 x = keep_if(tile_token_rows16_sync<TT>(src, 16 * ww), t < chunk_len(c));
-    *reinterpret_cast<uint4*>(fblk + blk_off(gc, h, H, b, DV) + j0 * kChunk + (uint32_t)(t * 32 + 8 * (lane >> 4))) = x;
+    store_stream16(fblk + blk_off(gc, h, H, b, DV) + j0 * kChunk + (uint32_t)(t * 32 + 8 * (lane >> 4)), x);
   };
   // side waves: chunk c's r rows and clip mask columns (waves 2, 3; one
   // 16-byte piece per lane)
@@ -875,7 +875,7 @@ __global__ __launch_bounds__(2 * kThreads, 2) void fwd_scan_ws_kernel(OpParams p
       };
       const uint4 v = {scaled(xh[it].x, xl[it].x), scaled(xh[it].y, xl[it].y), scaled(xh[it].z, xl[it].z),
                        scaled(xh[it].w, xl[it].w)};
-      *reinterpret_cast<uint4*>(dst + (uint32_t)((ww * (DK / 4) + 16 * it + (lane & 15)) * 32 + 8 * (lane >> 4))) = v;
+      store_stream16(dst + (uint32_t)((ww * (DK / 4) + 16 * it + (lane & 15)) * 32 + 8 * (lane >> 4)), v);
       sc[it] = exp2_int(ex);
     }
     static_assert(IT <= 2, "one or two tiles per wave");
