@@ -49,11 +49,11 @@ PEAK_HBM_GBS = 8000.0
 # numbers and commands are in profiles/), keyed by a hash of the kernel's
 # sources: a kernel changed since its counters were taken reports null.
 MEASURED_TRAFFIC = {
-    "prep": ("6d1faa0c02a5a94f", ('prep.hip', 'common.hpp', 'kernels.hpp'), 168030112, 109707264),
-    "grad_absmax": ("4b44d1d3f6c4cf05", ('grad_scale.hip', 'common.hpp', 'kernels.hpp'), 67196357, 131370),
-    "bwd_scan": ("89cbf6b2fe761bee", ('bwd_scan.hip', 'common.hpp', 'kernels.hpp'), 344435965, 613594794),
-    "bwd_grad": ("08848c41c5e9ad23", ('bwd_grad.hip', 'common.hpp', 'kernels.hpp'), 1232656230, 302521893),
-    "fwd_scan": ("017ad91aed089cd7", ('fwd_scan.hip', 'common.hpp', 'kernels.hpp'), 310649896, 638591833),
+    "prep": ("ca8a14450e1e9bfa", ('prep.hip', 'common.hpp', 'kernels.hpp'), 168134929, 109707264),
+    "grad_absmax": ("f88e1e130560045b", ('grad_scale.hip', 'common.hpp', 'kernels.hpp'), 67196085, 131349),
+    "bwd_scan": ("2667437b07d777b7", ('bwd_scan.hip', 'common.hpp', 'kernels.hpp'), 344385488, 613419008),
+    "bwd_grad": ("3a7f191e1eeca1cb", ('bwd_grad.hip', 'common.hpp', 'kernels.hpp'), 1232537094, 302493493),
+    "fwd_scan": ("54288ce06c30316e", ('fwd_scan.hip', 'common.hpp', 'kernels.hpp'), 310697625, 638591360),
     "decode": ("a6d19635132fd623", ('decode.hip', 'common.hpp', 'kernels.hpp'), 542746720, 539558630),
 }
 

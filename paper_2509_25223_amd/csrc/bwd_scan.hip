@@ -1353,7 +1353,8 @@ hipError_t launch_bwd_kernel(K kern, const OpParams& p, int BV, int threads, int
 // The operator's variants on the four-wave kernel; the boxed operator, with
 // plain or normalised rows, on the wave-specialised one (16000 packed tokens
 // from raw projections, H = 16, d = 128: 572 us with the four-wave kernel,
-// 427 us here).  fp32 inputs always take the four-wave kernel.
+// 427 us here, 334 since in fewer phases).  fp32 inputs always take the
+// four-wave kernel.
 template <typename IN, int DK, int BV, bool RDN>
 hipError_t launch_bwd_scan_t(const OpParams& p, hipStream_t s) {
   if constexpr (sizeof(IN) == 2) {

@@ -31,7 +31,7 @@
 //   everything else: fp16 operands (intermediates bounded by the data, clip
 //     and gates), fp32 accumulation.
 // With `CKPT` the chunk-start states, the clip mask |x| <= c and the blocks
-// U, UR and r (token-major, mm type) are stored for the backward pass.
+// U, UR and r (token-major in 32-column pieces, mm type) are stored for the backward pass.
 #include <type_traits>
 
 #include "kernels.hpp"
@@ -1262,7 +1262,8 @@ hipError_t launch_fwd_kernel(K kern, const OpParams& p, int BV, int threads, int
 // residual) on the four-wave kernel; the boxed operator, with plain or
 // normalised rows, on the wave-specialised one (packed prefill of 20011
 // tokens from raw projections, H = 16, d = 128: 482 us with the four-wave
-// kernel, 397 us here).  fp32 inputs always take the four-wave kernel.
+// kernel, 397 us here, 274 since in fewer phases).  fp32 inputs always take the
+// four-wave kernel.
 // Not saving, 16 columns per workgroup as long as that leaves one workgroup
 // per CU: more would run in turns, one per CU (registers), at 4800 cycles a
 // chunk for 16 columns against 6600 for 32 (20011 tokens packed, 1200
