@@ -162,7 +162,8 @@ typedef struct {
  *   RLA_FLAG_GATE_PREACT  alpha_s, alpha_r, beta, gamma hold pre-activations z:
  *       aS = exp(-a_h softplus(z + b_h)) (likewise aR, with the same per-head
  *       (a_h, b_h) from problem.decay_param: the Mamba-2 re-parameterisation),
- *       beta = sigmoid(z), gamma = sigmoid(z).  The backward returns the
+ *       beta = sigmoid(z), gamma = sigmoid(z).  Decays below 2^-126 are treated
+ *       as 2^-126 here too, and have no gradient.  The backward returns the
  *       gradients of the pre-activations and, in problem.decay_param_grad,
  *       of (a_h, b_h) summed over every token and both decays.
  */

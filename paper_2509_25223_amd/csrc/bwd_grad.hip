@@ -443,8 +443,10 @@ __global__ __launch_bounds__(64 * (DK / 16)) void bwd_grad_kernel(OpParams p) {
       int tt, st;
       tile_of(idx, tt, st);
       float zs[4], zp[4], zr[4], zb[4], zg[4];
-      // SL: a tile strictly below the diagonal (s < t everywhere: no masks,
-      // and every exponent is already <= 0)
+      // SL: a tile strictly below the diagonal (s < t everywhere: no masks, and
+      // no clamps: an exponent exceeds 0 by the prefix sums' rounding only,
+      // 1e-3 at the most, where every decay of the chunk is at its floor; with
+      // the clamps 348 us instead of 344 at 4 x 4096 tokens, 16 heads, 128 x 128)
       auto decay_step = [&](auto strict) {
       constexpr bool SL = decltype(strict)::value;
 #pragma unroll
@@ -729,13 +731,17 @@ __global__ __launch_bounds__(64 * (DK / 16)) void bwd_grad_kernel(OpParams p) {
       const float dgm = (esum[kChunk + t] + tot_at(sGM, t) + tot_at(sZGM, t)) * isig;
       if (vf & kVarGatePreact) {
         // log a = -A softplus(z + Bb): d/dz = -A sigmoid(z + Bb), d/dA = -softplus(z + Bb);
-        // beta = sigmoid(z): d/dz = beta (1 - beta), likewise gamma
+        // beta = sigmoid(z): d/dz = beta (1 - beta), likewise gamma; a decay at
+        // its floor has no gradient
         const float A = p.decay_param[h], Bb = p.decay_param[H + h];
         const float zs = a_s + Bb, zr = a_r + Bb;
+        float ls = softplus_f(zs), lr = softplus_f(zr);
+        if (-A * ls < kMinLogDecay) ss = ls = 0.f;
+        if (-A * lr < kMinLogDecay) sr = lr = 0.f;
         const float dzs = ss * (-A * sigmoid_f(zs)), dzr = sr * (-A * sigmoid_f(zr));
         p.dalpha_s[gi] = dzs;
         p.dalpha_r[gi] = dzr;
-        pa = -(ss * softplus_f(zs) + sr * softplus_f(zr));
+        pa = -(ss * ls + sr * lr);
         pb = dzs + dzr;
         p.dbeta[gi] = db * gbt[t] * (1.f - gbt[t]);
         p.dgamma[gi] = dgm * ggm[t] * (1.f - ggm[t]);

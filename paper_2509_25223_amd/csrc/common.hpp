@@ -1278,6 +1278,14 @@ __device__ __forceinline__ float log_decay(float a) { return __logf(fmaxf(a, 1.1
 __device__ __forceinline__ float softplus_f(float z) {
   return z > 20.f ? z : log1pf(__expf(z));
 }
+// log of a pre-activation's decay e^{-a softplus(z + b)}, floored alike: a
+// chunk's running sums keep their resolution behind any z (with a log decay of
+// -1e9 in them, the decays after it differ by multiples of 64).  NaN stays NaN.
+constexpr float kMinLogDecay = -87.3365448f;   // log 2^-126
+__device__ __forceinline__ float log_decay_preact(float a, float zb) {
+  const float la = -a * softplus_f(zb);
+  return la < kMinLogDecay ? kMinLogDecay : la;
+}
 __device__ __forceinline__ float sigmoid_f(float z) { return 1.f / (1.f + __expf(-z)); }
 
 // Inclusive prefix sum over the 64 lanes of a wave.

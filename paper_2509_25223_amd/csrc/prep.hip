@@ -24,7 +24,8 @@
 //   read-out's products all at once instead of one after the other (two
 //   dependent phases of a chunk less in the reverse, one in the forward).  RLA
 //   has T = I and U = Y: MG, MP, MR themselves.
-// All exponents are of differences g_t - g_s <= 0 (never e^{g} e^{-g}).
+// All exponents are of differences g_t - g_s, never e^{g} e^{-g}, clamped to
+// <= 0 (the prefix sums are monotone up to rounding only).
 #include <type_traits>
 
 #include "kernels.hpp"
@@ -192,13 +193,13 @@ __global__ __launch_bounds__(kThreads) void prep_kernel(OpParams p) {
     const int t = tid & 63;
     const bool valid = t < ci.len;
     float la = 0.f;
-    if (valid) la = pre ? -p.decay_param[h] * softplus_f(graw_a + p.decay_param[H + h]) : log_decay(graw_a);
-    const float cum = wave_inclusive_scan(la);
+    if (valid) la = pre ? log_decay_preact(p.decay_param[h], graw_a + p.decay_param[H + h]) : log_decay(graw_a);
+    const float cum = wave_inclusive_scan(la), prev = __shfl_up(cum, 1, 64);
     const float wb = valid ? (pre ? sigmoid_f(graw_b) : graw_b) : 0.f;
     if (tid < 64) {
       gs[t] = cum;
       bt[t] = wb;
-      gsp[t] = cum - la;
+      gsp[t] = t > 0 ? prev : 0.f;   // the scans' own g_{t-1}
     } else {
       gr[t] = cum;
       gm[t] = wb;
@@ -264,7 +265,7 @@ __global__ __launch_bounds__(kThreads) void prep_kernel(OpParams p) {
     const float gs_t = gs[t], gsp_t = gsp[t], gr_t = gr[t], bt_t = bt[t], gm_t = gm[t];
     const bool dec = (p.vflags & kVarDecayed) != 0, ung = (p.vflags & kVarUngated) != 0;
     auto strip = [&](int ct, auto strict) {
-      constexpr bool SL = decltype(strict)::value;   // strictly below the diagonal: no masks, exponents <= 0
+      constexpr bool SL = decltype(strict)::value;   // strictly below the diagonal: no masks
       const floatx4 gs_s = *reinterpret_cast<const floatx4*>(gs + 16 * ct + g4);
       const floatx4 gr_s = *reinterpret_cast<const floatx4*>(gr + 16 * ct + g4);
       floatx4 as, ar;
@@ -273,9 +274,9 @@ __global__ __launch_bounds__(kThreads) void prep_kernel(OpParams p) {
         const int s = 16 * ct + g4 + r;
         const bool lower = SL || s < t, diag = SL || s <= t;
         const float g = G[ct][r], pq = P[ct][r];
-        const float es = __expf(SL ? gs_t - gs_s[r] : fminf(gs_t - gs_s[r], 0.f));
-        const float esp = __expf(SL ? gsp_t - gs_s[r] : fminf(gsp_t - gs_s[r], 0.f));
-        const float er = __expf(SL ? gr_t - gr_s[r] : fminf(gr_t - gr_s[r], 0.f));
+        const float es = __expf(fminf(gs_t - gs_s[r], 0.f));
+        const float esp = __expf(fminf(gsp_t - gs_s[r], 0.f));
+        const float er = __expf(fminf(gr_t - gr_s[r], 0.f));
         mg[ct][r] = from_f<XT>(lower ? (dec ? es : esp) * g : 0.f);
         mp[ct][r] = from_f<XT>(lower ? (ung ? esp : es) * pq : 0.f);
         mr[ct][r] = from_f<XT>(diag ? er * pq : 0.f);
