@@ -904,6 +904,7 @@ __global__ __launch_bounds__(2 * kThreads) void bwd_scan_ws_kernel(OpParams p) {
       afr[s2] = __builtin_bit_cast(typename MI::frag, *reinterpret_cast<const u16x8*>(base + o + s2 * 32));
   };
   auto issue_do = [&](int c) {   // side: dO rows; past the end any valid row (zeroed by the chain)
+    RLA_NOTE("copy dO");
     static_assert(kChunk * BV * sizeof(IN) == kWaves * 1024, "dO block = one DMA instruction per side wave");
     constexpr int kPerRow = BV * (int)sizeof(IN) / 16;
     const int P = ww * 64 + lane, t = min(P / kPerRow, chunk_len(c) - 1), cc = P % kPerRow;
@@ -914,16 +915,21 @@ __global__ __launch_bounds__(2 * kThreads) void bwd_scan_ws_kernel(OpParams p) {
   // side wave 0 moves chunk c's gate block (g, h, beta, gamma) into LDS with
   // one DMA instruction and, after its wait, forms every gate vector
   auto issue_gates = [&](int c) {
-    if (ww == 0) dma_linear_wave(p.gate_ws + ((int64_t)(si.chunk0 + c) * H + h) * kGateBlock, graw, kGateBlock * 4);
+    if (ww != 0) return;
+    RLA_NOTE("copy gates");
+    dma_linear_wave(p.gate_ws + ((int64_t)(si.chunk0 + c) * H + h) * kGateBlock, graw, kGateBlock * 4);
   };
   auto write_gates = [&]() {
-    if (ww == 0) write_gate_vectors(graw, gates);
+    if (ww != 0) return;
+    RLA_NOTE("await gates");
+    write_gate_vectors(graw, gates);
   };
   // side: chunk c's matrix m; the side wave x issues two of the five DMA
   // instructions, the others one (the four of issue_mats: five instructions
   // of every wave; RLA's two: at least two)
   auto dma_mat = [&](int c, int m, int x) { dma_mat_packed<true>(mat_src(c, m), mat(m), (ww - x) & 3, kWaves); };
   auto issue_mats = [&](int c) {
+    RLA_NOTE("copy matrices");
     dma_mat(c, kMatMR, 0);
     dma_mat(c, kMatMP, 1);
     if constexpr (RDN) {
@@ -932,9 +938,13 @@ __global__ __launch_bounds__(2 * kThreads) void bwd_scan_ws_kernel(OpParams p) {
     }
   };
   // The side's waits leave its newest memory operations in flight, so the
-  // order in which it issues groups of them is pinned.
-  auto pin = [] { asm volatile("" ::: "memory"); };
+  // order in which it issues groups of them is pinned (RLA_NOTE).
+  auto issue_mg = [&](int c) {
+    RLA_NOTE("copy MG");
+    dma_mat(c, kMatMG, 2);
+  };
   auto issue_mask = [&](int c) {   // side
+    RLA_NOTE("copy mask");
     if (ww < BV / 16) dma_mask(p.ck_mask + mask_off(si.chunk0 + c, h, H, DV) + j0 * kChunk, mask, ww);
   };
   // side: block b (0 dX, 1 dY, 2 dYR) of chunk c, tokens 16 ww .. 16 ww + 15,
@@ -1029,13 +1039,14 @@ __global__ __launch_bounds__(2 * kThreads) void bwd_scan_ws_kernel(OpParams p) {
   } else {
     if (nch > 0) {
       const int c = nch - 1;
+      RLA_NOTE("side waves");
       load_rows(Kn, kg, c);
       load_rows(Qn, qg, c);
       issue_gates(c);
       issue_do(c);
       issue_mask(c);
       issue_mats(c);
-      dma_mat(c, kMatMG, 2);
+      issue_mg(c);
       wait_vmem();
       to_f16_rows(Kn);
       to_f16_rows(Qn);
@@ -1084,7 +1095,10 @@ __global__ __launch_bounds__(2 * kThreads) void bwd_scan_ws_kernel(OpParams p) {
     } else {
       commit_rows(KT, Kn);   // read by phases 1 and 2
       write_gates();
-      if (c + 1 < nch) store_ckpt(c + 1, 1);
+      if (c + 1 < nch) {
+        RLA_NOTE("store dR");
+        store_ckpt(c + 1, 1);
+      }
     }
     barrier_lds();
 
@@ -1149,15 +1163,16 @@ __global__ __launch_bounds__(2 * kThreads) void bwd_scan_ws_kernel(OpParams p) {
         load_rows(Kn, kg, c - 1);
         issue_gates(c - 1);
       }
-      pin();
       commit_rows(QT, Qn);   // read at the end of phase 2
       if (c + 1 < nch) {
+        RLA_NOTE("store dX, dYR");
         store_block(c + 1, 0);
         store_block(c + 1, 2);
       }
       // this chunk's matrices and mask (from phases 3, 4 of the later one);
       // since then MG, the checkpoints (2 IT + 1 stores) and these two blocks
       wait_vmem_but<2 * IT + 4>();
+      RLA_NOTE("await matrices, mask");
     }
     barrier_lds();
 
@@ -1234,13 +1249,17 @@ __global__ __launch_bounds__(2 * kThreads) void bwd_scan_ws_kernel(OpParams p) {
     } else {
       if (c > 0) {
         issue_do(c - 1);   // in the chain's tiles since phase 1
-        pin();
+        RLA_NOTE("load Q");
         load_rows(Qn, qg, c - 1);
       }
-      if (c + 1 < nch) store_block(c + 1, 1);
+      if (c + 1 < nch) {
+        RLA_NOTE("store dY");
+        store_block(c + 1, 1);
+      }
       // this chunk's MG (from phase 4 of the later one); since then the
       // checkpoints (2 IT + 1 stores) and three blocks
       wait_vmem_but<2 * IT + 4>();
+      RLA_NOTE("await MG");
     }
     barrier_lds();
 
@@ -1292,7 +1311,7 @@ __global__ __launch_bounds__(2 * kThreads) void bwd_scan_ws_kernel(OpParams p) {
         // compiler does not count past an LDS-DMA), and for none after it
         to_f16_rows(Kn);
         to_f16_rows(Qn);
-        pin();
+        RLA_NOTE("await dO");
         issue_mats(c - 1);   // in the chain's registers since phase 2
       }
     }
@@ -1306,10 +1325,10 @@ __global__ __launch_bounds__(2 * kThreads) void bwd_scan_ws_kernel(OpParams p) {
       publish_state_max();
     } else {
       if (c > 0) {   // the mask and MG are in the chain's registers since phases 2, 3
-        issue_mask(c - 1);
-        dma_mat(c - 1, kMatMG, 2);
+        issue_mask(c - 1);   // before MG: phase 1's wait counts on it
+        issue_mg(c - 1);
       }
-      pin();
+      RLA_NOTE("store dv, dS");   // dv: rows of this chunk only, perhaps none of this wave's
       store_dv(c);
       store_ckpt(c, 0);
     }
@@ -1327,6 +1346,7 @@ __global__ __launch_bounds__(2 * kThreads) void bwd_scan_ws_kernel(OpParams p) {
     if (p.dS0) save_state_f32<IT, JT>(dS, p.dS0 + state_off + j0, DV, ww * (DK / 4));
     if (p.dR0) save_state_f32<IT, JT>(dR, p.dR0 + state_off + j0, DV, ww * (DK / 4));
   } else if (nch > 0) {   // the first chunk's outputs
+    RLA_NOTE("end");
     store_block(0, 0);
     store_block(0, 1);
     store_block(0, 2);

@@ -604,6 +604,12 @@ __device__ __forceinline__ void dma_linear_wave(const void* gsrc, void* lds, int
 // DMA data visible.
 __device__ __forceinline__ void wait_vmem() { __builtin_amdgcn_s_waitcnt(0x0F70); }
 
+// A comment in the assembly that names the group of memory operations after it
+// ("copy X", "store X") or the copy that has landed before it ("await X"), for the
+// static check of the partial waits (tests/test_isa_waits.py); memory operations
+// are not moved across it, so it also pins the order of the groups.
+#define RLA_NOTE(text) asm volatile("; rla: " text ::: "memory")
+
 // s_waitcnt vmcnt(N): waits until at most N of this wave's vector memory
 // operations are outstanding.  They complete in issue order (loads, stores
 // and LDS-DMA share the counter), so with the last N operations being stores

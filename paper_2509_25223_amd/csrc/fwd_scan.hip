@@ -783,10 +783,14 @@ __global__ __launch_bounds__(2 * kThreads, 2) void fwd_scan_ws_kernel(OpParams p
   // side wave 0 moves chunk c's gate block (g, h, beta, gamma) into LDS with
   // one DMA instruction and, after its wait, forms every gate vector
   auto issue_gates = [&](int c) {
-    if (ww == 0) dma_linear_wave(p.gate_ws + ((int64_t)(si.chunk0 + c) * H + h) * kGateBlock, graw, kGateBlock * 4);
+    if (ww != 0) return;
+    RLA_NOTE("copy gates");
+    dma_linear_wave(p.gate_ws + ((int64_t)(si.chunk0 + c) * H + h) * kGateBlock, graw, kGateBlock * 4);
   };
   auto write_gates = [&](int c) {
-    if (ww == 0) write_gate_vectors(graw, gvec(c, 0));
+    if (ww != 0) return;
+    RLA_NOTE("await gates");
+    write_gate_vectors(graw, gvec(c, 0));
   };
   // side waves: the five DMA instructions of the g-th matrix of a group are
   // dealt round-robin over the four side waves (the group's instruction k
@@ -795,6 +799,7 @@ __global__ __launch_bounds__(2 * kThreads, 2) void fwd_scan_ws_kernel(OpParams p
     dma_mat_packed<false>(mat_src(c, m), mat(m), ((ww - 5 * g) % 4 + 4) % 4, kWaves);
   };
   auto issue_v = [&](int c) {   // V of chunk c (double-buffered)
+    RLA_NOTE("copy V");
     const int64_t tok = si.start + (int64_t)c * kChunk;
     const int len = chunk_len(c);
     constexpr int kChunksPerRow = BV * (int)sizeof(IN) / 16;
@@ -805,19 +810,20 @@ __global__ __launch_bounds__(2 * kThreads, 2) void fwd_scan_ws_kernel(OpParams p
           reinterpret_cast<char*>(vblk(c)) + ww * 1024);
   };
   auto issue_s_mats = [&](int c) {   // T^S, MG, MP (RLA: MG, MP, MR)
+    RLA_NOTE("copy S matrices");
     dma_mat(c, RDN ? (int)kMatTS : (int)kMatMR, 0);
     dma_mat(c, kMatMG, 1);
     dma_mat(c, kMatMP, 2);
   };
   auto issue_r_mats = [&](int c) {   // T^R, MR
     if constexpr (RDN) {
+      RLA_NOTE("copy R matrices");
       dma_mat(c, kMatTR, 0);
       dma_mat(c, kMatMR, 1);
     }
   };
   // The side's waits leave its newest memory operations in flight, so the
-  // order in which it issues groups of them is pinned.
-  auto pin = [] { asm volatile("" ::: "memory"); };
+  // order in which it issues groups of them is pinned (RLA_NOTE).
   constexpr int kCk = CKPT ? IT + 1 : 0;   // stores of one checkpoint
   constexpr int kBl = CKPT ? 1 : 0;        // store of one block
   // side waves: tokens 16 ww .. 16 ww + 15 of a token-major block, one
@@ -966,6 +972,7 @@ __global__ __launch_bounds__(2 * kThreads, 2) void fwd_scan_ws_kernel(OpParams p
       issue_rows(Kn, kg, 0);
       issue_rows(Qn, qg, 0);
     } else {
+      RLA_NOTE("side waves");
       issue_gates(0);
       issue_v(0);
       issue_s_mats(0);
@@ -1079,18 +1086,17 @@ __global__ __launch_bounds__(2 * kThreads, 2) void fwd_scan_ws_kernel(OpParams p
       eR = gvec(c, 7)[1];
     } else {
       if (more) issue_v(c + 1);
-      pin();
-      if constexpr (WRITE_O) {
-        if (c > 0) store_o(c - 1);
+      if (c > 0) {
+        RLA_NOTE("store o, r");   // of a whole chunk: every row of o is there
+        if constexpr (WRITE_O) store_o(c - 1);
+        if constexpr (CKPT) store_resid(c - 1);
       }
-      if constexpr (CKPT) {
-        if (c > 0) store_resid(c - 1);
-        if constexpr (RDN) store_ckpt(c, 0);   // chunk-start S
-      }
+      if constexpr (CKPT && RDN) store_ckpt(c, 0);   // chunk-start S
       // this chunk's T^S, MG, MP (from phase 3); since then: RDN T^R, MR, the
       // R checkpoint, U and what is above; RLA U, U^R and what is above (the
       // previous chunk's o and r; chunk 0 waited for everything)
       wait_vmem_but<RDN ? 2 + 2 * kCk + kBl : CKPT ? 3 : 1>();
+      RLA_NOTE("await S matrices");
     }
     barrier_lds();
 
@@ -1158,7 +1164,10 @@ __global__ __launch_bounds__(2 * kThreads, 2) void fwd_scan_ws_kernel(OpParams p
     } else {
       if constexpr (CKPT) {
         if constexpr (RDN) {
-          if (c > 0) store_block(c - 1, 1, URt);
+          if (c > 0) {
+            RLA_NOTE("store U^R");
+            store_block(c - 1, 1, URt);
+          }
         } else {
           store_ckpt(c, 0);
           store_ckpt(c, 1);
@@ -1166,11 +1175,17 @@ __global__ __launch_bounds__(2 * kThreads, 2) void fwd_scan_ws_kernel(OpParams p
       }
       // this chunk's T^R, MR (from phase 4); since then the S checkpoint or,
       // not saving, the previous chunk's o
-      if constexpr (RDN) wait_vmem_but<CKPT ? kCk + kBl : 1>();
+      if constexpr (RDN) {
+        wait_vmem_but<CKPT ? kCk + kBl : 1>();
+        RLA_NOTE("await R matrices");
+      }
       // the next gates: their copy, issued here a chunk ago, has landed (phase
       // 1 waited for what phase 3 issued after it; in chunk 0 for nothing)
       if (more && ww == 0) {
-        if (c == 0) wait_vmem();
+        if (c == 0) {
+          RLA_NOTE("first chunk");
+          wait_vmem();
+        }
         write_gates(c + 1);
         if (c + 2 < nch) issue_gates(c + 2);
       }
@@ -1212,8 +1227,8 @@ __global__ __launch_bounds__(2 * kThreads, 2) void fwd_scan_ws_kernel(OpParams p
       write_state_copies(Sacc, Shi, Slo);
     } else {
       if (more) issue_s_mats(c + 1);   // in the chain's registers since phase 2
-      pin();
       if constexpr (CKPT) {
+        RLA_NOTE("store R, U");
         if constexpr (RDN) store_ckpt(c, 1);   // chunk-start R (rewritten in phase 4)
         store_block(c, 0, Ut);
         if constexpr (!RDN) store_block(c, 1, URt);
@@ -1229,11 +1244,11 @@ __global__ __launch_bounds__(2 * kThreads, 2) void fwd_scan_ws_kernel(OpParams p
       write_state_copies(Racc, Rhi, Rlo);
     } else {
       if (more) {
-        pin();
         issue_r_mats(c + 1);   // in the chain's registers since phase 3
         // the next V (from phase 1); since then at least a checkpoint or two,
         // the matrices, U
         wait_vmem_but<RDN ? 2 * kCk + kBl + 5 : 2 * kCk + 2 * kBl + 3>();
+        RLA_NOTE("await V");
       }
     }
     barrier_lds();
@@ -1241,6 +1256,7 @@ __global__ __launch_bounds__(2 * kThreads, 2) void fwd_scan_ws_kernel(OpParams p
 
   if constexpr (!CH) {
     if (nch > 0) {
+      RLA_NOTE("end");
       if constexpr (WRITE_O) store_o(nch - 1);
       if constexpr (CKPT) {
         store_resid(nch - 1);
