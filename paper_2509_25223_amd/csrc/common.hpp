@@ -43,12 +43,9 @@ template <> __device__ __forceinline__ u16 from_f<u16>(float x) { return f2bf(x)
 __device__ __forceinline__ f16 to_f16(float x) { return (f16)x; }
 template <> __device__ __forceinline__ f16 from_f<f16>(float x) { return to_f16(x); }
 
-// bf16 residual of x after its bf16 rounding hi: x ~= hi + lo to ~16 bits,
-// with fp32 range.  Used for state operands (split-bf16 products).
-__device__ __forceinline__ u16 bf16_lo(float x, u16 hi) { return f2bf(x - bf2f(hi)); }
-
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
-// The same split for a pair, as two packed words (first element in the low
+// An fp32 pair as bf16 hi + bf16 lo (~16 bits with fp32's range: the state
+// operands of the split products), two packed words (first element in the low
 // half): hi by one v_cvt_pk_bf16_f32; each residual x - hi, exact in fp32, as
 // the bf16 dot product hi . (-1, -0) + x (v_dot2_f32_bf16: bf16 products are
 // exact), in place of a shift or mask and a subtraction; lo by one more
@@ -314,25 +311,6 @@ __device__ __forceinline__ uint4 tile_token_vec8(const void* base, int j0) {
   const char* b = reinterpret_cast<const char*>(base);
   const u16x4 a = lds_read_tr16(b + TL::off(j, t));
   const u16x4 c = lds_read_tr16(b + TL::off(j + 4, t));
-  return uint4{a[0] | ((uint32_t)a[1] << 16), a[2] | ((uint32_t)a[3] << 16),
-               c[0] | ((uint32_t)c[1] << 16), c[2] | ((uint32_t)c[3] << 16)};
-}
-
-// tile_token_vec8 with its two transpose reads issued as inline assembly, so
-// that the compiler does not drain the wave's in-flight LDS-DMA before them;
-// the function waits for its own reads (lgkmcnt(0), tied to their registers).
-template <class TL>
-__device__ __forceinline__ uint4 tile_token_vec8_sync(const void* base, int j0) {
-  typedef __attribute__((address_space(3))) const char* lds_ptr;
-  const int lane = threadIdx.x & 63, jj = lane & 15;
-  const int t = 16 * (lane >> 4) + 4 * (jj & 3), j = j0 + (jj >> 2);
-  const char* b = reinterpret_cast<const char*>(base);
-  const uint32_t a0 = (uint32_t)(uintptr_t)(lds_ptr)(b + TL::off(j, t));
-  const uint32_t a1 = (uint32_t)(uintptr_t)(lds_ptr)(b + TL::off(j + 4, t));
-  u16x4 a, c;
-  asm volatile("ds_read_b64_tr_b16 %0, %1" : "=v"(a) : "v"(a0));
-  asm volatile("ds_read_b64_tr_b16 %0, %1" : "=v"(c) : "v"(a1));
-  asm volatile("s_waitcnt lgkmcnt(0)" : "+v"(a), "+v"(c));
   return uint4{a[0] | ((uint32_t)a[1] << 16), a[2] | ((uint32_t)a[3] << 16),
                c[0] | ((uint32_t)c[1] << 16), c[2] | ((uint32_t)c[3] << 16)};
 }
@@ -878,14 +856,6 @@ __device__ __forceinline__ float group_sum(float x) {
   if constexpr (N >= 16) x += dpp<0x140>(x); // row_mirror
   return x;
 }
-template <int N>
-__device__ __forceinline__ float group_max(float x) {
-  x = fmaxf(x, dpp<0xB1>(x));
-  if constexpr (N >= 4) x = fmaxf(x, dpp<0x4E>(x));
-  if constexpr (N >= 8) x = fmaxf(x, dpp<0x141>(x));
-  if constexpr (N >= 16) x = fmaxf(x, dpp<0x140>(x));
-  return x;
-}
 
 // Power-of-two scale 2^e for a block of values whose largest magnitude has
 // the fp32 bit pattern mbits: e = (biased exponent) - 140, so that the largest
@@ -903,16 +873,6 @@ __device__ __forceinline__ float exp2_int(int e) {   // 2^e, -126 <= e <= 127
 template <int CTRL>
 __device__ __forceinline__ uint32_t dpp_u32(uint32_t x) {
   return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, CTRL, 0xF, 0xF, false);
-}
-
-// Largest |x| over a 16-lane row, as an fp32 bit pattern (unsigned compares
-// of the magnitude bits, which fold into DPP max instructions).
-__device__ __forceinline__ uint32_t row16_absmax_bits(float a, float b) {
-  uint32_t m = max(__float_as_uint(a) & 0x7FFFFFFFu, __float_as_uint(b) & 0x7FFFFFFFu);
-  m = max(m, dpp_u32<0xB1>(m));
-  m = max(m, dpp_u32<0x4E>(m));
-  m = max(m, dpp_u32<0x141>(m));
-  return max(m, dpp_u32<0x140>(m));
 }
 
 // Largest |x| over a wave, as an fp32 bit pattern (wave-uniform): the lane's
@@ -1124,18 +1084,6 @@ __device__ __forceinline__ void save_state_f16(const floatx4 (&acc)[IT][2], f16*
   save_state_f16_max<IT>(acc, mt, dst, ld, sc, sc_ld, row0);
 }
 
-// Scheduling hint for the enclosing basic block: alternate one LDS read, two
-// MFMAs and VALU_PER vector instructions, NMFMA / 2 times.
-template <int NMFMA, int VALU_PER>
-__device__ __forceinline__ void interleave_mfma_valu() {
-#pragma unroll
-  for (int i = 0; i < NMFMA / 2; ++i) {
-    __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);        // DS read
-    __builtin_amdgcn_sched_group_barrier(0x008, 2, 0);        // MFMA
-    __builtin_amdgcn_sched_group_barrier(0x002, VALU_PER, 0); // VALU
-  }
-}
-
 // fp32 counterpart of save_state_f16 (no scales): dst[row * ld + col].
 template <int IT, int JT>
 __device__ __forceinline__ void save_state_f32(const floatx4 (&acc)[IT][JT], float* dst, int64_t ld,
@@ -1170,23 +1118,6 @@ __device__ __forceinline__ void load_acc_state(floatx4 (&acc)[IT][JT], const flo
         acc[it][jt][r] = base[off + (int64_t)(row0 + 16 * it + acc_row(r)) * ld + 16 * jt + acc_col()];
 }
 
-// Stores the 4 accumulator rows of this lane, column-major into LDS as a
-// transposed tile: dst[col * ld + row]  (4 consecutive elements).
-template <typename T>
-__device__ __forceinline__ void store_acc_t(T* dst, int ld, floatx4 v) {
-  T* p = dst + acc_col() * ld + acc_row(0);
-  if constexpr (sizeof(T) == 2) {   // one 8-byte store (p is 8-byte aligned)
-    typedef T T4 __attribute__((ext_vector_type(4)));
-    T4 w;
-#pragma unroll
-    for (int r = 0; r < 4; ++r) w[r] = from_f<T>(v[r]);
-    *reinterpret_cast<T4*>(p) = w;
-  } else {
-#pragma unroll
-    for (int r = 0; r < 4; ++r) p[r] = from_f<T>(v[r]);
-  }
-}
-
 // Stores the 4 accumulator rows of this lane transposed into a tile: element
 // (row, col) of the accumulator tile goes to tile row r0 + col, column
 // c0 + row (4 consecutive elements, one 8- or 16-byte store).
@@ -1215,14 +1146,6 @@ __device__ __forceinline__ floatx4 load_acc_tile(const void* base, int r0, int c
 #pragma unroll
   for (int r = 0; r < 4; ++r) v[r] = to_f<T>(w[r]);
   return v;
-}
-
-// Stores the 4 accumulator rows of this lane into LDS row-major: dst[row * ld + col].
-template <typename T>
-__device__ __forceinline__ void store_acc(T* dst, int ld, floatx4 v) {
-  T* p = dst + acc_row(0) * ld + acc_col();
-#pragma unroll
-  for (int r = 0; r < 4; ++r) p[r * ld] = from_f<T>(v[r]);
 }
 
 // ---------------------------------------------------------------------------

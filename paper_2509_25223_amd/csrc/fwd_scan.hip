@@ -902,7 +902,6 @@ __global__ __launch_bounds__(2 * kThreads, 2) void fwd_scan_ws_kernel(OpParams p
       (st ? p.ck_R_sc : p.ck_S_sc)[so + (int64_t)(ww * IT + lane) * (DV / 32)] = lane ? sc[IT - 1] : sc[0];
   };
 
-  constexpr int KL_STEPS = Q16 ? KS_STEPS : 1;
   typedef Mfma<XT> MX;
   constexpr int XS = kChunk / MX::kStep;   // k-steps over the chunk's tokens
   // the fragments of a token tile's JT column blocks
@@ -992,7 +991,6 @@ __global__ __launch_bounds__(2 * kThreads, 2) void fwd_scan_ws_kernel(OpParams p
   MatFrags<XT> aTS, aMG, aMP, aTR, aMR;
   typename MX::frag kt[IT * XS];   // this wave's state rows of K^T
   for (int c = 0; c < nch; ++c) {
-    const int len = chunk_len(c);
     const bool more = c + 1 < nch;
     // this lane's four tokens of gate vector k
     auto gate4 = [&](int k) { return *reinterpret_cast<const floatx4*>(gvec(c, k) + 16 * ww + acc_row(0)); };
