@@ -194,12 +194,12 @@ __global__ __launch_bounds__(kThreads) void prep_kernel(OpParams p) {
     const bool valid = t < ci.len;
     float la = 0.f;
     if (valid) la = pre ? log_decay_preact(p.decay_param[h], graw_a + p.decay_param[H + h]) : log_decay(graw_a);
-    const float cum = wave_inclusive_scan(la), prev = __shfl_up(cum, 1, 64);
+    const float cum = wave_inclusive_scan(la);
     const float wb = valid ? (pre ? sigmoid_f(graw_b) : graw_b) : 0.f;
     if (tid < 64) {
       gs[t] = cum;
       bt[t] = wb;
-      gsp[t] = t > 0 ? prev : 0.f;   // the scans' own g_{t-1}
+      gsp[t] = cum - la;   // within cum's last place of g_{t-1}, as la has a floor
     } else {
       gr[t] = cum;
       gm[t] = wb;
