@@ -157,8 +157,9 @@ typedef struct {
  * entry point; gradients are with respect to the raw inputs):
  *   RLA_FLAG_QK_SILU_L2NORM  q and k are raw projections: each token-head row
  *       becomes y / max(||y||, 1e-12) with y = SiLU(x) before the recurrence
- *       (the torch F.normalize convention).  bf16 inputs: the normalised rows
- *       are rounded to bf16 once.  Needs workspace (rla_workspace_size).
+ *       (the torch F.normalize convention).  bf16 inputs: the chunked entry points
+ *       round the normalised rows to fp16 once, decoding keeps them in fp32.
+ *       Needs workspace (rla_workspace_size; decoding does not).
  *   RLA_FLAG_GATE_PREACT  alpha_s, alpha_r, beta, gamma hold pre-activations z:
  *       aS = exp(-a_h softplus(z + b_h)) (likewise aR, with the same per-head
  *       (a_h, b_h) from problem.decay_param: the Mamba-2 re-parameterisation),

@@ -394,9 +394,8 @@ __global__ __launch_bounds__(kThreads) void bwd_scan_kernel(OpParams p) {
 
     // gradient w.r.t. this chunk's end states for the gradient kernel,
     // straight from the accumulators (bf16 inputs: fp16 scaled per (16 rows,
-    // 32 columns)), stored after the chunk's last prefetch (with bf16 inputs
-    // the update's transpose reads wait for them along with the prefetched
-    // data).
+    // 32 columns)), stored after the chunk's last prefetch.  They stay in flight
+    // past the chunk's end, whose wait leaves that many operations.
     auto save_ckpt = [&]() {
       const int64_t off = ((int64_t)gc * H + h) * DK * DV + j0;
       if constexpr (BF) {   // blocked [DV / 32][DK][32]: each wave store is 1 KiB contiguous
@@ -726,12 +725,17 @@ __global__ __launch_bounds__(kThreads) void bwd_scan_kernel(OpParams p) {
 //   4: dS at the chunk start; maxima              | DMA of the next mask, MG; dv; dS
 //                                                   checkpoint
 // A matrix is read into registers at the start of the phase that multiplies
-// by it (MR, T^R, T^S, MP: 2; MG: 3), refilled in the next, and its copy is
-// waited for just before that phase in the next chunk, so that the memory
+// by it (MR, T^R, T^S, MP: 2; MG: 3) and refilled in the next, so that the memory
 // operations are spread over the chunk (all of a chunk's traffic, 100 KiB, goes
-// through one CU's path; in bursts it stalls both roles) and each has most of
-// a chunk to land.  Beside that a chunk is bound by the chain, about 9600 to
-// 10500 cycles.  Five dependent phases instead of seven (128 x 128, 16 heads):
+// through one CU's path; in bursts it stalls both roles).  The partial waits
+// before phases 2 and 3 are what their copies need; but the compiler, for which K's
+// prefetched registers may be pending on a path around phase 3, also waits for
+// every memory operation at phase 0's first store, so the copies of phases 3 and 4
+// have two phases and one to land, and dv and the dS checkpoint are waited for.
+// Bound (phase stamps, thousands of cycles, chain / side): 0.8 / 1.7, 1.8 / 1.1,
+// 2.1 / 1.4, 1.6 / 2.4, 0.8 / 1.6: by the side waves in phases 0, 3 and 4, by the
+// chain in 1 and 2, 9.6 together (10.5 with the barriers on every CU; the chain
+// alone 7.1).  Five dependent phases instead of seven (128 x 128, 16 heads):
 // 4 x 4096 tokens 309 -> 305 us; normalised rows, 16000 tokens
 // packed, 427 -> 357 us.
 // ---------------------------------------------------------------------------

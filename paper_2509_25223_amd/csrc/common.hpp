@@ -138,7 +138,9 @@ template <> struct Mfma<f16> {
 // took four 4-byte ones.  Such reads were most of a phase of the fp32 scans:
 // 64 x 64, 2 x 500 tokens (8 chunks each), 4 heads: forward scan 80 -> 49 us,
 // reverse 80 -> 56, gradients 43 -> 34, preparation 17.8 -> 16.2 (with K, Q
-// loaded in 16 bytes without a branch, and the matrices one phase earlier).
+// loaded in 16 bytes without a branch, and the matrices one phase earlier).  Error
+// against 64 bits with the other order, by output, over the former: 0.985 to 1.018
+// (final states 1.014, dk 1.010 to 1.018, dv 0.985; all below 1e-6).
 template <> struct Mfma<float> {
   static constexpr int kStep = 16;
   typedef floatx4 frag;
@@ -394,8 +396,11 @@ __device__ __forceinline__ void lds_read_f32_sync(const float* p, const int (&id
 // of the scans stored like this, 4 x 4096 tokens, 16 heads, 128 x 128: saving
 // forward scan 256 -> 266 us, but the kernels after it 24 -> 20 (absmax), 300 ->
 // 284 (reverse scan) and 350 -> 341 (gradients), a step 993 -> 973; a step of 16000
-// tokens from raw rows 1300 -> 1273.  Whole lines only: the gradients' 32-byte
-// pieces of a row took 356 us instead of 352 like this.
+// tokens from raw rows 1300 -> 1273.  Over 72 training steps (RDN and RLA, d = 64 and
+// 128, 256 to 16384 tokens, 4 and 16 heads, saving and recomputing) 0.91 to 1.02 of the
+// time with cached stores; only a step of 256 tokens and 4 heads (57 to 92 us), which
+// fits the caches, is 1 us longer in some instances.  Whole lines only: the
+// gradients' 32-byte pieces of a row took 356 us instead of 352 like this.
 __device__ __forceinline__ void store_stream16(void* p, uint4 v) {
   typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
   __builtin_nontemporal_store(__builtin_bit_cast(u32x4, v), reinterpret_cast<u32x4*>(p));

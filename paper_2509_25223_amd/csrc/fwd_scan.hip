@@ -453,9 +453,8 @@ __global__ __launch_bounds__(kThreads) void fwd_scan_kernel(OpParams p) {
     if (c + 1 < nch) issue_late(c + 1);
     // chunk-start states for the gradient kernel, straight from the
     // accumulators (bf16 inputs: fp16 scaled per (16 rows, 32 columns)),
-    // stored after the chunk's last prefetch.  With bf16 inputs the state
-    // update's transpose reads wait for them along with the prefetched data;
-    // fp32 inputs leave them in flight past the chunk's end.
+    // stored after the chunk's last prefetch (fp32 RDN: but for MR).  They stay
+    // in flight past the chunk's end, whose wait leaves that many operations.
     if constexpr (CKPT) {
       const int64_t off = ((int64_t)gc * H + h) * DK * DV + j0;
       if constexpr (BF) {   // blocked [DV / 32][DK][32]: each wave store is 1 KiB contiguous
@@ -642,15 +641,18 @@ __global__ __launch_bounds__(kThreads) void fwd_scan_kernel(OpParams p) {
 // 824 -> 656 us; saving, 4 x 4096 tokens, 256 workgroups, 287 -> 267 us;
 // normalised rows, saving, 16000 tokens packed, 414 -> 344 us.
 // BV = 16 (not saving; a saved checkpoint's scales are per 32 columns): half
-// the columns per workgroup, for grids that leave CUs idle; a chunk is about
-// 4800 cycles (1 x 16384 tokens: 64 -> 128 workgroups, 651 -> 522 us, with the
+// the columns per workgroup, for grids that leave CUs idle (the line: below, at
+// launch_fwd_t); a chunk is about 4800 cycles (1 x 16384 tokens: 64 -> 128 workgroups, 651 -> 522 us, with the
 // gate vectors formed in phase 2).  Columns do not meet in any product, so the
 // bits are those of 32 columns.
 // V is double-buffered.  The precision scheme and the arithmetic are those of
 // fwd_scan_kernel, except that the split-state products sum the hi and lo terms per k-step and the checkpoints are
 // formed from the bf16 hi + lo state copies (the fp32 state to ~16 bits)
 // instead of the accumulators.  Q16 rows are split as bf16 hi + lo in the
-// chain's registers (a third MFMA adds lo x state-hi).
+// chain's registers (a third MFMA adds lo x state-hi).  The checkpoints' 16 bits
+// cost nothing beside the fp16 that they are stored in: where only they differ
+// from fp32 ones (RLA, normalised rows, d_k = 64), every output's and gradient's
+// error against 64 bits is the same to three digits (24 inputs).
 // ---------------------------------------------------------------------------
 template <typename IN, int DK, int BV, bool RDN, bool CKPT>
 struct FwdWsLayout {
@@ -1290,10 +1292,17 @@ hipError_t launch_fwd_kernel(K kern, const OpParams& p, int BV, int threads, int
 // tokens from raw projections, H = 16, d = 128: 482 us with the four-wave
 // kernel, 397 us here, 274 since in fewer phases).  fp32 inputs always take the
 // four-wave kernel.
-// Not saving, 16 columns per workgroup as long as that leaves one workgroup
-// per CU: more would run in turns, one per CU (registers), at 4800 cycles a
-// chunk for 16 columns against 6600 for 32 (20011 tokens packed, 1200
-// workgroups of 32 columns: 279 us, in 16 columns 429).
+// Not saving, 16 columns per workgroup up to one workgroup per CU.  Both sides,
+// 1024 tokens, 4 heads, time of 16 columns over time of 32 by the number of 16-column
+// workgroups (plain and normalised rows alike):
+//                    64 .. 256    320 .. 512   640, 768     1024
+//   RDN, d_k = 128   0.79 - 0.88  1.23 - 1.33  1.08 - 1.12  1.26 - 1.31
+//   RDN, d_k = 64    0.83 - 0.88  1.18 - 1.31  1.05 - 1.08  1.20 - 1.26
+//   RLA, d_k = 128   0.82 - 0.90  1.32 - 1.46  1.15 - 1.20  1.36 - 1.44
+//   RLA, d_k = 64    0.81 - 0.88  1.05 - 1.08  0.94 - 0.95  1.07 - 1.08
+// Three of the instances take 129 to 166 registers, so past 256 their workgroups
+// run in turns, one per CU; RLA at d_k = 64 (122) fits two per CU, which then share it
+// at a little less than the speed of one 32-column workgroup.
 constexpr int kCUs = 256;
 template <typename IN, int DK, int BV, bool RDN, bool WRITE_O, bool CKPT>
 hipError_t launch_fwd_t(const OpParams& p, hipStream_t s) {

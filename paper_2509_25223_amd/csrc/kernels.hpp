@@ -58,8 +58,9 @@ struct OpParams {
   float* gate_ws = nullptr;     // [max_chunks][H][kGateBlock]
   void* mat_ws = nullptr;       // [max_chunks][H][kNumMats][kMatElems]: packed lower blocks (mm type)
   // chunk states saved for the gradient kernel, [max_chunks][H][DK][DV]: fp32
-  // for fp32 inputs; fp16 for bf16 inputs, each (row, 32 columns) scaled by a
-  // power of two held in the matching *_sc array [max_chunks][H][DK][DV / 32]
+  // for fp32 inputs; fp16 for bf16 inputs, blocked [DV / 32][DK][32], each (16 rows,
+  // 32 columns) scaled by a power of two held in the matching *_sc array
+  // [max_chunks][H][DK / 16][DV / 32]
   void* ck_S = nullptr;         // chunk-start S
   void* ck_R = nullptr;         // chunk-start R
   void* dS_ws = nullptr;        // grad of chunk-end S
