@@ -49,12 +49,12 @@ PEAK_HBM_GBS = 8000.0
 # numbers and commands are in profiles/), keyed by a hash of the kernel's
 # sources: a kernel changed since its counters were taken reports null.
 MEASURED_TRAFFIC = {
-    "prep": ("ca8a14450e1e9bfa", ('prep.hip', 'common.hpp', 'kernels.hpp'), 168134929, 109707264),
-    "grad_absmax": ("f88e1e130560045b", ('grad_scale.hip', 'common.hpp', 'kernels.hpp'), 67196085, 131349),
-    "bwd_scan": ("2667437b07d777b7", ('bwd_scan.hip', 'common.hpp', 'kernels.hpp'), 344385488, 613419008),
-    "bwd_grad": ("3a7f191e1eeca1cb", ('bwd_grad.hip', 'common.hpp', 'kernels.hpp'), 1232537094, 302493493),
-    "fwd_scan": ("54288ce06c30316e", ('fwd_scan.hip', 'common.hpp', 'kernels.hpp'), 310697625, 638591360),
-    "decode": ("a6d19635132fd623", ('decode.hip', 'common.hpp', 'kernels.hpp'), 542746720, 539558630),
+    "prep": ("c7dcbda285822420", ('prep.hip', 'common.hpp', 'kernels.hpp'), 168144931, 109707264),
+    "grad_absmax": ("659133779d6d4ab4", ('grad_scale.hip', 'common.hpp', 'kernels.hpp'), 67196195, 131493),
+    "bwd_scan": ("9174461dd67faf2c", ('bwd_scan.hip', 'common.hpp', 'kernels.hpp'), 344386247, 613419008),
+    "bwd_grad": ("e0865ddb40f92916", ('bwd_grad.hip', 'common.hpp', 'kernels.hpp'), 1232539096, 302548059),
+    "fwd_scan": ("9e83376062f9491d", ('fwd_scan.hip', 'common.hpp', 'kernels.hpp'), 310691136, 638595379),
+    "decode": ("14c403f06ed979e9", ('decode.hip', 'common.hpp', 'kernels.hpp'), 542749435, 539281715),
 }
 
 

@@ -1,7 +1,7 @@
 """The in-operator normalisation at row counts around its blocks (a workgroup
-takes 32 rows of 128, 64 of 64 bf16 values, in sets of 4 to 16 rows a wave),
-with a zero row (below the norm's floor) first and last, against the fp64
-oracle."""
+takes 32 rows of 128 bf16 or 64 fp32 values, 64 of 64 bf16 values, in two sets
+of 4 or 8 rows a wave), with a zero row (below the norm's floor) first and last,
+against the fp64 oracle."""
 import numpy as np
 import pytest
 
