@@ -49,12 +49,12 @@ PEAK_HBM_GBS = 8000.0
 # numbers and commands are in profiles/), keyed by a hash of the kernel's
 # sources: a kernel changed since its counters were taken reports null.
 MEASURED_TRAFFIC = {
-    "prep": ("c7dcbda285822420", ('prep.hip', 'common.hpp', 'kernels.hpp'), 168144931, 109707264),
-    "grad_absmax": ("659133779d6d4ab4", ('grad_scale.hip', 'common.hpp', 'kernels.hpp'), 67196195, 131493),
-    "bwd_scan": ("9174461dd67faf2c", ('bwd_scan.hip', 'common.hpp', 'kernels.hpp'), 344386247, 613419008),
-    "bwd_grad": ("e0865ddb40f92916", ('bwd_grad.hip', 'common.hpp', 'kernels.hpp'), 1232539096, 302548059),
-    "fwd_scan": ("9e83376062f9491d", ('fwd_scan.hip', 'common.hpp', 'kernels.hpp'), 310691136, 638595379),
-    "decode": ("14c403f06ed979e9", ('decode.hip', 'common.hpp', 'kernels.hpp'), 542749435, 539281715),
+    "prep": ("67ad2382af59e823", ('prep.hip', 'common.hpp', 'kernels.hpp'), 168145378, 109707264),
+    "grad_absmax": ("8b9dcc5face9dad9", ('grad_scale.hip', 'common.hpp', 'kernels.hpp'), 67196608, 131429),
+    "bwd_scan": ("9b5fd94d890cddc5", ('bwd_scan.hip', 'common.hpp', 'kernels.hpp'), 344386689, 613419029),
+    "bwd_grad": ("c71b25d8eacea658", ('bwd_grad.hip', 'common.hpp', 'kernels.hpp'), 1232578007, 302671029),
+    "fwd_scan": ("aa5ade39eab82778", ('fwd_scan.hip', 'common.hpp', 'kernels.hpp'), 310715265, 638600128),
+    "decode": ("acaf48eb9f4ae85d", ('decode.hip', 'common.hpp', 'kernels.hpp'), 542750210, 539234893),
 }
 
 

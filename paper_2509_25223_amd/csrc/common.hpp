@@ -988,13 +988,6 @@ __device__ __forceinline__ uint32_t mask_at(const uint8_t* lds, int j, int t0) {
   return *reinterpret_cast<const uint32_t*>(lds + j * kChunk + (((t0 >> 4) ^ ((j >> 2) & 3)) << 4) + (t0 & 15));
 }
 
-// Unsigned maxima of the two 16-bit halves.
-__device__ __forceinline__ uint32_t pk_max_u16(uint32_t a, uint32_t b) {
-  typedef u16 u16x2 __attribute__((ext_vector_type(2)));
-  const u16x2 x = __builtin_bit_cast(u16x2, a), y = __builtin_bit_cast(u16x2, b);
-  return __builtin_bit_cast(uint32_t, __builtin_elementwise_max(x, y));
-}
-
 // Instruction-scheduling fence: nothing moves across it.
 __device__ __forceinline__ void sched_fence() { __builtin_amdgcn_sched_barrier(0); }
 

@@ -611,8 +611,7 @@ __global__ __launch_bounds__(kThreads) void fwd_scan_kernel(OpParams p) {
 //     fwd_scan_kernel), loading only their own K and Q rows and storing
 //     nothing to HBM: o goes to LDS;
 //   side waves (4-7): all other HBM traffic — the chunk-start checkpoints
-//     (formed from the LDS state copies), the U, U^R, r blocks, the clip
-//     mask and o, and the staging of the next chunk (LDS-DMA of V and the
+//     (from the chain's stage), the U, U^R, r blocks, the clip mask and o, and the staging of the next chunk (LDS-DMA of V and the
 //     matrices, the gate values) — so it overlaps the chain instead of
 //     stalling it.
 // Per chunk (phase: chain waves | side waves):
@@ -646,13 +645,18 @@ __global__ __launch_bounds__(kThreads) void fwd_scan_kernel(OpParams p) {
 // gate vectors formed in phase 2).  Columns do not meet in any product, so the
 // bits are those of 32 columns.
 // V is double-buffered.  The precision scheme and the arithmetic are those of
-// fwd_scan_kernel, except that the split-state products sum the hi and lo terms per k-step and the checkpoints are
-// formed from the bf16 hi + lo state copies (the fp32 state to ~16 bits)
-// instead of the accumulators.  Q16 rows are split as bf16 hi + lo in the
-// chain's registers (a third MFMA adds lo x state-hi).  The checkpoints' 16 bits
-// cost nothing beside the fp16 that they are stored in: where only they differ
-// from fp32 ones (RLA, normalised rows, d_k = 64), every output's and gradient's
-// error against 64 bits is the same to three digits (24 inputs).
+// fwd_scan_kernel, except that the split-state products sum the hi and lo terms
+// per k-step.  Q16 rows are split as bf16 hi + lo in the chain's registers (a
+// third MFMA adds lo x state-hi).
+// The chunk-start checkpoints come from the fp32 accumulators through a stage in
+// LDS: at d_k = 128 the chain stores the fp32 state beside its split copies and the
+// side waves scale and convert it; at d_k = 64 (one 16-row tile of a state per wave)
+// the chain does.  Saving forward scan, 16 heads, against forming them from the split
+// copies (16 bits of the state): 128 x 128, packed 16000 normalised rows 340 -> 343 us,
+// 4 x 4096 tokens 268 -> 269; 64 x 64, 4 x 4096 tokens 152 -> 153, RLA 155 -> 140 (the
+// fp32 stage: 156, 155; converting in the chain at 128: 353, 269).  The split copies'
+// 16 bits made the error of the decay parameters' gradients, sums over every token,
+// 1 % larger (RLA, normalised rows, 64 x 64; 24 inputs); from fp32 it is what it was.
 // ---------------------------------------------------------------------------
 template <typename IN, int DK, int BV, bool RDN, bool CKPT>
 struct FwdWsLayout {
@@ -680,7 +684,16 @@ struct FwdWsLayout {
   // 4-byte gathers of one token's 4 columns in distinct banks)
   static constexpr int kOstLd = kChunk + 4;
   static constexpr int kOst = kZero + 16;
-  static constexpr int kBytes = kOst + BV * kOstLd * 4;
+  // S, R for the checkpoints: in fp32, column-major [BV][kCkLd] (padded like
+  // o's), or (kPack) in fp16, each 16-row tile divided by its power of two
+  // ([BV][DK] padded rows), with the tile scales [2][DK / 16] behind
+  static constexpr bool kPack = DK == 64;
+  typedef PadRows<XT, DK, 8> TCK;
+  static constexpr int kCkLd = DK + 4;
+  static constexpr int kCk = kOst + BV * kOstLd * 4;
+  static constexpr int kCkBytes = !CKPT ? 0 : kPack ? BV * TCK::kRowB : BV * kCkLd * 4;
+  static constexpr int kCkSc = kCk + 2 * kCkBytes;
+  static constexpr int kBytes = kCkSc + (CKPT && kPack ? 2 * (DK / 16) * 4 : 0);
   static_assert(sizeof(IN) == 2 && (BV == 32 || (BV == 16 && !CKPT)), "bf16; saved blocks have 32 columns");
   static_assert(kBytes <= (BV == 16 ? 80 : 160) * 1024, "forward scan LDS: one or two workgroups per CU");
   // RDN: T^S, MG, MP, T^R, MR; RLA: MG, MP, MR
@@ -721,6 +734,8 @@ __global__ __launch_bounds__(2 * kThreads, 2) void fwd_scan_ws_kernel(OpParams p
   XT* Rst = reinterpret_cast<XT*>(smem + L::kRst);            // r (saving mode)
   uint8_t* Mst = reinterpret_cast<uint8_t*>(smem + L::kMst);  // clip mask (saving mode)
   float* graw = reinterpret_cast<float*>(smem + L::kGraw);     // prep's gate block
+  auto ckst = [&](int st) { return reinterpret_cast<float*>(smem + L::kCk + st * L::kCkBytes); };   // saving mode
+  float* ckscl = reinterpret_cast<float*>(smem + L::kCkSc);
 
   const int H = p.H, DV = p.DV, tid = threadIdx.x, lane = tid & 63;
   const int wu = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -762,11 +777,35 @@ __global__ __launch_bounds__(2 * kThreads, 2) void fwd_scan_ws_kernel(OpParams p
     load_acc_state<IT, JT>(Sacc, p.S0, state_off + j0, DV, ww * (DK / 4));
     load_acc_state<IT, JT>(Racc, p.R0, state_off + j0, DV, ww * (DK / 4));
   }
-  auto write_state_copies = [&](const floatx4 (&acc)[IT][JT], IN* hi, IN* lo) {
+  // chain: state X's (st: 0 = S, 1 = R) split copies and, saving without
+  // kPack, its fp32 stage (tile by tile with the copies: behind them all it took
+  // 199 us instead of 193, RLA 1 x 4096 tokens, 16 heads, 128 x 128)
+  auto write_state_copies = [&](const floatx4 (&acc)[IT][JT], int st) {
 #pragma unroll
     for (int it = 0; it < IT; ++it)
 #pragma unroll
-      for (int jt = 0; jt < JT; ++jt) store_state_copy<TSC>(hi, lo, jt * 16, ww * (DK / 4) + it * 16, acc[it][jt]);
+      for (int jt = 0; jt < JT; ++jt) {
+        store_state_copy<TSC>(st ? Rhi : Shi, st ? Rlo : Slo, jt * 16, ww * (DK / 4) + it * 16, acc[it][jt]);
+        if constexpr (CKPT && !L::kPack)   // this lane's 4 rows of its column, one store
+          *reinterpret_cast<floatx4*>(ckst(st) + (jt * 16 + acc_col()) * L::kCkLd + ww * (DK / 4) + it * 16 + acc_row(0)) =
+              acc[it][jt];
+      }
+  };
+  // chain, saving with kPack: state X into its fp16 stage
+  auto stage_ckpt = [&](const floatx4 (&acc)[IT][JT], int st) {
+    if constexpr (CKPT && L::kPack) {
+      uint32_t m[IT];
+      state_tile_absmax<IT>(acc, m);
+#pragma unroll
+      for (int it = 0; it < IT; ++it) {
+        const int ex = pow2_scale_exp(m[it]);
+        const float f = exp2_int(-ex);
+#pragma unroll
+        for (int jt = 0; jt < JT; ++jt)
+          store_acc_tile<typename L::TCK>(ckst(st), jt * 16, ww * (DK / 4) + 16 * it, acc[it][jt] * f);
+        ckscl[st * (DK / 16) + ww * IT + it] = exp2_int(ex);   // every lane: the wave-uniform value
+      }
+    }
   };
   // Global addresses are a chunk's uniform base plus a 32-bit lane offset
   // that does not change from chunk to chunk, so the memory instructions take
@@ -847,56 +886,52 @@ __global__ __launch_bounds__(2 * kThreads, 2) void fwd_scan_ws_kernel(OpParams p
           lds_read16_sync(Mst + (e >> 2) * L::kMstLd + (e & 3) * 16);
     }
   };
-  // side waves: chunk-start state X (st: 0 = S, 1 = R) from its copies
-  // (hi + lo), rows 32 ww .. 32 ww + 31, fp16 blocked [DV / 32][DK][32] with
-  // one power-of-two scale per 16-row tile.  Transpose reads of the copies
-  // give lane (g, i) state row t0 + i at columns 8 g .. 8 g + 7, so one
-  // 16-row tile is one 1 KiB store; the wave's two tile scales leave in one
-  // store (lane l writes tile l's)
+  // side waves: chunk-start state X from its stage, rows ww DK / 4 .., fp16
+  // blocked [DV / 32][DK][32] with one power-of-two scale per 16-row tile.
+  // Transpose reads (fp32: eight reads) give lane (g, i) state row t0 + i at
+  // columns 8 g .. 8 g + 7, so one 16-row tile is one 1 KiB store; the wave's
+  // tile scales leave in one store (lane l writes tile l's)
   auto store_ckpt = [&](int c, int st) {
     const int64_t gc = si.chunk0 + c;
-    const IN* hi = st ? Rhi : Shi;
-    const IN* lo = st ? Rlo : Slo;
     f16* dst = reinterpret_cast<f16*>(st ? p.ck_R : p.ck_S) + ((int64_t)gc * H + h) * DK * DV + (int64_t)j0 * DK;
-    float sc[IT];
-    uint4 xh[IT], xl[IT];
-    {
-      const IN* src[2 * IT];
-      int t0[2 * IT];
-      uint4 x[2 * IT];
-#pragma unroll
-      for (int it = 0; it < IT; ++it) {
-        src[2 * it] = hi;
-        src[2 * it + 1] = lo;
-        t0[2 * it] = t0[2 * it + 1] = ww * (DK / 4) + 16 * it;
-      }
-      tile_token_rows16_sync<TSC>(src, t0, x);
-#pragma unroll
-      for (int it = 0; it < IT; ++it) {
-        xh[it] = x[2 * it];
-        xl[it] = x[2 * it + 1];
-      }
-    }
-    // the tile's scale from its hi parts: |hi + lo| <= (1 + 2^-8) |hi|, so the
-    // stored magnitudes stay below 2^14 (1 + 2^-8)
-#pragma unroll
-    for (int it = 0; it < IT; ++it) {
-      const uint32_t m = pk_max_u16(pk_max_u16(xh[it].x & 0x7FFF7FFFu, xh[it].y & 0x7FFF7FFFu),
-                                    pk_max_u16(xh[it].z & 0x7FFF7FFFu, xh[it].w & 0x7FFF7FFFu));
-      const int ex = pow2_scale_exp(wave_absmax_bits(max(m << 16, m & 0xFFFF0000u)));
-      const uint32_t f = __float_as_uint(exp2_int(-ex));   // a power of two: its bf16 bits are the upper half
-      const bf16x2 f0 = __builtin_bit_cast(bf16x2, f >> 16), f1 = __builtin_bit_cast(bf16x2, f);
-      // (hi + lo) f of an element: two bf16 dot products (exact but for the fp32 sum)
-      auto scaled = [&](uint32_t h2, uint32_t l2) {
-        const bf16x2 h = __builtin_bit_cast(bf16x2, h2), l = __builtin_bit_cast(bf16x2, l2);
-        const float v0 = __builtin_amdgcn_fdot2_f32_bf16(h, f0, __builtin_amdgcn_fdot2_f32_bf16(l, f0, 0.f, false), false);
-        const float v1 = __builtin_amdgcn_fdot2_f32_bf16(h, f1, __builtin_amdgcn_fdot2_f32_bf16(l, f1, 0.f, false), false);
-        return cvt_pk_f16(v0, v1);
-      };
-      const uint4 v = {scaled(xh[it].x, xl[it].x), scaled(xh[it].y, xl[it].y), scaled(xh[it].z, xl[it].z),
-                       scaled(xh[it].w, xl[it].w)};
+    auto put = [&](int it, uint4 v) {
       store_stream16(dst + (uint32_t)((ww * (DK / 4) + 16 * it + (lane & 15)) * 32 + 8 * (lane >> 4)), v);
-      sc[it] = exp2_int(ex);
+    };
+    float sc[IT];
+    if constexpr (L::kPack) {
+      uint4 v[IT];
+      float* src[IT];
+      int t0[IT], idx[IT];
+#pragma unroll
+      for (int it = 0; it < IT; ++it) {
+        src[it] = ckst(st);
+        t0[it] = ww * (DK / 4) + 16 * it;
+        idx[it] = st * (DK / 16) + ww * IT + it;
+      }
+      tile_token_rows16_sync<typename L::TCK>(src, t0, v);
+      lds_read_f32_sync<IT>(ckscl, idx, sc);
+#pragma unroll
+      for (int it = 0; it < IT; ++it) put(it, v[it]);
+    } else {
+      float x[8 * IT];
+      int idx[8 * IT];
+#pragma unroll
+      for (int k = 0; k < 8 * IT; ++k)
+        idx[k] = (8 * (lane >> 4) + (k & 7)) * L::kCkLd + ww * (DK / 4) + 16 * (k >> 3) + (lane & 15);
+      lds_read_f32_sync<8 * IT>(ckst(st), idx, x);
+#pragma unroll
+      for (int it = 0; it < IT; ++it) {
+        uint32_t m = 0;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) m = max(m, __float_as_uint(x[8 * it + e]) & 0x7FFFFFFFu);
+        const int ex = pow2_scale_exp(wave_absmax_bits(m));
+        const float f = exp2_int(-ex);
+        uint32_t u[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) u[e] = cvt_pk_f16(x[8 * it + 2 * e] * f, x[8 * it + 2 * e + 1] * f);
+        put(it, uint4{u[0], u[1], u[2], u[3]});
+        sc[it] = exp2_int(ex);
+      }
     }
     static_assert(IT <= 2, "one or two tiles per wave");
     const int64_t so = ((int64_t)gc * H + h) * (DK / 16) * (DV / 32) + j0 / 32;
@@ -984,8 +1019,9 @@ __global__ __launch_bounds__(2 * kThreads, 2) void fwd_scan_ws_kernel(OpParams p
     }
   }
   if constexpr (CH) {
-    write_state_copies(Sacc, Shi, Slo);
-    write_state_copies(Racc, Rhi, Rlo);
+    write_state_copies(Sacc, 0);
+    write_state_copies(Racc, 1);
+    if constexpr (RDN) stage_ckpt(Sacc, 0);
   }
   barrier_lds();
 
@@ -1084,6 +1120,8 @@ __global__ __launch_bounds__(2 * kThreads, 2) void fwd_scan_ws_kernel(OpParams p
       dlr = gate4(6);
       eS = gvec(c, 7)[0];
       eR = gvec(c, 7)[1];
+      if constexpr (!RDN) stage_ckpt(Sacc, 0);
+      stage_ckpt(Racc, 1);
     } else {
       if (more) issue_v(c + 1);
       if (c > 0) {
@@ -1224,7 +1262,7 @@ __global__ __launch_bounds__(2 * kThreads, 2) void fwd_scan_ws_kernel(OpParams p
           *reinterpret_cast<floatx4*>(ost + (jt * 16 + acc_col()) * L::kOstLd + 16 * ww + acc_row(0)) = ov;
         }
       }
-      write_state_copies(Sacc, Shi, Slo);
+      write_state_copies(Sacc, 0);
     } else {
       if (more) issue_s_mats(c + 1);   // in the chain's registers since phase 2
       if constexpr (CKPT) {
@@ -1240,8 +1278,9 @@ __global__ __launch_bounds__(2 * kThreads, 2) void fwd_scan_ws_kernel(OpParams p
     if constexpr (CH) {
       typename MX::frag fd[JT][XS];
       tok_frags(DURt, fd);
+      if constexpr (RDN) stage_ckpt(Sacc, 0);   // the next chunk's (RLA: in its phase 1)
       update_state(Racc, eR, kt, fd);
-      write_state_copies(Racc, Rhi, Rlo);
+      write_state_copies(Racc, 1);
     } else {
       if (more) {
         issue_r_mats(c + 1);   // in the chain's registers since phase 3
